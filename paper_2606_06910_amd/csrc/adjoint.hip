@@ -610,7 +610,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
                 char *dst[8] = {fdtd_ws(ctx, s.o_u[iu]), fdtd_ws(ctx, s.o_u[iu ^ 1])};
                 size_t len[8] = {a256(s.elems * s.esz), a256(s.elems * s.esz)};
                 for (int d = 0; d < 3; ++d) {
-                    dst[2 + 2 * d] = fdtd_ws(ctx, s.o_psi[d]);
+                    dst[2 + 2 * d] = fdtd_ws(ctx, fdtd_psi_off(s, d, iu));
                     dst[3 + 2 * d] = fdtd_ws(ctx, s.o_zeta[d]);
                     len[2 + 2 * d] = len[3 + 2 * d] = a256(s.psi_elems[d] * 4);
                 }
@@ -693,6 +693,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         fdtd_launch_copy_jobs(rjobs_d + ((size_t)k * 2 + ctx->iu) * 8 * nsh, 8 * nsh, maxck, st);
         fdtd_launch_set_int(stepc, s0, st);
         ctx->step = s0;
+        ctx->pend = 0;
         store_increment(b, 0, ctx->iu);   // e^{s0} = u^{s0} - u^{s0 - 1}
         for (int n = s0; n < s1; ++n) {
             fdtd_enqueue_step_shot(ctx, step_shot);
@@ -735,6 +736,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     }
     ctx->saving = was_saving;
     ctx->step = step_in;
+    ctx->pend = 0;
     ctx->iu = iu_in;
     ctx->ium1 = ium1_in;
     fdtd_launch_set_int(stepc, (int)step_in, st);

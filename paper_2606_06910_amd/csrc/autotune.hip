@@ -102,7 +102,7 @@ extern "C" int fdtd_autotune(fdtd_ctx *ctx, const char *cache_path) {
     const int zc_c[4] = {32, 64, 128, 4096};
     for (size_t i = 0; i < ctx->shots.size(); ++i) {
         ShotH &s = ctx->shots[i];
-        if (s.variant == FDTD_VARIANT_NAIVE) continue;
+        if (s.tile || s.variant == FDTD_VARIANT_NAIVE) continue;   // one shape each
         const std::string key = shape_key(ctx, s);
         auto it = cache.find(key);
         if (it != cache.end()) {

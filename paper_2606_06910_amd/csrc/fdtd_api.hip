@@ -216,6 +216,7 @@ template <> WorkItem idle_item(const std::vector<WorkItem> &sp) {
 template <> BandItem idle_item(const std::vector<BandItem> &sp) {
     return BandItem{sp.empty() ? 0 : sp[0].shot, 0, 1 << 20, 0, 0, 0, 0, 0};
 }
+template <> TileItem idle_item(const std::vector<TileItem> &) { return TileItem{-1, 0, 0, 0}; }
 template <typename W> static std::vector<W> xcd_order(const std::vector<W> &sp) {
     const int X = 8;
     size_t N = (sp.size() + X - 1) / X * X;
@@ -225,6 +226,20 @@ template <typename W> static std::vector<W> xcd_order(const std::vector<W> &sp) 
         size_t src = (w % X) * per + w / X;
         out[w] = src < sp.size() ? sp[src] : idle_item(sp);
     }
+    return out;
+}
+
+// The tile kernel's boxes dealt to the XCDs in pieces of consecutive boxes: each XCD
+// gets its share of the layers' boxes (which cost several times an interior one), and the boxes
+// that share halo planes and rows still run together.
+static std::vector<TileItem> xcd_deal(const std::vector<TileItem> &sp) {
+    const size_t X = 8, piece = std::min(std::max(sp.size() / 32, (size_t)8), kTilePiece);
+    std::vector<TileItem> out((sp.size() + X * piece - 1) / (X * piece) * X * piece, idle_item(sp));
+    for (size_t i = 0; i < sp.size(); ++i) {
+        const size_t c = i / piece;
+        out[(c / X * piece + i % piece) * X + c % X] = sp[i];
+    }
+    while (!out.empty() && out.back().flags < 0) out.pop_back();
     return out;
 }
 
@@ -265,6 +280,47 @@ static std::vector<WorkItem> shot_tiles(const ShotH &s, int shot, int ry, int zc
         for (int ty = 0; ty < nty; ++ty)
             for (int tx = 0; tx < ntx; ++tx) v.push_back(WorkItem{shot, tx, ty, zc});
     return v;
+}
+
+// boxes of the tile kernel, z fastest, then y: the boxes that share halo planes
+// and rows run close together on one XCD and find them in its L2
+static std::vector<TileItem> tile_boxes(const ShotH &s, int shot) {
+    // whether points c0 .. c0 + len - 1 (those below n) meet the band of an axis
+    auto meets = [&](int d, int c0, int len, int n) {
+        const int lo = s.Llo[d], hi = s.Lhi[d], c1 = std::min(c0 + len, n);
+        return (lo > 0 && c0 < lo + FDTD_R) || (hi > 0 && c1 > n - hi - FDTD_R);
+    };
+    std::vector<TileItem> v;
+    for (int x0 = 0; x0 < s.nx; x0 += TILE_X)
+        for (int y0 = 0; y0 < s.ny; y0 += TILE_Y)
+            for (int z0 = 0; z0 < s.nz; z0 += TILE_Z)
+                v.push_back(TileItem{shot | (meets(0, x0, TILE_X, s.nx) ? TILE_XB : 0) |
+                                         (meets(1, y0, TILE_Y, s.ny) ? TILE_YB : 0) |
+                                         (meets(2, z0, TILE_Z, s.nz) ? TILE_ZB : 0),
+                                     x0, y0, z0});
+    return v;
+}
+// Whether a shot takes the tile kernel (reported as the variant it replaces): the
+// automatic variant, no ghost faces, a z window of the kernel (TILE_Z + 8 planes)
+// that meets one z layer at most, every array of the shot within 2 GiB of its
+// first (32-bit offsets), and fewer points than the z-march needs to win.
+// Measured, us per step of a cube with 20-cell layers (10 below 128^3), the
+// other kernels against this one, FP32: 64^3 18.8 / 8.5, 96^3 33 / 11, 128^3
+// 57 / 23, 160^3 102 / 31, 200^3 138 / 58, 256^3 157 / 107, 300^3 226 / 179,
+// 384^3 350 / 313, 448^3 505 / 486; FP16: 256^3 158 / 115, 300^3 212 / 195,
+// 384^3 338 / 335, 448^3 476 / 507.
+static bool tile_rule(const ShotH &s) {
+    if (s.c.variant != FDTD_VARIANT_AUTO || s.gy || s.gz) return false;
+    if ((long)s.nx * s.ny * s.nz >= (s.esz == 4 ? kTileShot : kTileShot16)) return false;
+    if (s.Llo[2] > 0 && s.Lhi[2] > 0 && s.nz - s.Llo[2] - s.Lhi[2] < TILE_Z + 2 * FDTD_R) return false;
+    size_t b = (s.esz == 4 ? 2 : 3) * (s.elems * s.esz + 256) + s.elems * 4 + 256 + (size_t)3 * 4 * s.nmax * 4;
+    for (int d = 0; d < 3; ++d) b += 3 * (s.psi_elems[d] * 4 + 256);
+    return b < (size_t)1 << 31;
+}
+static size_t tile_capacity(const ShotH &s) {
+    return s.tile ? (size_t)((s.nx + TILE_X - 1) / TILE_X) * ((s.ny + TILE_Y - 1) / TILE_Y) *
+                            ((s.nz + TILE_Z - 1) / TILE_Z) + 8 * kTilePiece
+                  : 0;
 }
 
 static size_t work_capacity(const ShotH &s) {
@@ -351,6 +407,9 @@ static double d2_symbol_max() {
 // ---------------------------------------------------------------------------
 static char *wsp(fdtd_ctx *ctx, size_t off) { return ctx->ws + off; }
 
+// workspace offset of psi_d before the step whose u^n is in level buffer iu
+size_t fdtd_psi_off(const ShotH &s, int d, int iu) { return s.tile && iu == 1 ? s.o_psi2[d] : s.o_psi[d]; }
+
 static void *field_origin(fdtd_ctx *ctx, const ShotH &s, size_t off) {
     return wsp(ctx, off) + origin_elems(s) * s.esz;
 }
@@ -408,6 +467,7 @@ static void fill_desc(fdtd_ctx *ctx, int i) {
     D.ghost[1] = s.gy;
     D.ghost[2] = s.gz;
     D.fused = shot_fused(s) ? 1 : 0;
+    D.tile = s.tile ? 1 : 0;
     double cc = 0;
     for (int d = 0; d < 3; ++d) {
         const double h = s.c.h[d];
@@ -420,12 +480,55 @@ static void fill_desc(fdtd_ctx *ctx, int i) {
         cc += (kC2[0] + 2.0 * kC2[1]) / (h * h);
     }
     D.cc = (float)cc;
+    TileDesc &E = ctx->htile[i];
+    memset(&E, 0, sizeof E);
+    if (!s.tile) return;
+    auto rel = [&](size_t o) { return (uint32_t)(o - s.o_u[0]); };
+    E.tbase = wsp(ctx, s.o_u[0]);
+    for (int b = 0; b < 2; ++b) E.t_u[b] = rel(s.o_u[b]);
+    E.t_d = s.esz == 2 ? rel(s.o_d) : 0;
+    E.t_m = rel(s.o_m);
+    E.t_prof = rel(s.o_prof);
+    for (int d = 0; d < 3; ++d) {
+        E.t_psi[0][d] = rel(s.o_psi[d]);
+        E.t_psi[1][d] = rel(s.o_psi2[d]);
+        E.t_zeta[d] = rel(s.o_zeta[d]);
+        E.Llo[d] = D.Llo[d];
+        E.Lhi[d] = D.Lhi[d];
+    }
+    E.nx = D.nx;
+    E.ny = D.ny;
+    E.nz = D.nz;
+    E.P = D.P;
+    E.PY = D.PY;
+    E.S = D.S;
+    E.fy = D.fy;
+    E.fz = D.fz;
+    E.WX = D.WX;
+    E.SY = D.SY;
+    E.nmax = D.nmax;
+    E.cc = D.cc;
+    memcpy(E.w2, D.w2, sizeof E.w2);
+    memcpy(E.w1, D.w1, sizeof E.w1);
+    E.sx = D.sx;
+    E.sy = D.sy;
+    E.sz = D.sz;
+    E.src_nt = D.src_nt;
+    E.src_scale = D.src_scale;
+    E.wav = D.wav;
 }
 
 static int upload_desc(fdtd_ctx *ctx) {
     for (size_t i = 0; i < ctx->shots.size(); ++i) fill_desc(ctx, (int)i);
     HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), ctx->hdesc.data(), sizeof(DevShot) * ctx->hdesc.size(),
                                hipMemcpyHostToDevice, ctx->stream));
+    bool any_tile = false;
+    for (const ShotH &s : ctx->shots) any_tile = any_tile || s.tile;
+    if (any_tile) {
+        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_tdesc), ctx->htile.data(), sizeof(TileDesc) * ctx->htile.size(),
+                                   hipMemcpyHostToDevice, ctx->stream));
+        fdtd_clear_graphs(ctx);   // a launch over one tile shot carries its descriptor as it was
+    }
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return FDTD_OK;
 }
@@ -639,8 +742,27 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
     const int ext = R.ext;
     const int lo = shot < 0 ? 0 : shot, hi = shot < 0 ? (int)ctx->shots.size() : shot + 1;
     const bool grouped = shot < 0 && !ctx->groups.empty();
-    bool any_zm = false;
-    for (int i = lo; i < hi; ++i) any_zm = any_zm || ctx->shots[i].variant != FDTD_VARIANT_NAIVE;
+    bool any_zm = false, any_plain = false, any_tile = false;
+    for (int i = lo; i < hi; ++i) {
+        const ShotH &s = ctx->shots[i];
+        any_zm = any_zm || (!s.tile && s.variant != FDTD_VARIANT_NAIVE);
+        any_plain = any_plain || !s.tile;
+        any_tile = any_tile || s.tile;
+    }
+    // tile shots: their whole step in one launch; its extra blocks record the step
+    // before while no record launch has come in between (pend steps)
+    if (any_tile) {
+        hipEvent_t t0 = tic(ctx);
+        int nrec = 0;
+        for (int i = lo; i < hi; ++i)
+            if (ctx->pend > 0 && ctx->hdesc[i].traces) nrec = hi - lo;
+        const size_t off = shot < 0 ? ctx->o_tile_all : ctx->shots[shot].o_tile;
+        const TileStep A{R.iu, ctx->pend, shot < 0 ? ctx->ntile_all : ctx->shots[shot].ntile, lo};
+        fdtd_launch_tile(stor, dd, (const TileDesc *)wsp(ctx, ctx->o_tdesc), (const TileItem *)wsp(ctx, off), A, nrec, stepc,
+                         hi - lo == 1 ? &ctx->htile[lo] : nullptr, ctx->stream);
+        toc(ctx, 0, t0);
+    }
+    if (!any_plain) return;
     hipStream_t side = ctx->stream;
     if (any_zm && ctx->side && !ctx->timing) {
         (void)hipEventRecord(ctx->ev_fork, ctx->stream);
@@ -656,7 +778,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         } else {
             for (int i = lo; i < hi; ++i) {
                 const ShotH &s = ctx->shots[i];
-                if (s.variant == FDTD_VARIANT_NAIVE) continue;
+                if (s.tile || s.variant == FDTD_VARIANT_NAIVE) continue;
                 fdtd_launch_zmarch(stor, dd, (const WorkItem *)wsp(ctx, s.o_work), s.nwork, s.ry, s.zcols, R, s.zchunk,
                                    stepc,
                                    side);
@@ -670,6 +792,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
     long maxc = 0, maxl = 0;
     for (int i = lo; i < hi; ++i) {
         const ShotH &si = ctx->shots[i];
+        if (si.tile) continue;
         all_fused = all_fused && shot_fused(si);
         maxc = std::max(maxc, std::max(psi_count(si, 0, ext), psi_count(si, 2, ext)));
         if (si.LY > 0) maxl = std::max(maxl, (long)si.nx * (si.nz + (si.gz ? 2 * ext : 0)));
@@ -686,7 +809,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         } else {
             for (int i = lo; i < hi; ++i) {
                 const ShotH &s = ctx->shots[i];
-                if (s.variant == FDTD_VARIANT_NAIVE) continue;
+                if (s.tile || s.variant == FDTD_VARIANT_NAIVE) continue;
                 fdtd_launch_band(stor, dd, (const BandItem *)wsp(ctx, s.o_band), s.nband, R, kBandZ, stepc, ctx->band_ty,
                                  ctx->stream);
             }
@@ -695,7 +818,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
     }
     for (int i = lo; i < hi; ++i) {
         const ShotH &s = ctx->shots[i];
-        if (s.variant != FDTD_VARIANT_NAIVE) continue;
+        if (s.tile || s.variant != FDTD_VARIANT_NAIVE) continue;
         const int Ny = s.ny + (s.gy ? 2 * ext : 0), Nz = s.nz + (s.gz ? 2 * ext : 0);
         t0 = tic(ctx);
         fdtd_launch_naive(stor, dd, i, s.nx, Ny, Nz, R, stepc, ctx->stream);
@@ -705,6 +828,19 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         (void)hipEventRecord(ctx->ev_join, side);
         (void)hipStreamWaitEvent(ctx->stream, ctx->ev_join, 0);
     }
+}
+
+// Record the newest step's receivers and advance the device step counter by the
+// pending steps (those of tile shots enqueued since it last advanced).
+static void flush_steps(fdtd_ctx *ctx, int lo, int hi) {
+    if (ctx->pend == 0) return;
+    Roles R = plain_roles(ctx, 0);
+    R.iout = ctx->iu;   // the newest level
+    hipEvent_t t0 = tic(ctx);
+    fdtd_launch_record(ctx->storage, (const DevShot *)wsp(ctx, ctx->o_desc) + lo, hi - lo, R,
+                       (int *)wsp(ctx, ctx->o_stepc), ctx->pend, ctx->stream);
+    toc(ctx, 2, t0);
+    ctx->pend = 0;
 }
 
 // one step of one shot (shot >= 0) or of every shot (shot < 0)
@@ -724,10 +860,18 @@ static void enqueue_step(fdtd_ctx *ctx, int shot) {
     const int ext = ghost_ext(ctx, n);
     const DevShot *dd = (const DevShot *)wsp(ctx, ctx->o_desc);
     const Roles R = plain_roles(ctx, ext);
+    // steps of tile shots alone need no record launch of their own: the next
+    // step's launch records them, and flush_steps the last one
+    bool chain = true;
+    for (int i = lo; i < hi; ++i) chain = chain && ctx->shots[i].tile;
     enqueue_psi_update(ctx, shot, R);
-    hipEvent_t t0 = tic(ctx);
-    fdtd_launch_record(ctx->storage, dd + lo, hi - lo, R, (int *)wsp(ctx, ctx->o_stepc), ctx->stream);
-    toc(ctx, 2, t0);
+    if (chain) {
+        ++ctx->pend;
+    } else {
+        hipEvent_t t0 = tic(ctx);
+        fdtd_launch_record(ctx->storage, dd + lo, hi - lo, R, (int *)wsp(ctx, ctx->o_stepc), 1, ctx->stream);
+        toc(ctx, 2, t0);
+    }
     std::swap(ctx->iu, ctx->ium1);
     ctx->step = n + 1;
 }
@@ -780,7 +924,7 @@ static void enqueue_tblock(fdtd_ctx *ctx) {
         }
         enqueue_psi_update(ctx, 0, R);
         t0 = tic(ctx);
-        fdtd_launch_record(ctx->storage, dd, 1, R, stepc, ctx->stream);
+        fdtd_launch_record(ctx->storage, dd, 1, R, stepc, 1, ctx->stream);
         toc(ctx, 2, t0);
     }
     ctx->iu = Lv[K + 1];
@@ -817,6 +961,7 @@ static int enqueue_steps(fdtd_ctx *ctx, int nsteps) {
             ++scans;
         }
     }
+    flush_steps(ctx, 0, (int)ctx->shots.size());
     return scans;
 }
 
@@ -863,7 +1008,7 @@ static void copy_state(fdtd_ctx *ctx, int i, char *ck, bool save) {
     }
     for (int d = 0; d < 3; ++d) {
         size_t pb = s.psi_elems[d] * 4;
-        char *arr[2] = {wsp(ctx, s.o_psi[d]), wsp(ctx, s.o_zeta[d])};
+        char *arr[2] = {wsp(ctx, fdtd_psi_off(s, d, ctx->iu)), wsp(ctx, s.o_zeta[d])};
         for (int k = 0; k < 2; ++k) {
             if (pb) {
                 if (save) (void)hipMemcpyAsync(ck + off, arr[k], pb, hipMemcpyDeviceToDevice, ctx->stream);
@@ -877,6 +1022,60 @@ static void copy_state(fdtd_ctx *ctx, int i, char *ck, bool save) {
 static void save_checkpoint(fdtd_ctx *ctx, int i, int k) {
     ShotH &s = ctx->shots[i];
     copy_state(ctx, i, s.ck_buf + (size_t)k * fdtd_state_bytes(s), true);
+}
+
+// workspace layout
+static void layout(fdtd_ctx *ctx) {
+    const size_t nshots = ctx->shots.size();
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        size_t o = off;
+        off += align256(bytes);
+        return o;
+    };
+    ctx->o_stepc = take(256);
+    ctx->o_scratch = take(256);
+    ctx->o_desc = take(sizeof(DevShot) * nshots);
+    size_t cap_all = 0;
+    for (auto &s : ctx->shots) cap_all += work_capacity(s) + 8;
+    ctx->o_work_all = take(sizeof(WorkItem) * cap_all);
+    size_t band_all = 0;
+    for (auto &s : ctx->shots) band_all += band_capacity(s);
+    ctx->o_band_all = take(sizeof(BandItem) * band_all);
+    for (auto &s : ctx->shots) {
+        s.o_u[0] = take(s.elems * s.esz);
+        s.o_u[1] = take(s.elems * s.esz);
+        if (s.tb_bufs) {
+            s.o_u[2] = take(s.elems * s.esz);
+            s.o_u[3] = take(s.elems * s.esz);
+            s.o_tbwork = take(sizeof(WorkItem) * tblock_capacity(s));
+            s.o_reczs = take(sizeof(int) * (size_t)(s.nz + 1));
+            s.o_recix = take(sizeof(int) * (size_t)kMaxRec);
+        }
+        s.o_d = s.esz == 2 ? take(s.elems * s.esz) : 0;   // 16-bit: increment field
+        s.o_m = take(s.elems * 4);
+        for (int d = 0; d < 3; ++d) {
+            s.o_psi[d] = take(s.psi_elems[d] * 4);
+            s.o_zeta[d] = take(s.psi_elems[d] * 4);
+            s.o_psi2[d] = take(s.tile ? s.psi_elems[d] * 4 : 0);   // (one descriptor reaches all three)
+        }
+        s.o_prof = take((size_t)3 * 4 * s.nmax * 4);
+        s.o_work = take(sizeof(WorkItem) * work_capacity(s));
+        s.o_band = take(sizeof(BandItem) * band_capacity(s));
+        s.xbuf_bytes = xbuf_bytes(s);
+        s.o_xbuf = take(s.xbuf_bytes);
+        for (int p = 0; p < 2; ++p)
+            for (int ph = 0; ph < 4; ++ph) s.o_jobs[p][ph] = take(sizeof(CopyJob) * 16);
+    }
+    ctx->o_fill = take(sizeof(FillJob) * 11 * nshots);
+    size_t tile_all = 0;
+    for (auto &s : ctx->shots) {
+        s.o_tile = take(sizeof(TileItem) * tile_capacity(s));
+        tile_all += tile_capacity(s);
+    }
+    ctx->o_tdesc = take(sizeof(TileDesc) * nshots);
+    ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
+    ctx->need = off;
 }
 
 // ---------------------------------------------------------------------------
@@ -968,6 +1167,7 @@ int fdtd_create(const fdtd_shot_config *shots, int32_t nshots, void *hip_stream,
                 sh.zcols = 1;
             }
     }
+    for (auto &sh : ctx->shots) sh.tile = tile_rule(sh);
     for (auto &sh : ctx->shots)
         if (sh.tb_bufs && nshots != 1) {
             delete ctx;
@@ -981,48 +1181,9 @@ int fdtd_create(const fdtd_shot_config *shots, int32_t nshots, void *hip_stream,
     ctx->band_ty = BAND_TY;
     if (nshots == 1 && (long)ctx->shots[0].nx * ctx->shots[0].ny * ctx->shots[0].nz >= (1L << 27))
         ctx->band_ty = BAND_TY_TALL;
-    // workspace layout
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        size_t o = off;
-        off += align256(bytes);
-        return o;
-    };
-    ctx->o_stepc = take(256);
-    ctx->o_scratch = take(256);
-    ctx->o_desc = take(sizeof(DevShot) * nshots);
-    size_t cap_all = 0;
-    for (auto &s : ctx->shots) cap_all += work_capacity(s) + 8;
-    ctx->o_work_all = take(sizeof(WorkItem) * cap_all);
-    size_t band_all = 0;
-    for (auto &s : ctx->shots) band_all += band_capacity(s);
-    ctx->o_band_all = take(sizeof(BandItem) * band_all);
-    for (auto &s : ctx->shots) {
-        s.o_u[0] = take(s.elems * s.esz);
-        s.o_u[1] = take(s.elems * s.esz);
-        if (s.tb_bufs) {
-            s.o_u[2] = take(s.elems * s.esz);
-            s.o_u[3] = take(s.elems * s.esz);
-            s.o_tbwork = take(sizeof(WorkItem) * tblock_capacity(s));
-            s.o_reczs = take(sizeof(int) * (size_t)(s.nz + 1));
-            s.o_recix = take(sizeof(int) * (size_t)kMaxRec);
-        }
-        s.o_d = s.esz == 2 ? take(s.elems * s.esz) : 0;   // 16-bit: increment field
-        s.o_m = take(s.elems * 4);
-        for (int d = 0; d < 3; ++d) {
-            s.o_psi[d] = take(s.psi_elems[d] * 4);
-            s.o_zeta[d] = take(s.psi_elems[d] * 4);
-        }
-        s.o_prof = take((size_t)3 * 4 * s.nmax * 4);
-        s.o_work = take(sizeof(WorkItem) * work_capacity(s));
-        s.o_band = take(sizeof(BandItem) * band_capacity(s));
-        s.xbuf_bytes = xbuf_bytes(s);
-        s.o_xbuf = take(s.xbuf_bytes);
-        for (int p = 0; p < 2; ++p)
-            for (int ph = 0; ph < 4; ++ph) s.o_jobs[p][ph] = take(sizeof(CopyJob) * 16);
-    }
-    ctx->need = off;
+    layout(ctx);
     ctx->hdesc.resize(nshots);
+    ctx->htile.resize(nshots);
     *out = ctx;
     return FDTD_OK;
 }
@@ -1036,40 +1197,45 @@ int fdtd_workspace_size(const fdtd_ctx *ctx, size_t *bytes) {
 static int write_work_lists(fdtd_ctx *ctx) {
     std::map<std::array<int, 3>, std::vector<WorkItem>> byplan;
     std::vector<BandItem> band_all;
+    std::vector<TileItem> tile_all;
+    // (the copies read host memory until the stream is synchronised: every list lives until then)
+    auto upload = [&](size_t o, const void *src, size_t bytes) -> int {
+        if (bytes == 0) return FDTD_OK;
+        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, o), src, bytes, hipMemcpyHostToDevice, ctx->stream));
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        return FDTD_OK;
+    };
+    int rc;
     for (size_t i = 0; i < ctx->shots.size(); ++i) {
         ShotH &s = ctx->shots[i];
-        {
-            std::vector<BandItem> bt = band_tiles(s, (int)i, ctx->band_ty);
-            std::vector<BandItem> bw = xcd_order(bt);
-            if (bw.size() > band_capacity(s)) FAIL(ctx, FDTD_EINVAL, "band list overflow");
-            s.nband = (int)bw.size();
-            if (!bw.empty())
-                HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, s.o_band), bw.data(), sizeof(BandItem) * bw.size(),
-                                           hipMemcpyHostToDevice, ctx->stream));
-            if (s.variant != FDTD_VARIANT_NAIVE) band_all.insert(band_all.end(), bt.begin(), bt.end());
+        s.nband = s.nwork = s.ntbwork = s.ntile = 0;
+        if (s.tile) {
+            const std::vector<TileItem> bt = tile_boxes(s, (int)i), w = xcd_deal(bt);
+            if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
+            s.ntile = (int)w.size();
+            if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
+            tile_all.insert(tile_all.end(), bt.begin(), bt.end());
+            continue;
         }
-        std::vector<WorkItem> sp = shot_tiles(s, (int)i, s.ry, s.zchunk, s.zcols);
-        std::vector<WorkItem> w = xcd_order(sp);
+        const std::vector<BandItem> bt = band_tiles(s, (int)i, ctx->band_ty), bw = xcd_order(bt);
+        if (bw.size() > band_capacity(s)) FAIL(ctx, FDTD_EINVAL, "band list overflow");
+        s.nband = (int)bw.size();
+        if ((rc = upload(s.o_band, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
+        if (s.variant != FDTD_VARIANT_NAIVE) band_all.insert(band_all.end(), bt.begin(), bt.end());
+        const std::vector<WorkItem> sp = shot_tiles(s, (int)i, s.ry, s.zchunk, s.zcols), w = xcd_order(sp);
         if (w.size() > work_capacity(s)) FAIL(ctx, FDTD_EINVAL, "work list overflow");
         s.nwork = (int)w.size();
-        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, s.o_work), w.data(), sizeof(WorkItem) * w.size(), hipMemcpyHostToDevice,
-                                   ctx->stream));
-        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        if ((rc = upload(s.o_work, w.data(), sizeof(WorkItem) * w.size()))) return rc;
         if (s.variant != FDTD_VARIANT_NAIVE) {
             auto &v = byplan[std::array<int, 3>{s.ry, s.zchunk, s.zcols}];
             v.insert(v.end(), sp.begin(), sp.end());
         }
-        s.ntbwork = 0;
-        if (s.tb_bufs) {
-            std::vector<WorkItem> tb = tblock_tiles(s, (int)i);
-            if (!tb.empty()) {
-                std::vector<WorkItem> tw = xcd_order(tb);
-                if (tw.size() > tblock_capacity(s)) FAIL(ctx, FDTD_EINVAL, "tile list overflow");
-                s.ntbwork = (int)tw.size();
-                HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, s.o_tbwork), tw.data(), sizeof(WorkItem) * tw.size(),
-                                           hipMemcpyHostToDevice, ctx->stream));
-                HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-            }
+        const std::vector<WorkItem> tb = tblock_tiles(s, (int)i);
+        if (!tb.empty()) {
+            const std::vector<WorkItem> tw = xcd_order(tb);
+            if (tw.size() > tblock_capacity(s)) FAIL(ctx, FDTD_EINVAL, "tile list overflow");
+            s.ntbwork = (int)tw.size();
+            if ((rc = upload(s.o_tbwork, tw.data(), sizeof(WorkItem) * tw.size()))) return rc;
         }
     }
     ctx->groups.clear();
@@ -1081,39 +1247,49 @@ static int write_work_lists(fdtd_ctx *ctx) {
         all.insert(all.end(), wa.begin(), wa.end());
     }
     ctx->nwork_all = (int)all.size();
-    {
-        std::vector<BandItem> bw = xcd_order(band_all);
-        ctx->nband_all = (int)bw.size();
-        if (!bw.empty())
-            HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_band_all), bw.data(), sizeof(BandItem) * bw.size(),
-                                       hipMemcpyHostToDevice, ctx->stream));
+    const std::vector<BandItem> bw = xcd_order(band_all);
+    ctx->nband_all = (int)bw.size();
+    if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
+    const std::vector<TileItem> tw = xcd_deal(tile_all);
+    ctx->ntile_all = (int)tw.size();
+    if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
+    return upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
+}
+
+// the ranges a reset clears, one list for one launch: level buffers (and the
+// increment), psi and zeta
+static int write_fill_list(fdtd_ctx *ctx) {
+    std::vector<FillJob> v;
+    ctx->fill_max16 = 0;
+    auto add = [&](size_t o, size_t bytes) {
+        const size_t n16 = align256(bytes) / 16;
+        if (n16 == 0) return;
+        v.push_back(FillJob{wsp(ctx, o), n16});
+        ctx->fill_max16 = std::max(ctx->fill_max16, n16);
+    };
+    for (const ShotH &s : ctx->shots) {
+        for (int b = 0; b < (s.tb_bufs ? 4 : 2); ++b) add(s.o_u[b], s.elems * s.esz);
+        if (s.esz == 2) add(s.o_d, s.elems * s.esz);
+        for (int d = 0; d < 3; ++d) {
+            add(s.o_psi[d], s.psi_elems[d] * 4);
+            add(s.o_zeta[d], s.psi_elems[d] * 4);
+        }
     }
+    ctx->nfill = (int)v.size();
+    HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_fill), v.data(), sizeof(FillJob) * v.size(), hipMemcpyHostToDevice,
+                               ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    if (!all.empty()) {
-        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_work_all), all.data(), sizeof(WorkItem) * all.size(),
-                                   hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    }
     return FDTD_OK;
 }
 
 static int zero_state(fdtd_ctx *ctx) {
-    for (auto &s : ctx->shots) {
-        fdtd_launch_fill_zero(wsp(ctx, s.o_u[0]), align256(s.elems * s.esz), ctx->stream);
-        fdtd_launch_fill_zero(wsp(ctx, s.o_u[1]), align256(s.elems * s.esz), ctx->stream);
-        if (s.esz == 2) fdtd_launch_fill_zero(wsp(ctx, s.o_d), align256(s.elems * s.esz), ctx->stream);
-        if (s.tb_bufs)
-            for (int b = 2; b < 4; ++b) fdtd_launch_fill_zero(wsp(ctx, s.o_u[b]), align256(s.elems * s.esz), ctx->stream);
-        for (int d = 0; d < 3; ++d) {
-            fdtd_launch_fill_zero(wsp(ctx, s.o_psi[d]), align256(s.psi_elems[d] * 4), ctx->stream);
-            fdtd_launch_fill_zero(wsp(ctx, s.o_zeta[d]), align256(s.psi_elems[d] * 4), ctx->stream);
-        }
-    }
+    fdtd_launch_fill_jobs(wsp(ctx, ctx->o_fill), ctx->nfill, ctx->fill_max16, ctx->stream);
     fdtd_launch_set_int((int *)wsp(ctx, ctx->o_stepc), 0, ctx->stream);
     HIPCHK(ctx, hipGetLastError());
     ctx->iu = 0;
     ctx->ium1 = 1;
     ctx->step = 0;
+    ctx->pend = 0;
     return FDTD_OK;
 }
 
@@ -1133,8 +1309,12 @@ int fdtd_bind_workspace(fdtd_ctx *ctx, void *dev_ptr, size_t bytes) {
     for (auto &s : ctx->shots) {
         fdtd_launch_fill_zero(wsp(ctx, s.o_m), align256(s.elems * 4), ctx->stream);
         fdtd_launch_fill_zero(wsp(ctx, s.o_prof), align256((size_t)3 * 4 * s.nmax * 4), ctx->stream);
+        for (int d = 0; s.tile && d < 3; ++d)
+            fdtd_launch_fill_zero(wsp(ctx, s.o_psi2[d]), align256(s.psi_elems[d] * 4), ctx->stream);
     }
-    int rc = zero_state(ctx);
+    int rc = write_fill_list(ctx);
+    if (rc) return rc;
+    rc = zero_state(ctx);
     if (rc) return rc;
     rc = write_work_lists(ctx);
     if (rc) return rc;
@@ -1510,6 +1690,13 @@ int fdtd_set_plan(fdtd_ctx *ctx, int32_t shot, int32_t variant, int32_t tile_ry,
     ShotH &s = ctx->shots[shot];
     if (variant == FDTD_VARIANT_TBLOCK && !s.tb_bufs)
         FAIL(ctx, FDTD_EINVAL, "create the shot with the temporal-blocking variant to switch to it");
+    // a shot that leaves the tile kernel takes its psi along (the other kernels keep it in place)
+    if (s.tile && ctx->ws && ctx->iu == 1)
+        for (int d = 0; d < 3; ++d)
+            if (s.psi_elems[d])
+                HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, s.o_psi[d]), wsp(ctx, s.o_psi2[d]), s.psi_elems[d] * 4,
+                                           hipMemcpyDeviceToDevice, ctx->stream));
+    s.tile = false;
     s.variant = variant;
     s.ry = tile_ry;
     s.zchunk = zchunk;
@@ -1651,4 +1838,9 @@ int fdtd_rewrite_work(fdtd_ctx *ctx) { return write_work_lists(ctx); }
 int fdtd_reupload(fdtd_ctx *ctx) { return upload_desc(ctx); }
 int fdtd_ready(fdtd_ctx *ctx) { return ready(ctx); }
 int fdtd_zero_state(fdtd_ctx *ctx) { return zero_state(ctx); }
+// before a workspace is bound: no tile shots, and the smaller workspace that goes with it
+void fdtd_disable_tile(fdtd_ctx *ctx) {
+    for (auto &s : ctx->shots) s.tile = false;
+    layout(ctx);
+}
 void fdtd_set_copy_vec(CopyJob &j) { set_copy_vec(j); }

@@ -17,6 +17,7 @@
 
 #define FDTD_R 4          // stencil radius
 #define FDTD_MAXSHOTS 64
+constexpr int kFieldLead = 128;   // leading pad of every field (elements)
 
 // ---------------------------------------------------------------------------
 // storage types: FP32, FP16 (_Float16) and BF16 (__bf16); arithmetic is FP32.
@@ -91,9 +92,25 @@ struct DevShot {
     int SY, SZ;            // y, z layer arrays: strides along the slab axis, width + 1 slot that stays zero
     int ghost[3];          // 1 if the axis has ghost (loopback) faces
     int fused;             // 1: the band kernel advances psi_x and psi_z itself, the psi pass only psi_y
+    int tile;              // 1: k_tile does the whole step (the psi passes skip the shot)
     float cc;              // sum_d (c0 + 2 c1) / h_d^2
     float w2[3][5];        // (c0 + 2 c1) / h_d^2, then c_l / h_d^2 for l = 1..4
     float w1[3][5];        // d_l / h_d   (w1[d][0] unused)
+};
+
+// What the tile kernel needs of a shot (the fields of DevShot of the same
+// names, and the shot's arrays as byte offsets from its first).  psi alternates
+// between two buffers: t_psi[0] while level buffer 0 holds u^n, t_psi[1] while
+// buffer 1 does.
+struct TileDesc {
+    char *tbase;
+    uint32_t t_u[2], t_d, t_m, t_prof, t_psi[2][3], t_zeta[3];
+    int nx, ny, nz, P, PY, S, fy, fz, WX, SY, nmax;
+    int Llo[3], Lhi[3];
+    float cc, w2[3][5], w1[3][5];
+    int sx, sy, sz, src_nt;
+    float src_scale;
+    const float *wav;
 };
 
 // Strided box copy (ghost pack/unpack).  Rows (ex elements) are copied in
@@ -106,6 +123,12 @@ struct CopyJob {
     int ex, ey, ez;       // box extent (elements)
     long sy, sz, dy, dz;  // row / plane strides (elements) of source and destination
     int vb;               // bytes per copied piece
+};
+
+// A range zeroed by k_fill_jobs: n16 pieces of 16 bytes.
+struct FillJob {
+    void *p;
+    unsigned long long n16;
 };
 
 // Roles of the level buffers in one launch and an optional box of points the
@@ -121,9 +144,26 @@ __device__ __forceinline__ bool in_box(const Roles &R, int x, int y, int z) {
     return x >= R.lo[0] && x < R.hi[0] && y >= R.lo[1] && y < R.hi[1] && z >= R.lo[2] && z < R.hi[2];
 }
 
-// Work item of the z-marching kernels: shot, x tile, y tile, z chunk.
+// Work item of the z-marching and the tile kernels: shot, x tile, y tile, z chunk.
 struct WorkItem {
     int shot, tx, ty, zc;
+};
+
+// Box of the tile kernel (k_tile), and one step of it: the level buffer of u^n,
+// the step's number past the device step counter, the box items, and the first
+// shot whose receivers the extra blocks record (the step before's row).
+#define TILE_X 32
+#define TILE_Y 8
+#define TILE_Z 4
+struct TileStep {
+    int iu, k, nwork, rec_lo;
+};
+// One box: shot (low byte) and the axes whose band it meets (negative: an idle item); first point.
+#define TILE_XB 0x100
+#define TILE_YB 0x200
+#define TILE_ZB 0x400
+struct TileItem {
+    int flags, x0, y0, z0;
 };
 
 // Work item of the band kernel: shot, band box, x tile, y tile, z chunk.
@@ -381,6 +421,7 @@ __device__ __forceinline__ Rsrc make_rsrc(const void *base) {
 // L2, keeps plain loads: the hint on every load made the 512^3 step 16 %
 // slower.
 constexpr int kStoreNT = 2, kLoadNT = 2;
+// (stc: a store without the hint, for shots small enough that the next step finds the level in the caches)
 template <typename T> struct Buf;
 template <> struct Buf<float> {
     static __device__ __forceinline__ float ld(Rsrc r, uint32_t vo, uint32_t so) {
@@ -391,6 +432,9 @@ template <> struct Buf<float> {
     }
     static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float v) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, kStoreNT);
+    }
+    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float v) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, vo, so, 0);
     }
 };
 template <> struct Buf<_Float16> {
@@ -403,6 +447,9 @@ template <> struct Buf<_Float16> {
     static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float v) {
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (_Float16)v), r, vo, so, kStoreNT);
     }
+    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float v) {
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (_Float16)v), r, vo, so, 0);
+    }
 };
 template <> struct Buf<__bf16> {
     static __device__ __forceinline__ float ld(Rsrc r, uint32_t vo, uint32_t so) {
@@ -413,6 +460,9 @@ template <> struct Buf<__bf16> {
     }
     static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float v) {
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (__bf16)v), r, vo, so, kStoreNT);
+    }
+    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float v) {
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (__bf16)v), r, vo, so, 0);
     }
 };
 

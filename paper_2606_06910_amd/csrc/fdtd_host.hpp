@@ -9,12 +9,15 @@
 #include <utility>
 #include <vector>
 
-constexpr int kOFF = 128;   // leading pad of every field (elements)
+constexpr int kOFF = kFieldLead;   // leading pad of every field (elements)
 constexpr int kTYMAX = 64;  // tallest y tile (rows) a kernel may overhang
 constexpr int kMaxRec = 65536;  // receivers per shot with temporal blocking
 constexpr int kTimingClasses = 6;   // update, psi, record, exchange, band update, temporal block
 constexpr int kBandTX = BAND_TX, kBandZ = 32;   // band-kernel tile width and z chunk
 constexpr int kCUs = 256;   // compute units of an MI355X (the default z-march plan shares them)
+constexpr long kTileShot = 60000000, kTileShot16 = 30000000;   // shots below this many points (FP32, 16-bit
+                                                               // storage) take the tile kernel by default
+constexpr size_t kTilePiece = 512;   // most consecutive boxes of the tile kernel that go to one XCD
 constexpr long kSmallShot = 150L * 150 * 150;   // a lone shot below this many points runs naive by default
 
 struct ShotH {
@@ -33,6 +36,10 @@ struct ShotH {
     size_t psi_elems[3] = {0, 0, 0};
     // workspace offsets
     size_t o_u[4] = {0, 0, 0, 0}, o_d = 0, o_m = 0, o_psi[3] = {0, 0, 0}, o_zeta[3] = {0, 0, 0}, o_prof = 0;
+    // tile shots (k_tile does the whole step): the other psi buffers and the box list
+    bool tile = false;
+    size_t o_psi2[3] = {0, 0, 0}, o_tile = 0;
+    int ntile = 0;
     size_t o_work = 0, o_xbuf = 0, xbuf_bytes = 0;
     size_t o_jobs[2][4] = {};
     int njobs[2][4] = {};
@@ -70,6 +77,7 @@ struct ShotH {
 struct fdtd_ctx {
     std::vector<ShotH> shots;
     std::vector<DevShot> hdesc;
+    std::vector<TileDesc> htile;
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;   // private stream used only to capture graphs
     hipStream_t side = nullptr;         // second stream: interior update concurrent with psi + band
@@ -81,8 +89,10 @@ struct fdtd_ctx {
     bool single_stream = false;         // never create the side stream (everything on `stream`)
     char *ws = nullptr;
     size_t ws_bytes = 0, need = 0;
-    size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0;
-    int nwork_all = 0, nband_all = 0;
+    size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0, o_tile_all = 0, o_tdesc = 0, o_fill = 0;
+    int nwork_all = 0, nband_all = 0, ntile_all = 0, nfill = 0;
+    size_t fill_max16 = 0;    // longest range of the reset's fill list
+    int pend = 0;             // steps enqueued since the device step counter was last advanced
     // multi-shot z-march launches: one per distinct (ry, zchunk) plan
     struct Group {
         int ry, zchunk, cols;
@@ -131,6 +141,8 @@ int fdtd_rewrite_work(fdtd_ctx *ctx);
 int fdtd_reupload(fdtd_ctx *ctx);
 int fdtd_ready(fdtd_ctx *ctx);
 int fdtd_zero_state(fdtd_ctx *ctx);
+void fdtd_disable_tile(fdtd_ctx *ctx);
+size_t fdtd_psi_off(const ShotH &s, int d, int iu);
 void fdtd_set_copy_vec(CopyJob &j);
 
 inline void fdtd_clear_graphs(fdtd_ctx *ctx) {

@@ -17,7 +17,13 @@ void fdtd_launch_zmarch(int stor, const DevShot *d_shots, const WorkItem *work, 
 // band points (tiles of every box kind in one list; ty = BAND_TY or BAND_TY_TALL rows per tile)
 void fdtd_launch_band(int stor, const DevShot *d_shots, const BandItem *work, int nwork, const Roles &R, int zchunk,
                       const int *stepc, int ty, hipStream_t st);
-void fdtd_launch_record(int stor, const DevShot *d_shots, int nshots, const Roles &R, int *stepc, hipStream_t st);
+// receivers of the step numbered `adv` - 1 past the device step counter, which then advances by adv
+void fdtd_launch_record(int stor, const DevShot *d_shots, int nshots, const Roles &R, int *stepc, int adv,
+                        hipStream_t st);
+// whole step of tile shots (one: the host copy of the descriptor of a launch over one shot); nrec extra blocks
+// record the shots from A.rec_lo on
+void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
+                      const TileStep &A, int nrec, const int *stepc, const TileDesc *one, hipStream_t st);
 // temporal blocking: args points to a host TBArgs (kernels_tblock.hip); K = 2 or 4
 void fdtd_launch_tblock(const DevShot *d_shots, const WorkItem *work, int nwork, int K, const void *args, int zchunk,
                         const int *stepc, hipStream_t st);
@@ -30,6 +36,8 @@ struct TBArgsHost {
 };
 
 void fdtd_launch_fill_zero(void *p, size_t bytes, hipStream_t st);
+// zero every range of a device-resident FillJob list in one launch; max_n16 = longest range
+void fdtd_launch_fill_jobs(const void *jobs, int njobs, size_t max_n16, hipStream_t st);
 void fdtd_launch_vel_to_m(const float *v, float *m, int nx, int ny, int nz, int P, int S, double dt2,
                           unsigned int *vmax_bits, unsigned int *bad, hipStream_t st);
 void fdtd_launch_get_field(int stor, const void *u, float *dst, int nx, int ny, int nz, int P, int S, float inv,

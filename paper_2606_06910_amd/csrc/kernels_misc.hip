@@ -12,10 +12,21 @@
 //  k_finite          flag any NaN/Inf in a field
 #include "fdtd_dev.hpp"
 
+#include <algorithm>
+
 __global__ __launch_bounds__(256) void k_fill_zero(uint4 *p, size_t n16) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < n16; i += stride) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// grid: (blocks, jobs)
+__global__ __launch_bounds__(256) void k_fill_jobs(const FillJob *__restrict__ jobs) {
+    const FillJob j = jobs[blockIdx.y];
+    uint4 *p = (uint4 *)j.p;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < j.n16; i += stride)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // grid: (ceil(nx/256), ny, nz)
@@ -132,6 +143,11 @@ void fdtd_launch_fill_zero(void *p, size_t bytes, hipStream_t st) {
     size_t blocks = (n16 + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, st, (uint4 *)p, n16);
+}
+void fdtd_launch_fill_jobs(const void *jobs, int njobs, size_t max_n16, hipStream_t st) {
+    if (njobs <= 0 || max_n16 == 0) return;
+    const size_t blocks = std::min<size_t>((max_n16 + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_fill_jobs, dim3((unsigned)blocks, njobs), dim3(256), 0, st, (const FillJob *)jobs);
 }
 void fdtd_launch_vel_to_m(const float *v, float *m, int nx, int ny, int nz, int P, int S, double dt2,
                           unsigned int *vmax_bits, unsigned int *bad, hipStream_t st) {

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void k_psi(const DevShot *__restrict__ shots, 
     const DevShot &s = shots[blockIdx.z];
     const int d = d0 + (int)blockIdx.y;
     const int lo = s.Llo[d], hi = s.Lhi[d];
-    if (lo + hi == 0 || d == 1 || s.fused) return;   // psi_y: k_psi_y
+    if (lo + hi == 0 || d == 1 || s.fused || s.tile) return;   // psi_y: k_psi_y
     const Box bx = shot_box(s, ext);
     const unsigned Ny = bx.yhi - bx.ylo, Nz = bx.zhi - bx.zlo;
     // slab points as (a fastest, b, c): x-slab (is, y, z), y-slab (x, js, z), z-slab (x, y, ks)
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_psi_y(const DevShot *__restrict__ shots
     const DevShot &s = shots[blockIdx.z];
     const int side = (int)blockIdx.y;
     const int L = side ? s.Lhi[1] : s.Llo[1];
-    if (L == 0) return;
+    if (L == 0 || s.tile) return;
     const Box bx = shot_box(s, ext);
     const unsigned nx = (unsigned)s.nx, Nz = (unsigned)(bx.zhi - bx.zlo);
     // contiguous ranges of lines per XCD (as in k_psi)
@@ -719,8 +719,8 @@ __global__ __launch_bounds__(64 * NW) void k_zmarch2(const DevShot *__restrict__
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(1024) void k_record(const DevShot *__restrict__ shots, int nshots, Roles R,
-                                                 int *__restrict__ stepc) {
-    const int n = *stepc;
+                                                 int *__restrict__ stepc, int adv) {
+    const int n = *stepc + adv - 1;
     for (int si = 0; si < nshots; ++si) {
         const DevShot &s = shots[si];
         if (s.traces == nullptr || n >= s.trace_cap) continue;
@@ -795,8 +795,8 @@ static void launch_zmarch_t(const DevShot *d_shots, const WorkItem *work, int nw
     }
 }
 template <typename T>
-static void launch_record_t(const DevShot *d_shots, int nshots, const Roles &R, int *stepc, hipStream_t st) {
-    hipLaunchKernelGGL(k_record<T>, dim3(1), dim3(1024), 0, st, d_shots, nshots, R, stepc);
+static void launch_record_t(const DevShot *d_shots, int nshots, const Roles &R, int *stepc, int adv, hipStream_t st) {
+    hipLaunchKernelGGL(k_record<T>, dim3(1), dim3(1024), 0, st, d_shots, nshots, R, stepc, adv);
 }
 
 #define FDTD_DISPATCH(stor, F, ...)                                                                      \
@@ -821,6 +821,7 @@ void fdtd_launch_zmarch(int stor, const DevShot *d_shots, const WorkItem *work, 
                         const Roles &R, int zchunk, const int *stepc, hipStream_t st) {
     FDTD_DISPATCH(stor, launch_zmarch_t, d_shots, work, nwork, ry, cols, R, zchunk, stepc, st);
 }
-void fdtd_launch_record(int stor, const DevShot *d_shots, int nshots, const Roles &R, int *stepc, hipStream_t st) {
-    FDTD_DISPATCH(stor, launch_record_t, d_shots, nshots, R, stepc, st);
+void fdtd_launch_record(int stor, const DevShot *d_shots, int nshots, const Roles &R, int *stepc, int adv,
+                        hipStream_t st) {
+    FDTD_DISPATCH(stor, launch_record_t, d_shots, nshots, R, stepc, adv, st);
 }

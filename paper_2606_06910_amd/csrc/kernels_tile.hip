@@ -1,0 +1,430 @@
+// kernels_tile.hip -- one leapfrog step of a shot in one launch (gfx950), for
+// the shots whose step is bound by latency, launches and the layers' share of
+// the points rather than by HBM.
+//
+// A block owns a box of TILE_X x TILE_Y x TILE_Z points, inside or outside the
+// layers, and does the whole step there: psi, zeta and u^{n+1} (paper, section
+// "CPML Boundary Layers"; the arithmetic is lap_point's, operation for
+// operation, so the bits are those of every other variant).  psi_d at the
+// neighbours along d is recomputed from u^n and the old psi_d of the box grown
+// by 4 points along d (the u^n box grown by 8), so no pass has to come before
+// the update; the new psi goes to the other of two psi buffers (the old one is
+// still being read by the neighbouring blocks).  Receivers of a step are
+// recorded by extra blocks of the next step's launch.
+//
+// What bounds it: at 64^3 (one block per CU) the chain of one block: launch,
+// list item, loads, two barriers, stores; from 128^3 up instruction issue (118
+// VALU and 78 scalar instructions per plane of 64 points on a 160^3 grid with
+// 20-cell layers) and the load latency that four waves per SIMD leave open.
+// Why this box: 32 points are a 128-byte line; 4 planes keep the column (20
+// planes of u^n), its old psi and the second state within 114 VGPRs and the
+// three LDS arrays within 31 KB, so that four blocks share a CU; asking for
+// five spills 21 VGPRs (160^3: 28.7 -> 43 us per step).  Every load is issued
+// before the first wait, and one buffer descriptor covers the whole shot
+// (seven of them, and tests kept in scalar register pairs, cost 30 scalar
+// spills and 10 %).  Per step, before (psi passes, naive or z-march and band
+// kernels, record) and after: 64^3 19.5 -> 8.4 us, 101 x 87 x 119 (eager) 38 ->
+// 16 us, 160^3 100 -> 30 us (135 Gpts/s, 3.8 TB/s of the algorithmic bytes),
+// 24 batched shots of 96 .. 288 points per axis 1.45 -> 1.22 ms.
+#include "fdtd_dev.hpp"
+#include "fdtd_launch.hpp"
+
+namespace {
+constexpr int TX = TILE_X, TY = TILE_Y, TZ = TILE_Z;
+constexpr int UW = TX + 4 * FDTD_R, UH = TY + 4 * FDTD_R;   // LDS plane of u^n: 8 columns and rows on each side
+constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, new psi_y columns: 4 on each side
+static_assert(TX * TY == 256 && TZ == 4 && 2 * FDTD_R * TY * TZ == 256 && TY == 2 * FDTD_R, "lane maps below");
+
+__device__ __forceinline__ bool slab_point(int c, int n, int lo, int hi) {
+    return c >= 0 && c < n && in_slab(c, n, lo, hi);
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// the same scalar, its later tests computed anew: a test kept from one phase to the next costs two scalar
+// registers each, and the kernel has none to spare
+__device__ __forceinline__ int again(int v) {
+    v = uniform(v);
+    asm("" : "+s"(v));
+    return v;
+}
+// the descriptors read as constant memory: no store of the kernel changes them, so they may be loaded at once
+typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
+}  // namespace
+
+// one box (D: TileDesc in the constant or the kernel-argument address space)
+template <typename T, typename D>
+__device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const TileStep &A,
+                                         const int *__restrict__ stepc) {
+    const int t = (int)threadIdx.x;
+    const int nx = s.nx, ny = s.ny, nz = s.nz;
+    const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0;
+    const int lx = t % TX, ly = t / TX;
+    const int x = x0 + lx, y = y0 + ly;
+    const bool act = x < nx && y < ny;
+    const int xlo = s.Llo[0], xhi = s.Lhi[0], ylo = s.Llo[1], yhi = s.Lhi[1], zlo = s.Llo[2], zhi = s.Lhi[2];
+    // axes whose band the box meets: only these need psi, zeta and the wider u^n halo
+    const int xb = wi.flags & TILE_XB, yb = wi.flags & TILE_YB, zb = wi.flags & TILE_ZB;
+    // stencil weights in scalar registers for the whole kernel
+    float w1[3][5], w2[3][5];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) {
+            w1[d][l] = s.w1[d][l];
+            w2[d][l] = s.w2[d][l];
+        }
+
+    __shared__ float U[TZ][UH][UW];     // u^n at (x0 - 8 + c, y0 - 8 + r, z0 + p); corners unused
+    __shared__ float PX[TZ][TY][PXW];   // new psi_x at (x0 - 4 + c, y0 + r, z0 + p), 0 outside the slabs
+    __shared__ float PY[TZ][PYH][TX];   // new psi_y at (x0 + c, y0 - 4 + r, z0 + p)
+
+    // Every array of the shot lies within 2 GiB of its first (the tile rule sees to it), so one descriptor
+    // reaches them all: array at a scalar offset, position at a lane offset, plane by plane a running scalar
+    // offset.  Lanes whose position lies outside the frame that every field carries read zero; planes outside
+    // it are not read.
+    const Rsrc R = make_rsrc(s.tbase);
+    const int P = s.P, esz = (int)sizeof(T), fy = s.fy, fz = s.fz;
+    const uint32_t Sb = (uint32_t)s.S * (uint32_t)esz, Smb = (uint32_t)s.S * 4u;
+    // offset of (-4, -fy, z0) from a field's first byte: with elem() below, of (x, y, z0)
+    const uint32_t lead = (uint32_t)((fz + z0) * s.S) + (uint32_t)(kFieldLead - FDTD_R);
+    const uint32_t fu = s.t_u[A.iu] + lead * esz, fw = s.t_u[A.iu ^ 1] + lead * esz;
+    const uint32_t fs = IsInc<T>::v ? s.t_d + lead * esz : fw, fm = s.t_m + lead * 4u;
+    auto elem = [&](int xp, int yp) { return (uint32_t)((yp + fy) * P + xp + FDTD_R); };
+    auto off = [&](int xp, int yp) -> uint32_t {
+        return xp >= -FDTD_R && xp < nx + FDTD_R && yp >= -fy && yp < ny + fy ? elem(xp, yp) * (uint32_t)esz : kBufSkip;
+    };
+
+    // ---- every load of the box, before anything waits ----
+    // own column: u^n at z0 - 8 .. z0 + TZ + 7 (the outer 4 on each side only for psi_z); a plane past the
+    // frame (no tap of any point of the grid) is read as the last frame plane
+    constexpr int QN = TZ + 4 * FDTD_R;
+    float q[QN];
+    const uint32_t vq = off(x, y);
+    const uint32_t slast = fu + (uint32_t)(nz + fz - 1 - z0) * Sb;
+    {
+        uint32_t so = fu - FDTD_R * Sb;
+#pragma unroll
+        for (int o = FDTD_R; o < QN - FDTD_R; ++o, so += Sb) q[o] = Buf<T>::ld(R, vq, o < 3 * FDTD_R ? so : min(so, slast));
+    }
+    // y halo: 4 rows above and below the box, then the next 4 for psi_y: one row of each per thread
+    const int yn = ly < FDTD_R ? y0 - FDTD_R + ly : y0 + FDTD_R + ly;
+    const int yf = ly < FDTD_R ? yn - FDTD_R : yn + FDTD_R;
+    // x halo: 4 columns left and right of the box, then the next 4 for psi_x; wave w takes plane w
+    const int c8 = t & 7, hr = (t >> 3) & (TY - 1), hp = uniform(t >> 6);
+    const int xn = c8 < FDTD_R ? x0 - FDTD_R + c8 : x0 + TX - FDTD_R + c8;
+    const int xf = c8 < FDTD_R ? xn - FDTD_R : xn + FDTD_R;
+    const uint32_t sh = fu + (uint32_t)hp * Sb;
+    const float hxn = Buf<T>::ld(R, off(xn, y0 + hr), sh);
+    const uint32_t vyn = off(x, yn), vc = act ? vq : kBufSkip, vcm = act ? elem(x, y) * 4u : kBufSkip;
+    float hyn[TZ], hyf[TZ], hxf, second[TZ], mm[TZ];
+    {
+        uint32_t so = fu, ss = fs, sm = fm;
+#pragma unroll
+        for (int p = 0; p < TZ; ++p, so += Sb, ss += Sb, sm += Smb) {
+            hyn[p] = Buf<T>::ld(R, vyn, so);
+            second[p] = Buf<T>::ld(R, vc, ss);
+            mm[p] = Buf<float>::ld(R, vcm, sm);
+        }
+    }
+    auto prof = [&](int d, int f, int c) -> float {
+        return Buf<float>::ld(R, (uint32_t)c * 4u, s.t_prof + (uint32_t)((d * 4 + f) * s.nmax) * 4u);
+    };
+    // x layers: own psi and zeta, and psi of the 4 columns on each side (psi_index layout)
+    const uint32_t Spx = (uint32_t)(s.PY * s.WX) * 4u;
+    uint32_t xpn = 0, xze = 0;   // new psi and zeta at plane z0
+    bool bx = false, sx = false, hsx = false;
+    uint32_t vx = kBufSkip;
+    float pxo[TZ], zx[TZ], dx[TZ], pxh, ax[4], ahx[2];   // dx: D1 u^n at the column's points
+    if (xb) {
+        const uint32_t fo = (uint32_t)(z0 + fz) * Spx, xpo = s.t_psi[A.iu][0] + fo;
+        xpn = s.t_psi[A.iu ^ 1][0] + fo;
+        xze = s.t_zeta[0] + fo;
+        const uint32_t side = (uint32_t)(nz + 2 * fz) * Spx - (uint32_t)(nx - xhi) * 4u;
+        auto xoff = [&](int xp, int yp) -> uint32_t {
+            const uint32_t e = (uint32_t)((yp + fy) * s.WX + xp) * 4u;
+            return xp < xlo ? e : e + side;
+        };
+        hxf = Buf<T>::ld(R, off(xf, y0 + hr), sh);
+        bx = act && in_band(x, nx, xlo, xhi);
+        sx = act && slab_point(x, nx, xlo, xhi);
+        vx = sx ? xoff(x, y) : kBufSkip;
+        hsx = y0 + hr < ny && slab_point(xn, nx, xlo, xhi);
+        pxh = Buf<float>::ld(R, hsx ? xoff(xn, y0 + hr) : kBufSkip, xpo + (uint32_t)hp * Spx);
+        uint32_t so = xpo, sz = xze;
+#pragma unroll
+        for (int p = 0; p < TZ; ++p, so += Spx, sz += Spx) {
+            pxo[p] = Buf<float>::ld(R, vx, so);
+            zx[p] = Buf<float>::ld(R, vx, sz);
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) ax[f] = prof(0, f, min(x, nx - 1));
+#pragma unroll
+        for (int f = 0; f < 2; ++f) ahx[f] = prof(0, f, min(max(xn, 0), nx - 1));
+    }
+    // y layers
+    const uint32_t Spy = (uint32_t)(s.SY * nx) * 4u;
+    uint32_t ypn = 0, yze = 0;
+    bool by = false, sy = false, hsy = false;
+    uint32_t vy = kBufSkip;
+    float pyo[TZ], pyh[TZ], zy[TZ], dy[TZ], ay[4], ahy[2];
+    if (yb) {
+        const uint32_t fo = (uint32_t)(z0 + fz) * Spy, ypo = s.t_psi[A.iu][1] + fo;
+        ypn = s.t_psi[A.iu ^ 1][1] + fo;
+        yze = s.t_zeta[1] + fo;
+        auto yoff = [&](int yp) -> uint32_t { return (uint32_t)(slab_pos(yp, ny, ylo, yhi) * nx + x) * 4u; };
+        const uint32_t vyf = off(x, yf);
+        by = act && in_band(y, ny, ylo, yhi);
+        sy = act && slab_point(y, ny, ylo, yhi);
+        vy = sy ? yoff(y) : kBufSkip;
+        hsy = x < nx && slab_point(yn, ny, ylo, yhi);
+        const uint32_t vyh = hsy ? yoff(yn) : kBufSkip;
+        uint32_t su = fu, so = ypo, sz = yze;
+#pragma unroll
+        for (int p = 0; p < TZ; ++p, su += Sb, so += Spy, sz += Spy) {
+            hyf[p] = Buf<T>::ld(R, vyf, su);
+            pyo[p] = Buf<float>::ld(R, vy, so);
+            pyh[p] = Buf<float>::ld(R, vyh, so);
+            zy[p] = Buf<float>::ld(R, vy, sz);
+        }
+#pragma unroll
+        for (int f = 0; f < 4; ++f) ay[f] = prof(1, f, min(y, ny - 1));
+#pragma unroll
+        for (int f = 0; f < 2; ++f) ahy[f] = prof(1, f, min(max(yn, 0), ny - 1));
+    }
+    // z layers: the column's psi at z0 - 4 .. z0 + TZ + 3 (bit o of zm: plane z0 - 4 + o lies in a layer; the
+    // window meets one layer only, the tile rule sees to that too); the profiles of those planes, one per lane
+    const uint32_t Spz = (uint32_t)(s.PY * nx) * 4u;
+    const uint32_t vz = act ? (uint32_t)((y + fy) * nx + x) * 4u : kBufSkip;
+    constexpr int PN = TZ + 2 * FDTD_R;
+    float pz[PN], zz[TZ], dz[TZ], az[4];
+    uint32_t zm = 0, zpn = 0, zze = 0;   // new psi and zeta at plane z0 - 4
+    if (zb) {
+        auto bits = [&](int lo, int hi) -> uint32_t {   // bits of planes lo .. hi - 1
+            const int a = min(max(lo - z0 + FDTD_R, 0), PN), b = min(max(hi - z0 + FDTD_R, 0), PN);
+            return ((1u << b) - 1u) & ~((1u << a) - 1u);
+        };
+        const uint32_t zlm = bits(0, zlo);
+        zm = zlm | bits(nz - zhi, nz);
+        // slab position of plane z0 - 4 (as if it lay in the layer of the window)
+        const uint32_t fo = (uint32_t)(z0 - FDTD_R + (zlm ? 0 : zlo - (nz - zhi))) * Spz;
+        const uint32_t zpo = s.t_psi[A.iu][2] + fo;
+        zpn = s.t_psi[A.iu ^ 1][2] + fo;
+        zze = s.t_zeta[2] + fo;
+        // (z0 - 8 .. z0 - 5 of a box at the low face: no tap, read as plane z0)
+        uint32_t su = z0 >= FDTD_R ? fu - 2 * FDTD_R * Sb : fu, sh2 = fu + (TZ + FDTD_R) * Sb;
+#pragma unroll
+        for (int o = 0; o < FDTD_R; ++o, su += Sb, sh2 += Sb) {
+            q[o] = Buf<T>::ld(R, vq, su);
+            q[TZ + 3 * FDTD_R + o] = Buf<T>::ld(R, vq, min(sh2, slast));
+        }
+        uint32_t so = zpo;
+#pragma unroll
+        for (int o = 0; o < PN; ++o, so += Spz) {
+            pz[o] = 0.0f;
+            if ((zm >> o) & 1u) pz[o] = Buf<float>::ld(R, vz, so);
+        }
+        uint32_t sz = zze + FDTD_R * Spz;
+#pragma unroll
+        for (int p = 0; p < TZ; ++p, sz += Spz) {
+            zz[p] = 0.0f;
+            if ((zm >> (p + FDTD_R)) & 1u) zz[p] = Buf<float>::ld(R, vz, sz);
+        }
+        const int zl = min(max(z0 - FDTD_R + (t & 15), 0), nz - 1);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) az[f] = prof(2, f, zl);
+    }
+
+    // ---- u^n of the box's planes and their halo to LDS ----
+    const int rn = ly < FDTD_R ? ly : ly + TY;   // row of yn in PY
+    float *const Uc = &U[0][ly + 8][lx + 8];     // the column's place in plane 0
+    constexpr int UP = UH * UW;
+#pragma unroll
+    for (int p = 0; p < TZ; ++p) {
+        Uc[p * UP] = q[p + 8];
+        U[p][rn + 4][lx + 8] = hyn[p];
+    }
+    const int cn = c8 < FDTD_R ? c8 : c8 + TX;   // column of xn in PX
+    U[hp][hr + 8][cn + 4] = hxn;
+    if (again(xb)) U[hp][hr + 8][c8 < FDTD_R ? cn : cn + 8] = hxf;
+    if (again(yb)) {
+#pragma unroll
+        for (int p = 0; p < TZ; ++p) U[p][ly < FDTD_R ? rn : rn + 8][lx + 8] = hyf[p];
+    }
+    __syncthreads();
+
+    // ---- new psi of the box grown by 4 along each axis; the box's own is stored ----
+    auto d1_lds = [&](const float *c, int stride, const float *w) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int l = 1; l <= 4; ++l) {
+            lo[l - 1] = c[-l * stride];
+            hi[l - 1] = c[l * stride];
+        }
+        return d1_axis(w, lo, hi);
+    };
+    const int np = nz - z0;   // planes of the box inside the grid (TZ or fewer)
+    if (again(xb)) {
+        const int n1 = again(np);
+#pragma unroll
+        for (int p = 0; p < TZ; ++p) {
+            dx[p] = d1_lds(Uc + p * UP, 1, w1[0]);
+            const float v = sx ? psi_update(ax[0], pxo[p], ax[1], dx[p]) : 0.0f;
+            PX[p][ly][lx + 4] = v;
+            if (p < n1) Buf<float>::stc(R, vx, xpn + p * Spx, v);
+        }
+        const float v = psi_update(ahx[0], pxh, ahx[1], d1_lds(&U[hp][hr + 8][cn + 4], 1, w1[0]));
+        PX[hp][hr][cn] = hsx ? v : 0.0f;
+    }
+    if (again(yb)) {
+        const int n1 = again(np);
+#pragma unroll
+        for (int p = 0; p < TZ; ++p) {
+            dy[p] = d1_lds(Uc + p * UP, UW, w1[1]);
+            const float v = sy ? psi_update(ay[0], pyo[p], ay[1], dy[p]) : 0.0f;
+            const float h = hsy ? psi_update(ahy[0], pyh[p], ahy[1], d1_lds(&U[p][rn + 4][lx + 8], UW, w1[1])) : 0.0f;
+            PY[p][ly + 4][lx] = v;
+            PY[p][rn][lx] = h;
+            if (p < n1) Buf<float>::stc(R, vy, ypn + p * Spy, v);
+        }
+    }
+    if (again(zb)) {
+        const uint32_t z1 = (uint32_t)again((int)zm);
+#pragma unroll
+        for (int o = 0; o < PN; ++o)
+            if (((z1 >> o) & 1u) || (o >= FDTD_R && o < FDTD_R + TZ)) {
+                float lo[4], hi[4];
+#pragma unroll
+                for (int l = 1; l <= 4; ++l) {
+                    lo[l - 1] = q[o + 4 - l];
+                    hi[l - 1] = q[o + 4 + l];
+                }
+                const float d1 = d1_axis(w1[2], lo, hi);
+                if (o >= FDTD_R && o < FDTD_R + TZ) dz[o - FDTD_R] = d1;
+                if (!((z1 >> o) & 1u)) continue;
+                pz[o] = psi_update(lane_value(az[0], o), pz[o], lane_value(az[1], o), d1);
+                if (o >= FDTD_R && o < FDTD_R + TZ) Buf<float>::stc(R, vz, zpn + o * Spz, pz[o]);
+            }
+    }
+    if (again(xb | yb)) __syncthreads();
+
+    // ---- the update ----
+    const int src_tile = uniform(s.sx >= x0 && s.sx < x0 + TX && s.sy >= y0 && s.sy < y0 + TY && s.sz >= z0 &&
+                                 s.sz < z0 + TZ);
+    float srcamp = 0.0f;
+    if (src_tile && s.wav != nullptr) {
+        const int n = *stepc + A.k;
+        if (n >= 0 && n < s.src_nt) srcamp = s.wav[n] * s.src_scale;
+    }
+    Coef K;
+    K.cc = s.cc;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) K.w2[d][l] = w2[d][l];
+#pragma unroll
+    for (int p = 0; p < TZ; ++p) {
+        if (p >= again(np)) break;
+        const float *c0 = Uc + p * UP;
+        float xl[4], xh[4], yl[4], yh[4], zl[4], zh[4];
+#pragma unroll
+        for (int l = 1; l <= 4; ++l) {
+            xl[l - 1] = c0[-l];
+            xh[l - 1] = c0[l];
+            yl[l - 1] = c0[-l * UW];
+            yh[l - 1] = c0[l * UW];
+            zl[l - 1] = q[p + 8 - l];
+            zh[l - 1] = q[p + 8 + l];
+        }
+        const float c = q[p + 8];
+        float lt;
+        if (!again(xb | yb | zb)) {
+            lt = lap_interior(K, c, xl, xh, yl, yh, zl, zh);
+        } else {
+            const bool bz = zb && in_band(again(z0 + p), nz, zlo, zhi);
+            float L[3] = {d2_axis(w2[0], c, xl, xh), d2_axis(w2[1], c, yl, yh), d2_axis(w2[2], c, zl, zh)};
+            if (again(xb)) {
+                float zn = 0.0f;
+                const float e = cpml_axis(L[0], dx[p], d1_lds(&PX[p][ly][lx + 4], 1, w1[0]), ax[2],
+                                          ax[3], ax[1], ax[0], sx, zx[p], &zn);
+                if (bx) L[0] = e;
+                Buf<float>::stc(R, vx, xze + p * Spx, zn);
+            }
+            if (again(yb)) {
+                float zn = 0.0f;
+                const float e = cpml_axis(L[1], dy[p], d1_lds(&PY[p][ly + 4][lx], TX, w1[1]), ay[2],
+                                          ay[3], ay[1], ay[0], sy, zy[p], &zn);
+                if (by) L[1] = e;
+                Buf<float>::stc(R, vy, yze + p * Spy, zn);
+            }
+            if (bz) {
+                float pl[4], ph[4], zn = 0.0f;
+#pragma unroll
+                for (int l = 1; l <= 4; ++l) {
+                    pl[l - 1] = pz[p + 4 - l];
+                    ph[l - 1] = pz[p + 4 + l];
+                }
+                const bool sz = ((uint32_t)again((int)zm) >> (p + 4)) & 1u;
+                L[2] = cpml_axis(L[2], dz[p], d1_axis(w1[2], pl, ph), lane_value(az[2], p + 4),
+                                 lane_value(az[3], p + 4), lane_value(az[1], p + 4), lane_value(az[0], p + 4), sz, zz[p],
+                                 &zn);
+                if (sz) Buf<float>::stc(R, vz, zze + (p + 4) * Spz, zn);
+            }
+            lt = (L[0] + L[1]) + L[2];
+            const bool none = act && !(bx || by || bz);
+            if (__any(none)) {
+                const float li = lap_interior(K, c, xl, xh, yl, yh, zl, zh);
+                if (none) lt = li;
+            }
+        }
+        const bool src = again(src_tile) && z0 + p == s.sz && x == s.sx && y == s.sy;
+        const Upd up = time_update<T>(mm[p], lt, c, second[p], src, srcamp);
+        Buf<T>::stc(R, vc, fw + p * Sb, up.u);
+        if constexpr (IsInc<T>::v) Buf<T>::stc(R, vc, fs + p * Sb, up.d);
+    }
+}
+
+// ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
+// before the box's own)
+template <typename T, bool ONE>
+__global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ shots, const TileDesc *__restrict__ descs,
+                                                 const TileItem *__restrict__ work, TileStep A,
+                                                 const int *__restrict__ stepc, const TileDesc one) {
+    const int t = (int)threadIdx.x;
+    if ((int)blockIdx.x >= A.nwork) {
+        // receivers of the step before this one (the newest level is complete now)
+        const int n = *stepc + A.k;
+        const DevShot &s = shots[A.rec_lo + (int)blockIdx.x - A.nwork];
+        if (s.traces == nullptr || n - 1 >= s.trace_cap) return;
+        const T *u = (const T *)s.u[A.iu];
+        for (int r = t; r < s.nrec; r += 256) {
+            const int32_t *q = s.rec + 3 * r;
+            const long c = (long)q[2] * s.S + (long)q[1] * s.P + q[0];
+            s.traces[(long)(n - 1) * s.nrec + r] = Store<T>::ld(u + c) * s.inv_scale;
+        }
+        return;
+    }
+    const TileItem wi = work[blockIdx.x];
+    if (wi.flags < 0) return;   // the idle items that pad the list
+    if constexpr (ONE) tile_box<T>(one, wi, A, stepc);
+    else tile_box<T>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+}
+
+template <typename T>
+static void launch_tile_t(const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
+                          int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
+    const dim3 grid((unsigned)(A.nwork + nrec));
+    if (one)
+        hipLaunchKernelGGL((k_tile<T, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
+    else
+        hipLaunchKernelGGL((k_tile<T, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, TileDesc{});
+}
+
+void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
+                      const TileStep &A, int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
+    if (A.nwork <= 0) return;
+    if (stor == 1) launch_tile_t<_Float16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
+    else if (stor == 2) launch_tile_t<__bf16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
+    else launch_tile_t<float>(d_shots, d_descs, work, A, nrec, stepc, one, st);
+}

@@ -48,6 +48,8 @@ extern "C" int fdtd_forward_static(const fdtd_shot_config *shot, const float *v_
     fdtd_ctx *ctx = nullptr;
     rc = fdtd_create(shot, 1, hip_stream, &ctx);
     if (rc) return rc;
+    // a shot whose state fits without the tile kernel's second psi buffers runs without it
+    if (ctx->need > (size_t)FDTD_STATIC_BYTES) fdtd_disable_tile(ctx);
     if (ctx->need > (size_t)FDTD_STATIC_BYTES) {
         fprintf(stderr, "fdtd_forward_static: the shot needs %zu bytes of device state; the static array holds %zu\n",
                 ctx->need, (size_t)FDTD_STATIC_BYTES);

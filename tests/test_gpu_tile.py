@@ -1,0 +1,187 @@
+"""The one-launch step of small shots (the automatic variant) against the
+naive kernel, bit for bit: every point goes through the same operations in the
+same order, so nothing may differ, in any storage, at any edge of a box
+(32 x 8 x 4 points), with layers that meet no, one, two or three axes of it,
+eager and as a graph, over a save, a change of plan, and in the adjoint's
+recomputation.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+AUTO, NAIVE, ZMARCH = 0, 1, 2
+
+# n, layers: whole boxes; one point over and one under; the smallest grid; layers wider than a box,
+# on one axis only, on one face only, almost meeting in the middle; no layer
+GEOMETRIES = [
+    ((64, 32, 24), (10, 10, 8, 8, 6, 6)),
+    ((65, 33, 25), (10, 7, 5, 8, 6, 3)),
+    ((63, 31, 23), (3, 12, 12, 3, 2, 9)),
+    ((9, 9, 9), (4, 4, 4, 4, 4, 4)),
+    ((100, 41, 38), (36, 40, 0, 0, 0, 0)),
+    ((37, 58, 30), (0, 0, 20, 25, 0, 0)),
+    ((34, 19, 61), (0, 0, 0, 0, 29, 28)),   # z layers too close for the tile kernel
+    ((34, 19, 61), (0, 0, 0, 0, 25, 24)),   # just far enough
+    ((40, 24, 20), (0, 6, 0, 0, 1, 0)),
+    ((33, 47, 29), (0,) * 6),
+]
+
+
+def _workload(n, cpml, nt, seed=3):
+    rng = np.random.default_rng(seed)
+    nx, ny, nz = n
+    v = 1800.0 + 900.0 * rng.uniform(size=(nz, ny, nx))
+    dt = synth.dt_from_courant(v.max(), (10.0, 11.0, 9.0)) * 0.9
+    u = [rng.standard_normal((nz, ny, nx)).astype(np.float32) * 1e-3 for _ in range(2)]
+    src = (nx // 3, ny // 2, nz // 2)
+    rec = np.stack([rng.integers(0, m, 12) for m in n], 1).astype(np.int32)
+    return v.astype(np.float32), dt, u, src, synth.ricker(nt, dt, 30.0).astype(np.float32), rec
+
+
+def _prop(cases, nt, variants, storage=0):
+    import torch
+
+    from paper_2606_06910_amd import Propagator, Shot
+
+    ws = [_workload(n, cpml, nt) for n, cpml in cases]
+    p = Propagator([Shot(n=n, h=(10.0, 11.0, 9.0), dt=w[1], cpml=cpml, variant=var, storage=storage,
+                         field_scale=1024.0 if storage else 0.0)
+                    for (n, cpml), w, var in zip(cases, ws, variants)])
+    traces = []
+    for i, (v, _, _, src, wav, rec) in enumerate(ws):
+        p.set_velocity(i, torch.from_numpy(v).cuda())
+        p.inject_source(i, src, torch.from_numpy(wav).cuda())
+        p.set_receivers(i, rec)
+        traces.append(p.record(i, nt))
+    return p, ws, traces
+
+
+def _start(p, ws):
+    """Both levels seeded noise over the whole grid, layers included."""
+    import torch
+
+    p.reset()
+    for i, w in enumerate(ws):
+        p.set_field(i, 0, torch.from_numpy(w[2][0]).cuda())
+        p.set_field(i, 1, torch.from_numpy(w[2][1]).cuda())
+
+
+def _out(p, traces):
+    import torch
+
+    torch.cuda.synchronize()
+    return [x.cpu().numpy().copy() for i in range(len(traces)) for x in (traces[i], p.get_field(i, 0), p.get_field(i, 1))]
+
+
+def _same(a, b):
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("storage", [0, 1, 2])
+@pytest.mark.parametrize("case", GEOMETRIES, ids=lambda c: "x".join(map(str, c[0])))
+def test_tile_step_equals_naive(case, storage):
+    nt = 15
+    got = []
+    for variant in (AUTO, NAIVE):
+        p, ws, tr = _prop([case], nt, [variant], storage)
+        _start(p, ws)
+        p.step(7)       # two calls, an odd number of steps in each
+        p.step(8)
+        got.append(_out(p, tr))
+        p.close()
+    assert np.abs(got[0][1]).max() > 0
+    _same(*got)
+
+
+def test_tile_batch_equals_single_shots():
+    """All geometries in one context (one launch over every shot), and beside shots of the other variants."""
+    nt = 12
+    single = []
+    for c in GEOMETRIES:
+        p, ws, tr = _prop([c], nt, [NAIVE])
+        _start(p, ws)
+        p.step(nt)
+        single += _out(p, tr)
+        p.close()
+    for variants in ([AUTO] * len(GEOMETRIES), [(AUTO, NAIVE, ZMARCH)[i % 3] for i in range(len(GEOMETRIES))]):
+        p, ws, tr = _prop(GEOMETRIES, nt, variants)
+        _start(p, ws)
+        p.step(5)
+        p.step(nt - 5)
+        _same(_out(p, tr), single)
+        p.close()
+
+
+def test_tile_graph_replays_equal_eager():
+    """A small shot's graph, replayed with eager work between, against the eager steps."""
+    nt = 9
+    p, ws, tr = _prop([GEOMETRIES[1]], 3 * nt, [AUTO])
+    _start(p, ws)
+    for _ in range(3):
+        p.step(nt)
+    ref = _out(p, tr)
+    for _ in range(3):
+        tr[0].zero_()
+        _start(p, ws)
+        for _ in range(3):
+            p.step(nt, graph=True)
+            p.check_finite()
+        _same(_out(p, tr), ref)
+    p.close()
+
+
+def test_tile_state_and_change_of_plan():
+    """Saved and restored at an odd step, and handed over to the other variants at one."""
+    nt, k = 16, 7
+    case = GEOMETRIES[1]
+    p, ws, tr = _prop([case], nt, [AUTO])
+    _start(p, ws)
+    p.step(k)
+    blob = p.save_state()
+    p.step(nt - k)
+    ref = _out(p, tr)
+    q, _, tq = _prop([case], nt, [AUTO])
+    q.step(2)
+    q.load_state(blob)
+    q.step(nt - k)
+    got = _out(q, tq)
+    assert np.array_equal(got[0][k:], ref[0][k:])
+    _same(got[1:], ref[1:])
+    for variant in (NAIVE, ZMARCH):
+        r, wr, trr = _prop([case], nt, [AUTO])
+        _start(r, wr)
+        r.step(k)
+        r.set_plan(0, variant, 2, 64)
+        r.step(nt - k)
+        _same(_out(r, trr), ref)
+        r.close()
+    p.close()
+    q.close()
+
+
+@pytest.mark.parametrize("every", [4, 7])
+def test_tile_gradient_equals_naive(every):
+    """Checkpoints, recomputation and gradient of two shots, batched and one by one."""
+    import torch
+
+    nt = 17
+    cases = [GEOMETRIES[1], GEOMETRIES[0]]
+    got = []
+    for variant in (AUTO, NAIVE):
+        p, ws, tr = _prop(cases, nt, [variant] * 2)
+        for i in range(2):
+            p.set_checkpointing(i, every, nt)
+        p.reset()
+        p.step(nt)
+        g = torch.Generator().manual_seed(1)
+        resid = [torch.randn(nt, 12, generator=g) for _ in range(2)]
+        grads = p.adjoint_all(nt, resid) + [p.adjoint(i, nt, resid[i]) for i in (1, 0)]
+        got.append([x.cpu().numpy() for x in tr + grads])
+        p.close()
+    assert np.abs(got[0][2]).max() > 0
+    assert np.array_equal(got[0][2], got[0][5]) and np.array_equal(got[0][3], got[0][4])
+    _same(*got)

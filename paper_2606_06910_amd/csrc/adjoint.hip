@@ -25,6 +25,7 @@
 // the FP64 accumulator is read and written once per G reverse steps, by a
 // pass over the last G levels, and not by every step.  One sweep covers one
 // shot or every shot of the context: each pass is one launch over all of them.
+#include "adj_tile.hpp"
 #include "fdtd_host.hpp"
 #include "fdtd_launch.hpp"
 
@@ -401,6 +402,8 @@ struct AdjLayout {
     // tables of a sweep over every shot of the context (those of a sweep's first shot are used):
     // AdjShot entries, increment jobs, checkpoint-restore jobs, the slab-pass and pass-3 block tables
     size_t tab = 0, jobs = 0, rjobs = 0, smap = 0, bmap = 0, bmap2 = 0;
+    // one-launch reverse step: the other psi_b, zeta_b buffers (no E, K, W, smap, bmap2), its descriptors and boxes
+    size_t psib2[3] = {}, zetab2[3] = {}, atab = 0, items = 0;
     size_t total = 0;
     int nck = 0;   // checkpoint slots
 };
@@ -416,7 +419,21 @@ static int grad_chunk(int every) {
 }
 static int mu_slots(int every) { return grad_chunk(every) + 1; }
 
+// Whether the sweeps of a context take the reverse step in one launch
+// (k_adj_tile) and not in passes: every shot's z window (TILE_Z + 16 planes)
+// meets one z layer at most, and 32 bits reach each field and the layer arrays.
+static bool adj_tiles(const fdtd_ctx *ctx) {
+    for (const ShotH &s : ctx->shots) {
+        if (s.Llo[2] > 0 && s.Lhi[2] > 0 && s.nz - s.Llo[2] - s.Lhi[2] < TILE_Z + 4 * FDTD_R) return false;
+        size_t b = 0;
+        for (int d = 0; d < 3; ++d) b += 4 * a256(s.psi_elems[d] * 4);
+        if (b >= (size_t)1 << 31 || s.elems * 4 >= (size_t)1 << 31) return false;
+    }
+    return true;
+}
+
 static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int nslots) {
+    const bool tiles = adj_tiles(ctx);
     AdjLayout L;
     size_t off = 0;
     auto take = [&](size_t b) {
@@ -425,21 +442,25 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
         return o;
     };
     const size_t nctx = ctx->shots.size();
-    long sblocks = 0, blocks = 0, blocks2 = 0;
+    long sblocks = 0, blocks = 0, blocks2 = 0, boxes = 0;
     for (const ShotH &t : ctx->shots) {
         const AdjCounts c = adj_counts(t);
         sblocks += c.slab_blocks();
         blocks += c.blocks(t);
         blocks2 += c.blocks2(t);
+        boxes += (long)fdtd_tile_count(t);
     }
     L.nck = nslots;
     L.ck = take(fdtd_state_bytes(s) * (size_t)L.nck);
     L.seg = take(a256(s.elems * s.esz) * (size_t)(every + 1) * 2);   // two segments' increments
     L.mu = take(a256(s.elems * 4) * (size_t)mu_slots(every));   // the ring of mu levels
     for (int d = 0; d < 3; ++d) {
-        const size_t full = (s.Llo[d] + s.Lhi[d]) > 0 ? s.elems * 4 : 0;
+        const size_t full = (s.Llo[d] + s.Lhi[d]) > 0 && !tiles ? s.elems * 4 : 0;
+        const size_t other = tiles ? s.psi_elems[d] * 4 : 0;
         L.psib[d] = take(s.psi_elems[d] * 4);
         L.zetab[d] = take(s.psi_elems[d] * 4);
+        L.psib2[d] = take(other);
+        L.zetab2[d] = take(other);
         L.E[d] = take(full);
         L.K[d] = take(full);
         L.W[d] = take(full);
@@ -449,9 +470,11 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
     L.tab = take(sizeof(AdjShot) * nctx);
     L.jobs = take(sizeof(DiffJob) * (size_t)(2 * (every + 1) * 2) * nctx);
     L.rjobs = take(sizeof(CopyJob) * (size_t)L.nck * 2 * 8 * nctx);
-    L.smap = take(sizeof(SlabBlock) * (size_t)std::max(sblocks, 1L));
+    L.smap = take(sizeof(SlabBlock) * (size_t)std::max(tiles ? 0L : sblocks, 1L));
     L.bmap = take(sizeof(int) * (size_t)std::max(blocks, 1L));
-    L.bmap2 = take(sizeof(int) * (size_t)std::max(blocks2, 1L));
+    L.bmap2 = take(sizeof(int) * (size_t)std::max(tiles ? 0L : blocks2, 1L));
+    L.atab = take(tiles ? sizeof(AdjTile) * nctx : 0);
+    L.items = take(tiles ? sizeof(TileItem) * (size_t)(boxes + fdtd_tile_slack()) : 0);
     L.total = off;
     return L;
 }
@@ -525,6 +548,9 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     std::vector<CopyJob> rjobs((size_t)nck * 2 * 8 * nsh);
     std::vector<SlabBlock> smap;
     std::vector<int> bmap, bmap2;
+    const bool tiles = adj_tiles(ctx);
+    std::vector<AdjTile> atab(tiles ? nsh : 0);
+    std::vector<TileItem> boxes;
     int bbase = 0, bbase2 = 0, maxg = 0;
     long maxrows = 0, maxck = 0;
     for (int q = 0; q < nsh; ++q) {
@@ -543,7 +569,10 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
             fdtd_launch_fill_zero(B + L.zetab[d], a256(s.psi_elems[d] * 4), st);
             a.psib[d] = (float *)(B + L.psib[d]);
             a.zetab[d] = (float *)(B + L.zetab[d]);
-            if (s.Llo[d] + s.Lhi[d] > 0) {
+            if (tiles) {
+                fdtd_launch_fill_zero(B + L.psib2[d], a256(s.psi_elems[d] * 4), st);
+                fdtd_launch_fill_zero(B + L.zetab2[d], a256(s.psi_elems[d] * 4), st);
+            } else if (s.Llo[d] + s.Lhi[d] > 0) {
                 fdtd_launch_fill_zero(B + L.E[d], a256(s.elems * 4), st);
                 fdtd_launch_fill_zero(B + L.K[d], a256(s.elems * 4), st);
                 fdtd_launch_fill_zero(B + L.W[d], a256(s.elems * 4), st);
@@ -592,16 +621,49 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         maxg = std::max(maxg, a.ngroups);
         // wave units of passes 1, 2 and blocks of pass 3
         const AdjCounts cnt = adj_counts(s);
-        for (int d = 0; d < 3; ++d)
+        for (int d = 0; d < 3 && !tiles; ++d)
             for (long t0 = 0; t0 < cnt.slab[d]; t0 += 256) smap.push_back(SlabBlock{q * 4 + d, (int)t0});
+        if (tiles) {
+            const DevShot &ds = a.s;
+            AdjTile &e = atab[q];
+            memset(&e, 0, sizeof e);
+            e.mu = B + L.mu;
+            e.mstride = a.mstride * 4;
+            e.m = fdtd_ws(ctx, s.o_m);
+            e.lay = B + L.psib[0];
+            for (int d = 0; d < 3; ++d) {
+                e.t_psib[0][d] = (uint32_t)(L.psib[d] - L.psib[0]);
+                e.t_psib[1][d] = (uint32_t)(L.psib2[d] - L.psib[0]);
+                e.t_zetab[0][d] = (uint32_t)(L.zetab[d] - L.psib[0]);
+                e.t_zetab[1][d] = (uint32_t)(L.zetab2[d] - L.psib[0]);
+                e.Llo[d] = ds.Llo[d];
+                e.Lhi[d] = ds.Lhi[d];
+            }
+            e.prof = ds.prof;
+            e.nx = ds.nx;
+            e.ny = ds.ny;
+            e.nz = ds.nz;
+            e.P = ds.P;
+            e.PY = ds.PY;
+            e.S = ds.S;
+            e.WX = ds.WX;
+            e.SY = ds.SY;
+            e.nmax = ds.nmax;
+            memcpy(e.w2, ds.w2, sizeof e.w2);
+            memcpy(e.w1, ds.w1, sizeof e.w1);
+            const std::vector<TileItem> b = fdtd_tile_boxes(s, q);
+            boxes.insert(boxes.end(), b.begin(), b.end());
+        }
         a.btx = cnt.btx;
         a.bty = cnt.bty;
         a.bbase = bbase;
         bbase += (int)cnt.blocks(s);
         bmap.insert(bmap.end(), (size_t)cnt.blocks(s), q);
         a.bbase2 = bbase2;
-        bbase2 += (int)cnt.blocks2(s);
-        bmap2.insert(bmap2.end(), (size_t)cnt.blocks2(s), q);
+        if (!tiles) {
+            bbase2 += (int)cnt.blocks2(s);
+            bmap2.insert(bmap2.end(), (size_t)cnt.blocks2(s), q);
+        }
         // checkpoint restore of segment k with u^n going to level buffer iu: u^n,
         // u^{n-1}, then psi_d and zeta_d of each axis, as the checkpoint stores them
         for (int k = 0; k < nck; ++k)
@@ -657,7 +719,16 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         AHIP(ctx, hipMemcpyAsync((void *)smap_d, smap.data(), sizeof(SlabBlock) * smap.size(), hipMemcpyHostToDevice,
                                  st));
     AHIP(ctx, hipMemcpyAsync((void *)bmap_d, bmap.data(), sizeof(int) * bmap.size(), hipMemcpyHostToDevice, st));
-    AHIP(ctx, hipMemcpyAsync((void *)bmap2_d, bmap2.data(), sizeof(int) * bmap2.size(), hipMemcpyHostToDevice, st));
+    if (!bmap2.empty())
+        AHIP(ctx, hipMemcpyAsync((void *)bmap2_d, bmap2.data(), sizeof(int) * bmap2.size(), hipMemcpyHostToDevice, st));
+    const AdjTile *atab_d = (const AdjTile *)(s0h.ck_buf + L0.atab);
+    const TileItem *items_d = (const TileItem *)(s0h.ck_buf + L0.items);
+    const std::vector<TileItem> items = fdtd_tile_deal(boxes);
+    if (tiles) {
+        AHIP(ctx, hipMemcpyAsync((void *)atab_d, atab.data(), sizeof(AdjTile) * atab.size(), hipMemcpyHostToDevice, st));
+        AHIP(ctx, hipMemcpyAsync((void *)items_d, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice,
+                                 st));
+    }
     AHIP(ctx, hipStreamSynchronize(st));
     // e of the newest level (in buffer qb) into slot j of half b, every shot in one launch
     auto store_increment = [&](int b, int j, int qb) {
@@ -715,7 +786,8 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
                 hipLaunchKernelGGL(k_adj_p1, dim3(nslab), dim3(256), 0, sa, tab_d, smap_d, as);
                 hipLaunchKernelGGL(k_adj_p2, dim3(nslab), dim3(256), 0, sa, tab_d, smap_d, as);
             }
-            hipLaunchKernelGGL(k_adj_p3, dim3((unsigned)bbase2), dim3(256), 0, sa, tab_d, bmap2_d, as);
+            if (tiles) fdtd_launch_adj_tile(atab_d, items_d, (int)items.size(), n, as.m0, as.m1, as.m2, sa);
+            else hipLaunchKernelGGL(k_adj_p3, dim3((unsigned)bbase2), dim3(256), 0, sa, tab_d, bmap2_d, as);
             if (top - n + 1 == chunk || n == s0) {
                 const AdjGrad ag{b, s0, n, top - n + 1};
                 hipLaunchKernelGGL(k_adj_grad, dim3((unsigned)bbase), dim3(256), 0, sa, tab_d, bmap_d, ag);

@@ -229,10 +229,11 @@ template <typename W> static std::vector<W> xcd_order(const std::vector<W> &sp) 
     return out;
 }
 
+size_t fdtd_tile_slack() { return 8 * kTilePiece; }
 // The tile kernel's boxes dealt to the XCDs in pieces of consecutive boxes: each XCD
 // gets its share of the layers' boxes (which cost several times an interior one), and the boxes
 // that share halo planes and rows still run together.
-static std::vector<TileItem> xcd_deal(const std::vector<TileItem> &sp) {
+std::vector<TileItem> fdtd_tile_deal(const std::vector<TileItem> &sp) {
     const size_t X = 8, piece = std::min(std::max(sp.size() / 32, (size_t)8), kTilePiece);
     std::vector<TileItem> out((sp.size() + X * piece - 1) / (X * piece) * X * piece, idle_item(sp));
     for (size_t i = 0; i < sp.size(); ++i) {
@@ -282,9 +283,12 @@ static std::vector<WorkItem> shot_tiles(const ShotH &s, int shot, int ry, int zc
     return v;
 }
 
+size_t fdtd_tile_count(const ShotH &s) {
+    return (size_t)((s.nx + TILE_X - 1) / TILE_X) * ((s.ny + TILE_Y - 1) / TILE_Y) * ((s.nz + TILE_Z - 1) / TILE_Z);
+}
 // boxes of the tile kernel, z fastest, then y: the boxes that share halo planes
 // and rows run close together on one XCD and find them in its L2
-static std::vector<TileItem> tile_boxes(const ShotH &s, int shot) {
+std::vector<TileItem> fdtd_tile_boxes(const ShotH &s, int shot) {
     // whether points c0 .. c0 + len - 1 (those below n) meet the band of an axis
     auto meets = [&](int d, int c0, int len, int n) {
         const int lo = s.Llo[d], hi = s.Lhi[d], c1 = std::min(c0 + len, n);
@@ -318,9 +322,7 @@ static bool tile_rule(const ShotH &s) {
     return b < (size_t)1 << 31;
 }
 static size_t tile_capacity(const ShotH &s) {
-    return s.tile ? (size_t)((s.nx + TILE_X - 1) / TILE_X) * ((s.ny + TILE_Y - 1) / TILE_Y) *
-                            ((s.nz + TILE_Z - 1) / TILE_Z) + 8 * kTilePiece
-                  : 0;
+    return s.tile ? fdtd_tile_count(s) + fdtd_tile_slack() : 0;
 }
 
 static size_t work_capacity(const ShotH &s) {
@@ -1210,7 +1212,7 @@ static int write_work_lists(fdtd_ctx *ctx) {
         ShotH &s = ctx->shots[i];
         s.nband = s.nwork = s.ntbwork = s.ntile = 0;
         if (s.tile) {
-            const std::vector<TileItem> bt = tile_boxes(s, (int)i), w = xcd_deal(bt);
+            const std::vector<TileItem> bt = fdtd_tile_boxes(s, (int)i), w = fdtd_tile_deal(bt);
             if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
             s.ntile = (int)w.size();
             if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
@@ -1250,7 +1252,7 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<BandItem> bw = xcd_order(band_all);
     ctx->nband_all = (int)bw.size();
     if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
-    const std::vector<TileItem> tw = xcd_deal(tile_all);
+    const std::vector<TileItem> tw = fdtd_tile_deal(tile_all);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
     return upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());

@@ -142,6 +142,10 @@ int fdtd_reupload(fdtd_ctx *ctx);
 int fdtd_ready(fdtd_ctx *ctx);
 int fdtd_zero_state(fdtd_ctx *ctx);
 void fdtd_disable_tile(fdtd_ctx *ctx);
+std::vector<TileItem> fdtd_tile_boxes(const ShotH &s, int shot);
+std::vector<TileItem> fdtd_tile_deal(const std::vector<TileItem> &boxes);
+size_t fdtd_tile_count(const ShotH &s);
+size_t fdtd_tile_slack();   // items that dealing may add to a list
 size_t fdtd_psi_off(const ShotH &s, int d, int iu);
 void fdtd_set_copy_vec(CopyJob &j);
 

@@ -26,29 +26,12 @@
 // kernels, record) and after: 64^3 19.5 -> 8.4 us, 101 x 87 x 119 (eager) 38 ->
 // 16 us, 160^3 100 -> 30 us (135 Gpts/s, 3.8 TB/s of the algorithmic bytes),
 // 24 batched shots of 96 .. 288 points per axis 1.45 -> 1.22 ms.
-#include "fdtd_dev.hpp"
 #include "fdtd_launch.hpp"
+#include "tile_dev.hpp"
 
 namespace {
-constexpr int TX = TILE_X, TY = TILE_Y, TZ = TILE_Z;
 constexpr int UW = TX + 4 * FDTD_R, UH = TY + 4 * FDTD_R;   // LDS plane of u^n: 8 columns and rows on each side
 constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, new psi_y columns: 4 on each side
-static_assert(TX * TY == 256 && TZ == 4 && 2 * FDTD_R * TY * TZ == 256 && TY == 2 * FDTD_R, "lane maps below");
-
-__device__ __forceinline__ bool slab_point(int c, int n, int lo, int hi) {
-    return c >= 0 && c < n && in_slab(c, n, lo, hi);
-}
-__device__ __forceinline__ float lane_value(float v, int lane) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-// the same scalar, its later tests computed anew: a test kept from one phase to the next costs two scalar
-// registers each, and the kernel has none to spare
-__device__ __forceinline__ int again(int v) {
-    v = uniform(v);
-    asm("" : "+s"(v));
-    return v;
-}
 // the descriptors read as constant memory: no store of the kernel changes them, so they may be loaded at once
 typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
 }  // namespace
@@ -201,12 +184,8 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     float pz[PN], zz[TZ], dz[TZ], az[4];
     uint32_t zm = 0, zpn = 0, zze = 0;   // new psi and zeta at plane z0 - 4
     if (zb) {
-        auto bits = [&](int lo, int hi) -> uint32_t {   // bits of planes lo .. hi - 1
-            const int a = min(max(lo - z0 + FDTD_R, 0), PN), b = min(max(hi - z0 + FDTD_R, 0), PN);
-            return ((1u << b) - 1u) & ~((1u << a) - 1u);
-        };
-        const uint32_t zlm = bits(0, zlo);
-        zm = zlm | bits(nz - zhi, nz);
+        const uint32_t zlm = plane_bits<PN>(z0 - FDTD_R, 0, zlo);
+        zm = zlm | plane_bits<PN>(z0 - FDTD_R, nz - zhi, nz);
         // slab position of plane z0 - 4 (as if it lay in the layer of the window)
         const uint32_t fo = (uint32_t)(z0 - FDTD_R + (zlm ? 0 : zlo - (nz - zhi))) * Spz;
         const uint32_t zpo = s.t_psi[A.iu][2] + fo;
@@ -255,15 +234,6 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     __syncthreads();
 
     // ---- new psi of the box grown by 4 along each axis; the box's own is stored ----
-    auto d1_lds = [&](const float *c, int stride, const float *w) {
-        float lo[4], hi[4];
-#pragma unroll
-        for (int l = 1; l <= 4; ++l) {
-            lo[l - 1] = c[-l * stride];
-            hi[l - 1] = c[l * stride];
-        }
-        return d1_axis(w, lo, hi);
-    };
     const int np = nz - z0;   // planes of the box inside the grid (TZ or fewer)
     if (again(xb)) {
         const int n1 = again(np);

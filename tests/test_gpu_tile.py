@@ -185,3 +185,42 @@ def test_tile_gradient_equals_naive(every):
     assert np.abs(got[0][2]).max() > 0
     assert np.array_equal(got[0][2], got[0][5]) and np.array_equal(got[0][3], got[0][4])
     _same(*got)
+
+
+# z layers (where there are two) at least 20 planes apart: the reverse step in one launch
+ADJOINT_GEOMETRIES = [
+    ((64, 32, 33), (10, 10, 8, 8, 6, 6)),
+    ((65, 33, 30), (10, 7, 5, 8, 6, 3)),
+    ((63, 31, 31), (3, 12, 12, 3, 2, 9)),
+    ((100, 41, 38), (36, 40, 0, 0, 0, 0)),
+    ((37, 58, 30), (0, 0, 20, 25, 0, 0)),
+    ((40, 24, 20), (0, 6, 0, 0, 1, 0)),
+    ((20, 19, 60), (9, 9, 9, 9, 15, 25)),
+    ((33, 47, 29), (0,) * 6),
+]
+
+
+@pytest.mark.parametrize("case", ADJOINT_GEOMETRIES, ids=lambda c: "x".join(map(str, c[0])))
+def test_adjoint_in_one_launch_equals_passes(case):
+    """The one-launch reverse step against the three passes, bit for bit: a shot whose z layers are too close for
+    the one launch puts every sweep of its context on the passes."""
+    import torch
+
+    nt = 13
+    close = ((24, 20, 30), (4, 4, 4, 4, 8, 8))
+    got = []
+    for cases in ([case], [case, close]):
+        p, ws, tr = _prop(cases, nt, [ZMARCH] * len(cases))
+        for i in range(len(cases)):
+            p.set_checkpointing(i, 5, nt)
+        p.reset()
+        for i, w in enumerate(ws):
+            p.set_field(i, 0, torch.from_numpy(w[2][0]).cuda())
+            p.set_field(i, 1, torch.from_numpy(w[2][1]).cuda())
+        p.step(nt)
+        g = torch.Generator().manual_seed(2)
+        grad = p.adjoint(0, nt, torch.randn(nt, 12, generator=g))
+        got.append(grad.cpu().numpy())
+        p.close()
+    assert np.abs(got[0]).max() > 0
+    assert np.array_equal(got[0], got[1])

@@ -50,8 +50,9 @@ typedef struct {
     double kappa_max;        /* default 5                                               */
     double alpha_frac;       /* alpha_max / sigma_max, default 0.05                     */
     int32_t variant;         /* 1: one thread per point; 2: z-marching stages (LDS xy
-                                planes, register queue along z); 0: 2 from 2^24
-                                points up, else 1.  Both give the same bits.            */
+                                planes, register queue along z); 0: both stages in
+                                one launch where a field is below 2 GiB, else 2.  All
+                                give the same bits.                                     */
 } fdtd_pv_config;
 
 /* Create a context on hip_stream (a hipStream_t, may be NULL).  EINVAL for a
@@ -63,7 +64,8 @@ typedef struct {
 int fdtd_pv_create(const fdtd_pv_config *cfg, void *hip_stream, fdtd_pv_ctx **out);
 
 /* Bytes of device workspace: p, v_x, v_y, v_z and the six memory-variable
- * fields (each padded by 4 points on every side), and the profiles. */
+ * fields (each padded by 4 points on every side), a second buffer of p, v and
+ * the three psi_v where both stages run in one launch, and the profiles. */
 int fdtd_pv_workspace_size(const fdtd_pv_ctx *ctx, size_t *bytes);
 
 /* Hand the context a device workspace of at least fdtd_pv_workspace_size
@@ -87,7 +89,7 @@ int fdtd_pv_set_source(fdtd_pv_ctx *ctx, int32_t i, int32_t j, int32_t k, const 
  * for a receiver outside the grid (checked on the host: synchronises). */
 int fdtd_pv_set_receivers(fdtd_pv_ctx *ctx, const int32_t *rec_dev, int32_t nrec, float *traces_dev, int32_t cap);
 
-/* Advance nsteps steps (two kernels per step, plus the receiver gather). */
+/* Advance nsteps steps (one kernel per step, or two, plus the receiver gather). */
 int fdtd_pv_step(fdtd_pv_ctx *ctx, int32_t nsteps);
 
 /* Message of the last failed call on this context. */

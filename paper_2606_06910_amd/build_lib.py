@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfdtd.so")
 SOURCES = ["fdtd_api.hip", "kernels_step.hip", "kernels_misc.hip", "adjoint.hip", "autotune.hip", "kernels_tblock.hip",
-           "kernels_band.hip", "kernels_tile.hip", "kernels_adj_tile.hip", "pv_api.hip", "static_api.hip"]
+           "kernels_band.hip", "kernels_tile.hip", "kernels_adj_tile.hip",
+           "pv_api.hip", "kernels_pv_tile.hip", "static_api.hip"]
 FLAGS = [
     "--offload-arch=gfx950",
     "-O3",

@@ -448,7 +448,7 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
         sblocks += c.slab_blocks();
         blocks += c.blocks(t);
         blocks2 += c.blocks2(t);
-        boxes += (long)fdtd_tile_count(t);
+        boxes += (long)fdtd_tile_grid(t, 0).boxes();
     }
     L.nck = nslots;
     L.ck = take(fdtd_state_bytes(s) * (size_t)L.nck);
@@ -474,7 +474,7 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
     L.bmap = take(sizeof(int) * (size_t)std::max(blocks, 1L));
     L.bmap2 = take(sizeof(int) * (size_t)std::max(tiles ? 0L : blocks2, 1L));
     L.atab = take(tiles ? sizeof(AdjTile) * nctx : 0);
-    L.items = take(tiles ? sizeof(TileItem) * (size_t)(boxes + fdtd_tile_slack()) : 0);
+    L.items = take(tiles ? sizeof(TileItem) * tile_list_bound((size_t)boxes) : 0);
     L.total = off;
     return L;
 }
@@ -550,7 +550,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     std::vector<int> bmap, bmap2;
     const bool tiles = adj_tiles(ctx);
     std::vector<AdjTile> atab(tiles ? nsh : 0);
-    std::vector<TileItem> boxes;
+    std::vector<TileGrid> grids;
     int bbase = 0, bbase2 = 0, maxg = 0;
     long maxrows = 0, maxck = 0;
     for (int q = 0; q < nsh; ++q) {
@@ -651,8 +651,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
             e.nmax = ds.nmax;
             memcpy(e.w2, ds.w2, sizeof e.w2);
             memcpy(e.w1, ds.w1, sizeof e.w1);
-            const std::vector<TileItem> b = fdtd_tile_boxes(s, q);
-            boxes.insert(boxes.end(), b.begin(), b.end());
+            grids.push_back(fdtd_tile_grid(s, q));
         }
         a.btx = cnt.btx;
         a.bty = cnt.bty;
@@ -723,7 +722,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         AHIP(ctx, hipMemcpyAsync((void *)bmap2_d, bmap2.data(), sizeof(int) * bmap2.size(), hipMemcpyHostToDevice, st));
     const AdjTile *atab_d = (const AdjTile *)(s0h.ck_buf + L0.atab);
     const TileItem *items_d = (const TileItem *)(s0h.ck_buf + L0.items);
-    const std::vector<TileItem> items = fdtd_tile_deal(boxes);
+    const std::vector<TileItem> items = tile_list(grids);
     if (tiles) {
         AHIP(ctx, hipMemcpyAsync((void *)atab_d, atab.data(), sizeof(AdjTile) * atab.size(), hipMemcpyHostToDevice, st));
         AHIP(ctx, hipMemcpyAsync((void *)items_d, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice,

@@ -12,6 +12,7 @@
 #include "../../include/fdtd.h"
 #include "fdtd_launch.hpp"
 #include "fdtd_host.hpp"
+#include "tile_host.hpp"
 
 #include <algorithm>
 #include <array>
@@ -216,7 +217,6 @@ template <> WorkItem idle_item(const std::vector<WorkItem> &sp) {
 template <> BandItem idle_item(const std::vector<BandItem> &sp) {
     return BandItem{sp.empty() ? 0 : sp[0].shot, 0, 1 << 20, 0, 0, 0, 0, 0};
 }
-template <> TileItem idle_item(const std::vector<TileItem> &) { return TileItem{-1, 0, 0, 0}; }
 template <typename W> static std::vector<W> xcd_order(const std::vector<W> &sp) {
     const int X = 8;
     size_t N = (sp.size() + X - 1) / X * X;
@@ -226,21 +226,6 @@ template <typename W> static std::vector<W> xcd_order(const std::vector<W> &sp) 
         size_t src = (w % X) * per + w / X;
         out[w] = src < sp.size() ? sp[src] : idle_item(sp);
     }
-    return out;
-}
-
-size_t fdtd_tile_slack() { return 8 * kTilePiece; }
-// The tile kernel's boxes dealt to the XCDs in pieces of consecutive boxes: each XCD
-// gets its share of the layers' boxes (which cost several times an interior one), and the boxes
-// that share halo planes and rows still run together.
-std::vector<TileItem> fdtd_tile_deal(const std::vector<TileItem> &sp) {
-    const size_t X = 8, piece = std::min(std::max(sp.size() / 32, (size_t)8), kTilePiece);
-    std::vector<TileItem> out((sp.size() + X * piece - 1) / (X * piece) * X * piece, idle_item(sp));
-    for (size_t i = 0; i < sp.size(); ++i) {
-        const size_t c = i / piece;
-        out[(c / X * piece + i % piece) * X + c % X] = sp[i];
-    }
-    while (!out.empty() && out.back().flags < 0) out.pop_back();
     return out;
 }
 
@@ -283,26 +268,13 @@ static std::vector<WorkItem> shot_tiles(const ShotH &s, int shot, int ry, int zc
     return v;
 }
 
-size_t fdtd_tile_count(const ShotH &s) {
-    return (size_t)((s.nx + TILE_X - 1) / TILE_X) * ((s.ny + TILE_Y - 1) / TILE_Y) * ((s.nz + TILE_Z - 1) / TILE_Z);
-}
-// boxes of the tile kernel, z fastest, then y: the boxes that share halo planes
-// and rows run close together on one XCD and find them in its L2
-std::vector<TileItem> fdtd_tile_boxes(const ShotH &s, int shot) {
-    // whether points c0 .. c0 + len - 1 (those below n) meet the band of an axis
-    auto meets = [&](int d, int c0, int len, int n) {
-        const int lo = s.Llo[d], hi = s.Lhi[d], c1 = std::min(c0 + len, n);
-        return (lo > 0 && c0 < lo + FDTD_R) || (hi > 0 && c1 > n - hi - FDTD_R);
-    };
-    std::vector<TileItem> v;
-    for (int x0 = 0; x0 < s.nx; x0 += TILE_X)
-        for (int y0 = 0; y0 < s.ny; y0 += TILE_Y)
-            for (int z0 = 0; z0 < s.nz; z0 += TILE_Z)
-                v.push_back(TileItem{shot | (meets(0, x0, TILE_X, s.nx) ? TILE_XB : 0) |
-                                         (meets(1, y0, TILE_Y, s.ny) ? TILE_YB : 0) |
-                                         (meets(2, z0, TILE_Z, s.nz) ? TILE_ZB : 0),
-                                     x0, y0, z0});
-    return v;
+TileGrid fdtd_tile_grid(const ShotH &s, int shot) {
+    TileGrid g{{s.nx, s.ny, s.nz}, {}, {}, shot};
+    for (int d = 0; d < 3; ++d) {
+        g.lo[d] = s.Llo[d];
+        g.hi[d] = s.Lhi[d];
+    }
+    return g;
 }
 // Whether a shot takes the tile kernel (reported as the variant it replaces): the
 // automatic variant, no ghost faces, a z window of the kernel (TILE_Z + 8 planes)
@@ -322,7 +294,7 @@ static bool tile_rule(const ShotH &s) {
     return b < (size_t)1 << 31;
 }
 static size_t tile_capacity(const ShotH &s) {
-    return s.tile ? fdtd_tile_count(s) + fdtd_tile_slack() : 0;
+    return s.tile ? tile_list_bound(fdtd_tile_grid(s, 0).boxes()) : 0;
 }
 
 static size_t work_capacity(const ShotH &s) {
@@ -1199,7 +1171,7 @@ int fdtd_workspace_size(const fdtd_ctx *ctx, size_t *bytes) {
 static int write_work_lists(fdtd_ctx *ctx) {
     std::map<std::array<int, 3>, std::vector<WorkItem>> byplan;
     std::vector<BandItem> band_all;
-    std::vector<TileItem> tile_all;
+    std::vector<TileGrid> tile_all;
     // (the copies read host memory until the stream is synchronised: every list lives until then)
     auto upload = [&](size_t o, const void *src, size_t bytes) -> int {
         if (bytes == 0) return FDTD_OK;
@@ -1212,11 +1184,12 @@ static int write_work_lists(fdtd_ctx *ctx) {
         ShotH &s = ctx->shots[i];
         s.nband = s.nwork = s.ntbwork = s.ntile = 0;
         if (s.tile) {
-            const std::vector<TileItem> bt = fdtd_tile_boxes(s, (int)i), w = fdtd_tile_deal(bt);
+            const TileGrid g = fdtd_tile_grid(s, (int)i);
+            const std::vector<TileItem> w = tile_list({g});
             if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
             s.ntile = (int)w.size();
             if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
-            tile_all.insert(tile_all.end(), bt.begin(), bt.end());
+            tile_all.push_back(g);
             continue;
         }
         const std::vector<BandItem> bt = band_tiles(s, (int)i, ctx->band_ty), bw = xcd_order(bt);
@@ -1252,7 +1225,7 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<BandItem> bw = xcd_order(band_all);
     ctx->nband_all = (int)bw.size();
     if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
-    const std::vector<TileItem> tw = fdtd_tile_deal(tile_all);
+    const std::vector<TileItem> tw = tile_list(tile_all);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
     return upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());

@@ -3,6 +3,7 @@
 #pragma once
 #include "../../include/fdtd.h"
 #include "fdtd_dev.hpp"
+#include "tile_host.hpp"
 
 #include <map>
 #include <string>
@@ -17,7 +18,6 @@ constexpr int kBandTX = BAND_TX, kBandZ = 32;   // band-kernel tile width and z 
 constexpr int kCUs = 256;   // compute units of an MI355X (the default z-march plan shares them)
 constexpr long kTileShot = 60000000, kTileShot16 = 30000000;   // shots below this many points (FP32, 16-bit
                                                                // storage) take the tile kernel by default
-constexpr size_t kTilePiece = 512;   // most consecutive boxes of the tile kernel that go to one XCD
 constexpr long kSmallShot = 150L * 150 * 150;   // a lone shot below this many points runs naive by default
 
 struct ShotH {
@@ -142,10 +142,7 @@ int fdtd_reupload(fdtd_ctx *ctx);
 int fdtd_ready(fdtd_ctx *ctx);
 int fdtd_zero_state(fdtd_ctx *ctx);
 void fdtd_disable_tile(fdtd_ctx *ctx);
-std::vector<TileItem> fdtd_tile_boxes(const ShotH &s, int shot);
-std::vector<TileItem> fdtd_tile_deal(const std::vector<TileItem> &boxes);
-size_t fdtd_tile_count(const ShotH &s);
-size_t fdtd_tile_slack();   // items that dealing may add to a list
+TileGrid fdtd_tile_grid(const ShotH &s, int shot);
 size_t fdtd_psi_off(const ShotH &s, int d, int iu);
 void fdtd_set_copy_vec(CopyJob &j);
 

@@ -8,7 +8,8 @@
 //  k_pv_pres  pressure stage: p -= lambda sum_d (kinv_d delta_d v_d + psi_p,d),
 //             then the point source
 //  k_pv_vel_zm, k_pv_pres_zm  the same stages z-marching: register queue of
-//             the z taps, x / y taps from an LDS plane (the default variant)
+//             the z taps, x / y taps from an LDS plane
+//  k_pv_tile  both stages in one launch (kernels_pv_tile.hip; the automatic variant)
 //  k_pv_rec   receiver gather
 //
 // Layout: every field x fastest with a zero frame of 4 points on each side
@@ -17,6 +18,8 @@
 // thread per point; the neighbours of a stencil come through the caches.
 #include "../../include/fdtd.h"
 #include "../../include/fdtd_pv.h"
+#include "pv_tile.hpp"
+#include "tile_host.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -432,6 +435,11 @@ struct fdtd_pv_ctx {
     int nmax = 0;
     long P = 0, S = 0;
     size_t elems = 0, field_bytes = 0, prof_bytes = 0, total = 0;
+    // one-launch step (k_pv_tile): p, v and psi_v in two buffers each (fields 0 .. 6 and kNF .. kNF + 6, `par`
+    // says which hold the state), and its box list
+    bool tile = false;
+    int par = 0, nwork = 0;
+    size_t o_prof = 0, o_work = 0;
     std::vector<float> prof;
     char *ws = nullptr;
     int src[3] = {-1, -1, -1};
@@ -444,6 +452,16 @@ struct fdtd_pv_ctx {
     long step = 0;       // steps since the workspace was bound (source sample index)
     long rec0 = 0;       // step at which the receivers were set (trace row 0)
 
+    TileGrid grid() const {
+        TileGrid g{};
+        for (int d = 0; d < 3; ++d) {
+            g.n[d] = n[d];
+            g.lo[d] = lo[d];
+            g.hi[d] = hi[d];
+        }
+        return g;
+    }
+    int cur(int f, int parity) const { return parity && f < 7 ? kNF + f : f; }   // buffer of field f
     float *field(int f) const { return (float *)(ws + (size_t)f * field_bytes) + kLead + 4 * S + 4 * P; }
 };
 
@@ -472,7 +490,7 @@ static PvArgs pv_args(const fdtd_pv_ctx *ctx) {
         g.hi[d] = ctx->hi[d];
         g.src[d] = ctx->src[d];
     }
-    g.prof = (const float *)(ctx->ws + (size_t)kNF * ctx->field_bytes);
+    g.prof = (const float *)(ctx->ws + ctx->o_prof);
     g.wav = ctx->wav;
     g.wav_n = ctx->wav_n;
     g.nmax = ctx->nmax;
@@ -520,7 +538,14 @@ int fdtd_pv_create(const fdtd_pv_config *cfg, void *hip_stream, fdtd_pv_ctx **ou
     ctx->elems = (size_t)kLead + (size_t)(ctx->n[2] + 2 * kR) * ctx->S + (size_t)(kTY + 2 * kR) * ctx->P + 128;
     ctx->field_bytes = a256(ctx->elems * 4);
     ctx->prof_bytes = a256((size_t)3 * 3 * ctx->nmax * 4);
-    ctx->total = (size_t)kNF * ctx->field_bytes + ctx->prof_bytes;
+    // (the automatic variant: the one launch wins at every size measured, 48^3 to 640^3)
+    ctx->tile = cfg->variant == 0 && ctx->field_bytes < ((size_t)1 << 31);
+    ctx->o_prof = (size_t)(ctx->tile ? kNF + 7 : kNF) * ctx->field_bytes;
+    ctx->o_work = ctx->o_prof + ctx->prof_bytes;
+    ctx->total = ctx->o_work;
+    if (ctx->tile) {
+        ctx->total += a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
+    }
     ctx->prof.assign((size_t)3 * 3 * ctx->nmax, 0.0f);
     for (int d = 0; d < 3; ++d) {
         float *base = ctx->prof.data() + (size_t)d * 3 * ctx->nmax;
@@ -542,15 +567,23 @@ int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
     if (((uintptr_t)dev_ptr) & 255) PVFAIL(ctx, FDTD_EINVAL, "workspace must be 256-byte aligned");
     if (bytes < ctx->total) PVFAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, ctx->total);
     ctx->ws = (char *)dev_ptr;
-    const size_t n16 = ((size_t)kNF * ctx->field_bytes) / 16;
+    const size_t n16 = ctx->o_prof / 16;
     hipLaunchKernelGGL(k_pv_zero, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 65536)), dim3(256), 0, ctx->st,
                        (uint4 *)ctx->ws, n16);
     PVHIP(ctx, hipGetLastError());
-    PVHIP(ctx, hipMemcpyAsync(ctx->ws + (size_t)kNF * ctx->field_bytes, ctx->prof.data(), ctx->prof.size() * 4,
-                              hipMemcpyHostToDevice, ctx->st));
+    PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_prof, ctx->prof.data(), ctx->prof.size() * 4, hipMemcpyHostToDevice,
+                              ctx->st));
+    std::vector<TileItem> work;
+    if (ctx->tile) {
+        work = tile_list({ctx->grid()});
+        ctx->nwork = (int)work.size();
+        PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_work, work.data(), sizeof(TileItem) * work.size(),
+                                  hipMemcpyHostToDevice, ctx->st));
+    }
     PVHIP(ctx, hipStreamSynchronize(ctx->st));
     ctx->step = 0;
     ctx->rec0 = 0;
+    ctx->par = 0;
     return FDTD_OK;
 }
 
@@ -564,12 +597,12 @@ static int pv_copy(fdtd_pv_ctx *ctx, float *dst, const float *src, int to_padded
 
 int fdtd_pv_set_pressure(fdtd_pv_ctx *ctx, const float *p_dev) {
     if (!ctx || !p_dev) return FDTD_EINVAL;
-    return pv_copy(ctx, ctx->ws ? ctx->field(0) : nullptr, p_dev, 1);
+    return pv_copy(ctx, ctx->ws ? ctx->field(ctx->cur(0, ctx->par)) : nullptr, p_dev, 1);
 }
 
 int fdtd_pv_get_pressure(fdtd_pv_ctx *ctx, float *p_dev) {
     if (!ctx || !p_dev) return FDTD_EINVAL;
-    return pv_copy(ctx, p_dev, ctx->ws ? ctx->field(0) : nullptr, 0);
+    return pv_copy(ctx, p_dev, ctx->ws ? ctx->field(ctx->cur(0, ctx->par)) : nullptr, 0);
 }
 
 int fdtd_pv_set_source(fdtd_pv_ctx *ctx, int32_t i, int32_t j, int32_t k, const float *w_dev, int32_t nt) {
@@ -603,16 +636,59 @@ int fdtd_pv_set_receivers(fdtd_pv_ctx *ctx, const int32_t *rec_dev, int32_t nrec
     return FDTD_OK;
 }
 
+// nsteps steps of one launch each; a step's receivers are recorded by the next
+// step's launch, the last one's by a launch of their own
+static int pv_step_tile(fdtd_pv_ctx *ctx, int nsteps) {
+    auto first = [&](int f) { return (float *)(ctx->ws + (size_t)f * ctx->field_bytes); };
+    const PvArgs a = pv_args(ctx);
+    PvTile g;
+    g.prof = a.prof;
+    g.wav = a.wav;
+    g.wav_n = a.wav_n;
+    g.rec = ctx->rec;
+    g.nmax = a.nmax;
+    g.nwork = ctx->nwork;
+    g.P = (int)ctx->P;
+    g.S = (int)ctx->S;
+    g.lam = a.lam;
+    for (int l = 0; l <= kR; ++l) g.w[l] = a.w[l];
+    for (int d = 0; d < 3; ++d) {
+        g.n[d] = a.n[d];
+        g.lo[d] = a.lo[d];
+        g.hi[d] = a.hi[d];
+        g.src[d] = a.src[d];
+        g.psp[d] = first(7 + d);
+    }
+    float *row = nullptr;   // where the last step's receivers go
+    for (int s = 0; s < nsteps; ++s) {
+        for (int f = 0; f < 7; ++f) {
+            g.in[f] = first(ctx->cur(f, ctx->par));
+            g.out[f] = first(ctx->cur(f, ctx->par ^ 1));
+        }
+        g.step = (int)ctx->step;
+        g.row = row;
+        g.nrec = row ? ctx->nrec : 0;
+        pv_launch_tile(g, (const TileItem *)(ctx->ws + ctx->o_work), ctx->st);
+        const long r = ctx->step - ctx->rec0;
+        row = ctx->nrec > 0 && r < ctx->cap ? ctx->traces + (size_t)r * ctx->nrec : nullptr;
+        ctx->par ^= 1;
+        ++ctx->step;
+    }
+    if (row)
+        hipLaunchKernelGGL(k_pv_rec, dim3((ctx->nrec + 255) / 256), dim3(256), 0, ctx->st,
+                           (const float *)ctx->field(ctx->cur(0, ctx->par)), ctx->rec, ctx->nrec, ctx->P, ctx->S, row);
+    PVHIP(ctx, hipGetLastError());
+    return FDTD_OK;
+}
+
 int fdtd_pv_step(fdtd_pv_ctx *ctx, int32_t nsteps) {
     if (!ctx || nsteps < 0) return FDTD_EINVAL;
     if (!ctx->ws) PVFAIL(ctx, FDTD_ESTATE, "no workspace bound");
+    if (ctx->tile) return pv_step_tile(ctx, nsteps);
     const dim3 grid((ctx->n[0] + 63) / 64, (ctx->n[1] + 3) / 4, ctx->n[2]), block(64, 4);
     const dim3 zgrid((ctx->n[0] + 63) / 64, (ctx->n[1] + kTY - 1) / kTY, (ctx->n[2] + kZC - 1) / kZC),
         zblock(64, kNW);
-    // automatic choice: the z-march from 2^24 points up (measured crossover between
-    // 224^3 and 256^3: below it its workgroups fill the chip in too few rounds)
-    const double npts = (double)ctx->n[0] * ctx->n[1] * ctx->n[2];
-    const bool naive = ctx->c.variant == 1 || (ctx->c.variant == 0 && npts < (double)(1L << 24));
+    const bool naive = ctx->c.variant == 1;
     for (int s = 0; s < nsteps; ++s) {
         PvArgs g = pv_args(ctx);
         if (naive) {

@@ -494,16 +494,18 @@ static void fill_desc(fdtd_ctx *ctx, int i) {
 
 static int upload_desc(fdtd_ctx *ctx) {
     for (size_t i = 0; i < ctx->shots.size(); ++i) fill_desc(ctx, (int)i);
-    HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), ctx->hdesc.data(), sizeof(DevShot) * ctx->hdesc.size(),
-                               hipMemcpyHostToDevice, ctx->stream));
-    bool any_tile = false;
-    for (const ShotH &s : ctx->shots) any_tile = any_tile || s.tile;
-    if (any_tile) {
-        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_tdesc), ctx->htile.data(), sizeof(TileDesc) * ctx->htile.size(),
-                                   hipMemcpyHostToDevice, ctx->stream));
-        fdtd_clear_graphs(ctx);   // a launch over one tile shot carries its descriptor as it was
-    }
+    // both descriptor arrays in one copy (the second follows the first in the workspace)
+    const size_t nd = sizeof(DevShot) * ctx->hdesc.size(), nt = sizeof(TileDesc) * ctx->htile.size(), at = align256(nd);
+    std::vector<char> both(at + nt);
+    memcpy(both.data(), ctx->hdesc.data(), nd);
+    memcpy(both.data() + at, ctx->htile.data(), nt);
+    HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), both.data(), both.size(), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    for (const ShotH &s : ctx->shots)
+        if (s.tile) {
+            fdtd_clear_graphs(ctx);   // a launch over one tile shot carries its descriptor as it was
+            break;
+        }
     return FDTD_OK;
 }
 
@@ -1010,6 +1012,7 @@ static void layout(fdtd_ctx *ctx) {
     ctx->o_stepc = take(256);
     ctx->o_scratch = take(256);
     ctx->o_desc = take(sizeof(DevShot) * nshots);
+    ctx->o_tdesc = take(sizeof(TileDesc) * nshots);   // (upload_desc copies both at once)
     size_t cap_all = 0;
     for (auto &s : ctx->shots) cap_all += work_capacity(s) + 8;
     ctx->o_work_all = take(sizeof(WorkItem) * cap_all);
@@ -1047,7 +1050,6 @@ static void layout(fdtd_ctx *ctx) {
         s.o_tile = take(sizeof(TileItem) * tile_capacity(s));
         tile_all += tile_capacity(s);
     }
-    ctx->o_tdesc = take(sizeof(TileDesc) * nshots);
     ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
     ctx->need = off;
 }
@@ -1172,11 +1174,12 @@ static int write_work_lists(fdtd_ctx *ctx) {
     std::map<std::array<int, 3>, std::vector<WorkItem>> byplan;
     std::vector<BandItem> band_all;
     std::vector<TileGrid> tile_all;
-    // (the copies read host memory until the stream is synchronised: every list lives until then)
+    // the copies read host memory until the stream is synchronised at the end: `alive` keeps every list until then
+    std::vector<std::vector<char>> alive;
     auto upload = [&](size_t o, const void *src, size_t bytes) -> int {
         if (bytes == 0) return FDTD_OK;
-        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, o), src, bytes, hipMemcpyHostToDevice, ctx->stream));
-        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        alive.emplace_back((const char *)src, (const char *)src + bytes);
+        HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, o), alive.back().data(), bytes, hipMemcpyHostToDevice, ctx->stream));
         return FDTD_OK;
     };
     int rc;
@@ -1228,7 +1231,9 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<TileItem> tw = tile_list(tile_all);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
-    return upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
+    rc = upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    return rc;
 }
 
 // the ranges a reset clears, one list for one launch: level buffers (and the

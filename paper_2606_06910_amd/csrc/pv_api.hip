@@ -364,6 +364,22 @@ __global__ __launch_bounds__(256) void k_pv_zero(uint4 *p, size_t n16) {
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// zero a field outside its grid points: the frames, the rows' tails and the pads (what stages read and never
+// write).  grid: (rows, fields)
+__global__ __launch_bounds__(256) void k_pv_zero_frame(float *f, long stride, int nx, int ny, int nz, int P, long elems) {
+    f += (long)blockIdx.y * stride;
+    const int py = ny + 2 * kR, rows = py * (nz + 2 * kR);
+    for (int r = (int)blockIdx.x; r < rows; r += (int)gridDim.x) {
+        const int z = r / py - kR, y = r % py - kR;
+        const bool in = z >= 0 && z < nz && y >= 0 && y < ny;
+        for (int x = (in ? nx : 0) + (int)threadIdx.x; x < P; x += 256) f[kLead + (long)r * P + x] = 0.0f;
+    }
+    if (blockIdx.x == 0) {
+        for (int i = (int)threadIdx.x; i < kLead; i += 256) f[i] = 0.0f;
+        for (long i = kLead + (long)rows * P + threadIdx.x; i < elems; i += 256) f[i] = 0.0f;
+    }
+}
+
 size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // FP64 layer coefficients of one axis in the normalised units (h = 1, c = 1,
@@ -567,9 +583,13 @@ int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
     if (((uintptr_t)dev_ptr) & 255) PVFAIL(ctx, FDTD_EINVAL, "workspace must be 256-byte aligned");
     if (bytes < ctx->total) PVFAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, ctx->total);
     ctx->ws = (char *)dev_ptr;
-    const size_t n16 = ctx->o_prof / 16;
+    const size_t n16 = (size_t)kNF * ctx->field_bytes / 16;
     hipLaunchKernelGGL(k_pv_zero, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 65536)), dim3(256), 0, ctx->st,
                        (uint4 *)ctx->ws, n16);
+    if (ctx->tile)   // the second buffers' grid points are written before they are read
+        hipLaunchKernelGGL(k_pv_zero_frame, dim3(4096, 7), dim3(256), 0, ctx->st,
+                           (float *)(ctx->ws + (size_t)kNF * ctx->field_bytes), (long)(ctx->field_bytes / 4), ctx->n[0],
+                           ctx->n[1], ctx->n[2], (int)ctx->P, (long)(ctx->field_bytes / 4));
     PVHIP(ctx, hipGetLastError());
     PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_prof, ctx->prof.data(), ctx->prof.size() * 4, hipMemcpyHostToDevice,
                               ctx->st));

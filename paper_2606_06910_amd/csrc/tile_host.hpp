@@ -65,6 +65,8 @@ inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids) {
     while (want < kTileBrick && 2 * want <= all / 24) want *= 2;
     std::vector<TileItem> v;
     std::vector<int> brick;
+    v.reserve(all);
+    brick.reserve(all);
     for (const TileGrid &g : grids) tile_boxes(g.n, g.lo, g.hi, g.shot, want, v, brick);
     std::vector<TileItem> seq[8];
     long cost[8] = {};

@@ -276,22 +276,38 @@ TileGrid fdtd_tile_grid(const ShotH &s, int shot) {
     }
     return g;
 }
-// Whether a shot takes the tile kernel (reported as the variant it replaces): the
-// automatic variant, no ghost faces, a z window of the kernel (TILE_Z + 8 planes)
-// that meets one z layer at most, every array of the shot within 2 GiB of its
-// first (32-bit offsets), and fewer points than the z-march needs to win.
-// Measured, us per step of a cube with 20-cell layers (10 below 128^3), the
-// other kernels against this one, FP32: 64^3 18.8 / 8.5, 96^3 33 / 11, 128^3
-// 57 / 23, 160^3 102 / 31, 200^3 138 / 58, 256^3 157 / 107, 300^3 226 / 179,
-// 384^3 350 / 313, 448^3 505 / 486; FP16: 256^3 158 / 115, 300^3 212 / 195,
-// 384^3 338 / 335, 448^3 476 / 507.
+// Whether a shot takes the tile kernels (reported as the variant they replace): the
+// automatic variant, no ghost faces, a z window of k_tile (TILE_Z + 8 planes) that
+// meets one z layer at most, layer arrays within 32 bits of offset, and in 16-bit
+// storage fewer than kTileShot16 points.  Measured, us per step of a cube with
+// 20-cell layers (10 below 128^3), the other kernels against these, FP32: 64^3
+// 18.8 / 8.5, 96^3 33 / 11, 128^3 57 / 22, 160^3 100 / 30, 200^3 135 / 53, 256^3 157
+// / 106, 300^3 225 / 158, 384^3 350 / 277, 512^3 674 / 617, 576^3 918 / 835, 640^3
+// 1168 / 1173, 768^3 1953 / 1887; FP16: 256^3 159 / 115, 384^3 336 / 291, 512^3 695
+// / 643, 640^3 1230 / 1153, 768^3 1764 / 1879.
 static bool tile_rule(const ShotH &s) {
     if (s.c.variant != FDTD_VARIANT_AUTO || s.gy || s.gz) return false;
-    if ((long)s.nx * s.ny * s.nz >= (s.esz == 4 ? kTileShot : kTileShot16)) return false;
+    if (s.esz == 2 && (long)s.nx * s.ny * s.nz >= kTileShot16) return false;
     if (s.Llo[2] > 0 && s.Lhi[2] > 0 && s.nz - s.Llo[2] - s.Lhi[2] < TILE_Z + 2 * FDTD_R) return false;
-    size_t b = (s.esz == 4 ? 2 : 3) * (s.elems * s.esz + 256) + s.elems * 4 + 256 + (size_t)3 * 4 * s.nmax * 4;
+    size_t b = (size_t)3 * 4 * s.nmax * 4;
     for (int d = 0; d < 3; ++d) b += 3 * (s.psi_elems[d] * 4 + 256);
     return b < (size_t)1 << 31;
+}
+// How the tile shots of a context of `points` points in all are stepped: inner_z,
+// the depth of k_inner's boxes (0: k_tile takes every box, one launch), and nt,
+// the non-temporal hint.  A launch of its own for the points outside the bands
+// (54 instead of 115 VGPRs, 8 instead of 4 waves per SIMD) costs one launch more;
+// us per step without it / with boxes of 8 / of 16 planes, FP32: 160^3 30.3 / 34.7
+// / 35.8, 200^3 52.9 / 56.1 / 57.1, 256^3 106 / 106 / 106, 384^3 294 / 277 / 278,
+// 512^3 650 / 617 / 613, 768^3 - / 1908 / 1887; FP16: 256^3 114 / 114 / 114, 384^3
+// 309 / 287 / 292, 512^3 689 / 640 / 646.  The hint, once the shots outgrow the
+// 256 MiB last-level cache: FP32 200^3 52.9 -> 59.9, 256^3 108.5 -> 105.5, 512^3 640
+// -> 617; never in 16-bit storage, where a box row is half a line and its stores
+// have to meet their other half in L2 (512^3 640 -> 687).
+static void tile_plan(long points, int storage, int &inner_z, bool &nt) {
+    const bool large = points >= 12000000;
+    inner_z = !large ? 0 : (storage == FDTD_F32 && points >= 100000000 ? 16 : 8);
+    nt = large && storage == FDTD_F32;
 }
 static size_t tile_capacity(const ShotH &s) {
     return s.tile ? tile_list_bound(fdtd_tile_grid(s, 0).boxes()) : 0;
@@ -457,11 +473,11 @@ static void fill_desc(fdtd_ctx *ctx, int i) {
     TileDesc &E = ctx->htile[i];
     memset(&E, 0, sizeof E);
     if (!s.tile) return;
-    auto rel = [&](size_t o) { return (uint32_t)(o - s.o_u[0]); };
-    E.tbase = wsp(ctx, s.o_u[0]);
-    for (int b = 0; b < 2; ++b) E.t_u[b] = rel(s.o_u[b]);
-    E.t_d = s.esz == 2 ? rel(s.o_d) : 0;
-    E.t_m = rel(s.o_m);
+    auto rel = [&](size_t o) { return (uint32_t)(o - s.o_psi[0]); };
+    for (int b = 0; b < 2; ++b) E.u[b] = wsp(ctx, s.o_u[b]);
+    E.dinc = s.esz == 2 ? wsp(ctx, s.o_d) : nullptr;
+    E.m = wsp(ctx, s.o_m);
+    E.lay = wsp(ctx, s.o_psi[0]);
     E.t_prof = rel(s.o_prof);
     for (int d = 0; d < 3; ++d) {
         E.t_psi[0][d] = rel(s.o_psi[d]);
@@ -728,15 +744,24 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
     // tile shots: their whole step in one launch; its extra blocks record the step
     // before while no record launch has come in between (pend steps)
     if (any_tile) {
-        hipEvent_t t0 = tic(ctx);
         int nrec = 0;
         for (int i = lo; i < hi; ++i)
             if (ctx->pend > 0 && ctx->hdesc[i].traces) nrec = hi - lo;
-        const size_t off = shot < 0 ? ctx->o_tile_all : ctx->shots[shot].o_tile;
-        const TileStep A{R.iu, ctx->pend, shot < 0 ? ctx->ntile_all : ctx->shots[shot].ntile, lo};
-        fdtd_launch_tile(stor, dd, (const TileDesc *)wsp(ctx, ctx->o_tdesc), (const TileItem *)wsp(ctx, off), A, nrec, stepc,
-                         hi - lo == 1 ? &ctx->htile[lo] : nullptr, ctx->stream);
-        toc(ctx, 0, t0);
+        const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc), *one = hi - lo == 1 ? &ctx->htile[lo] : nullptr;
+        const ShotH &s0 = ctx->shots[lo];
+        TileStep A{R.iu, ctx->pend, shot < 0 ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt};
+        hipEvent_t t0 = tic(ctx);
+        fdtd_launch_inner(stor, ctx->inner_z, descs, (const TileItem *)wsp(ctx, shot < 0 ? ctx->o_inner_all : s0.o_inner),
+                          A, stepc, one, ctx->stream);
+        if (A.nwork > 0) {
+            toc(ctx, 0, t0);
+            t0 = tic(ctx);
+        }
+        const int cls = A.nwork > 0 ? 4 : 0;
+        A.nwork = shot < 0 ? ctx->ntile_all : s0.ntile;
+        fdtd_launch_tile(stor, dd, descs, (const TileItem *)wsp(ctx, shot < 0 ? ctx->o_tile_all : s0.o_tile), A, nrec,
+                         stepc, one, ctx->stream);
+        toc(ctx, cls, t0);
     }
     if (!any_plain) return;
     hipStream_t side = ctx->stream;
@@ -1048,9 +1073,11 @@ static void layout(fdtd_ctx *ctx) {
     size_t tile_all = 0;
     for (auto &s : ctx->shots) {
         s.o_tile = take(sizeof(TileItem) * tile_capacity(s));
+        s.o_inner = take(ctx->inner_z > 0 ? sizeof(TileItem) * tile_capacity(s) : 0);
         tile_all += tile_capacity(s);
     }
     ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
+    ctx->o_inner_all = take(ctx->inner_z > 0 ? sizeof(TileItem) * tile_all : 0);
     ctx->need = off;
 }
 
@@ -1143,7 +1170,12 @@ int fdtd_create(const fdtd_shot_config *shots, int32_t nshots, void *hip_stream,
                 sh.zcols = 1;
             }
     }
-    for (auto &sh : ctx->shots) sh.tile = tile_rule(sh);
+    long tile_points = 0;
+    for (auto &sh : ctx->shots) {
+        sh.tile = tile_rule(sh);
+        if (sh.tile) tile_points += (long)sh.nx * sh.ny * sh.nz;
+    }
+    tile_plan(tile_points, ctx->storage, ctx->inner_z, ctx->tile_nt);
     for (auto &sh : ctx->shots)
         if (sh.tb_bufs && nshots != 1) {
             delete ctx;
@@ -1185,13 +1217,19 @@ static int write_work_lists(fdtd_ctx *ctx) {
     int rc;
     for (size_t i = 0; i < ctx->shots.size(); ++i) {
         ShotH &s = ctx->shots[i];
-        s.nband = s.nwork = s.ntbwork = s.ntile = 0;
+        s.nband = s.nwork = s.ntbwork = s.ntile = s.ninner = 0;
         if (s.tile) {
             const TileGrid g = fdtd_tile_grid(s, (int)i);
-            const std::vector<TileItem> w = tile_list({g});
+            const std::vector<TileItem> w = tile_list({g}, ctx->inner_z);
             if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
             s.ntile = (int)w.size();
             if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
+            if (ctx->inner_z > 0) {
+                const std::vector<TileItem> in = tile_list({g}, ctx->inner_z, true);
+                if (in.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
+                s.ninner = (int)in.size();
+                if ((rc = upload(s.o_inner, in.data(), sizeof(TileItem) * in.size()))) return rc;
+            }
             tile_all.push_back(g);
             continue;
         }
@@ -1228,9 +1266,15 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<BandItem> bw = xcd_order(band_all);
     ctx->nband_all = (int)bw.size();
     if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
-    const std::vector<TileItem> tw = tile_list(tile_all);
+    const std::vector<TileItem> tw = tile_list(tile_all, ctx->inner_z);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
+    ctx->ninner_all = 0;
+    if (ctx->inner_z > 0) {
+        const std::vector<TileItem> in = tile_list(tile_all, ctx->inner_z, true);
+        ctx->ninner_all = (int)in.size();
+        if ((rc = upload(ctx->o_inner_all, in.data(), sizeof(TileItem) * in.size()))) return rc;
+    }
     rc = upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return rc;

@@ -99,12 +99,12 @@ struct DevShot {
 };
 
 // What the tile kernel needs of a shot (the fields of DevShot of the same
-// names, and the shot's arrays as byte offsets from its first).  psi alternates
-// between two buffers: t_psi[0] while level buffer 0 holds u^n, t_psi[1] while
-// buffer 1 does.
+// names; u, dinc and m from their first byte; the layer arrays and profiles as
+// byte offsets from psi[0]).  psi alternates between two buffers: t_psi[0] while
+// level buffer 0 holds u^n, t_psi[1] while buffer 1 does.
 struct TileDesc {
-    char *tbase;
-    uint32_t t_u[2], t_d, t_m, t_prof, t_psi[2][3], t_zeta[3];
+    char *u[2], *dinc, *m, *lay;
+    uint32_t t_prof, t_psi[2][3], t_zeta[3];
     int nx, ny, nz, P, PY, S, fy, fz, WX, SY, nmax;
     int Llo[3], Lhi[3];
     float cc, w2[3][5], w1[3][5];
@@ -151,12 +151,13 @@ struct WorkItem {
 
 // Box of the tile kernel (k_tile), and one step of it: the level buffer of u^n,
 // the step's number past the device step counter, the box items, and the first
-// shot whose receivers the extra blocks record (the step before's row).
+// shot whose receivers the extra blocks record (the step before's row); nt: the
+// non-temporal hint on what a step reads or writes once.
 #define TILE_X 32
 #define TILE_Y 8
 #define TILE_Z 4
 struct TileStep {
-    int iu, k, nwork, rec_lo;
+    int iu, k, nwork, rec_lo, nt;
 };
 // One box: shot (low byte) and the axes whose band it meets (negative: an idle item); first point.
 #define TILE_XB 0x100

@@ -16,8 +16,7 @@ constexpr int kMaxRec = 65536;  // receivers per shot with temporal blocking
 constexpr int kTimingClasses = 6;   // update, psi, record, exchange, band update, temporal block
 constexpr int kBandTX = BAND_TX, kBandZ = 32;   // band-kernel tile width and z chunk
 constexpr int kCUs = 256;   // compute units of an MI355X (the default z-march plan shares them)
-constexpr long kTileShot = 60000000, kTileShot16 = 30000000;   // shots below this many points (FP32, 16-bit
-                                                               // storage) take the tile kernel by default
+constexpr long kTileShot16 = 300000000;   // 16-bit shots below this many points take the tile kernels by default
 constexpr long kSmallShot = 150L * 150 * 150;   // a lone shot below this many points runs naive by default
 
 struct ShotH {
@@ -38,8 +37,8 @@ struct ShotH {
     size_t o_u[4] = {0, 0, 0, 0}, o_d = 0, o_m = 0, o_psi[3] = {0, 0, 0}, o_zeta[3] = {0, 0, 0}, o_prof = 0;
     // tile shots (k_tile does the whole step): the other psi buffers and the box list
     bool tile = false;
-    size_t o_psi2[3] = {0, 0, 0}, o_tile = 0;
-    int ntile = 0;
+    size_t o_psi2[3] = {0, 0, 0}, o_tile = 0, o_inner = 0;
+    int ntile = 0, ninner = 0;
     size_t o_work = 0, o_xbuf = 0, xbuf_bytes = 0;
     size_t o_jobs[2][4] = {};
     int njobs[2][4] = {};
@@ -90,7 +89,10 @@ struct fdtd_ctx {
     char *ws = nullptr;
     size_t ws_bytes = 0, need = 0;
     size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0, o_tile_all = 0, o_tdesc = 0, o_fill = 0;
-    int nwork_all = 0, nband_all = 0, ntile_all = 0, nfill = 0;
+    int nwork_all = 0, nband_all = 0, ntile_all = 0, ninner_all = 0, nfill = 0;
+    size_t o_inner_all = 0;
+    int inner_z = 0;          // planes of a box of k_inner; 0: k_tile takes every box
+    bool tile_nt = false;     // tile shots too large for any cache to hold a level from step to step
     size_t fill_max16 = 0;    // longest range of the reset's fill list
     int pend = 0;             // steps enqueued since the device step counter was last advanced
     // multi-shot z-march launches: one per distinct (ry, zchunk) plan

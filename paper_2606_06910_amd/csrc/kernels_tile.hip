@@ -1,8 +1,8 @@
-// kernels_tile.hip -- one leapfrog step of a shot in one launch (gfx950), for
-// the shots whose step is bound by latency, launches and the layers' share of
-// the points rather than by HBM.
+// kernels_tile.hip -- one leapfrog step of a shot in one launch (k_tile), or on
+// large grids two: k_inner for the boxes outside every band, k_tile for the rest
+// (gfx950).
 //
-// A block owns a box of TILE_X x TILE_Y x TILE_Z points, inside or outside the
+// A block of k_tile owns a box of TILE_X x TILE_Y x TILE_Z points, inside or outside the
 // layers, and does the whole step there: psi, zeta and u^{n+1} (paper, section
 // "CPML Boundary Layers"; the arithmetic is lap_point's, operation for
 // operation, so the bits are those of every other variant).  psi_d at the
@@ -37,7 +37,7 @@ typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
 }  // namespace
 
 // one box (D: TileDesc in the constant or the kernel-argument address space)
-template <typename T, typename D>
+template <typename T, bool NT, typename D>
 __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const TileStep &A,
                                          const int *__restrict__ stepc) {
     const int t = (int)threadIdx.x;
@@ -63,17 +63,17 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     __shared__ float PX[TZ][TY][PXW];   // new psi_x at (x0 - 4 + c, y0 + r, z0 + p), 0 outside the slabs
     __shared__ float PY[TZ][PYH][TX];   // new psi_y at (x0 + c, y0 - 4 + r, z0 + p)
 
-    // Every array of the shot lies within 2 GiB of its first (the tile rule sees to it), so one descriptor
-    // reaches them all: array at a scalar offset, position at a lane offset, plane by plane a running scalar
-    // offset.  Lanes whose position lies outside the frame that every field carries read zero; planes outside
-    // it are not read.
-    const Rsrc R = make_rsrc(s.tbase);
+    // One descriptor per field, based 8 planes before the box, and one for the layer arrays and profiles (32-bit
+    // offsets reach them all, the tile rule sees to it): position at a lane offset, plane by plane a running
+    // scalar offset.  Lanes whose position lies outside the frame that every field carries read zero; planes
+    // outside it are not read.
     const int P = s.P, esz = (int)sizeof(T), fy = s.fy, fz = s.fz;
+    const long base = (long)(fz + z0 - 2 * FDTD_R) * s.S;
+    const Rsrc ru = make_rsrc(s.u[A.iu] + base * esz), rl = make_rsrc(s.lay);
     const uint32_t Sb = (uint32_t)s.S * (uint32_t)esz, Smb = (uint32_t)s.S * 4u;
     // offset of (-4, -fy, z0) from a field's first byte: with elem() below, of (x, y, z0)
-    const uint32_t lead = (uint32_t)((fz + z0) * s.S) + (uint32_t)(kFieldLead - FDTD_R);
-    const uint32_t fu = s.t_u[A.iu] + lead * esz, fw = s.t_u[A.iu ^ 1] + lead * esz;
-    const uint32_t fs = IsInc<T>::v ? s.t_d + lead * esz : fw, fm = s.t_m + lead * 4u;
+    const uint32_t lead = (uint32_t)(2 * FDTD_R * s.S) + (uint32_t)(kFieldLead - FDTD_R);
+    const uint32_t fu = lead * esz, fm = lead * 4u;
     auto elem = [&](int xp, int yp) { return (uint32_t)((yp + fy) * P + xp + FDTD_R); };
     auto off = [&](int xp, int yp) -> uint32_t {
         return xp >= -FDTD_R && xp < nx + FDTD_R && yp >= -fy && yp < ny + fy ? elem(xp, yp) * (uint32_t)esz : kBufSkip;
@@ -89,7 +89,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     {
         uint32_t so = fu - FDTD_R * Sb;
 #pragma unroll
-        for (int o = FDTD_R; o < QN - FDTD_R; ++o, so += Sb) q[o] = Buf<T>::ld(R, vq, o < 3 * FDTD_R ? so : min(so, slast));
+        for (int o = FDTD_R; o < QN - FDTD_R; ++o, so += Sb) q[o] = Buf<T>::ld(ru, vq, o < 3 * FDTD_R ? so : min(so, slast));
     }
     // y halo: 4 rows above and below the box, then the next 4 for psi_y: one row of each per thread
     const int yn = ly < FDTD_R ? y0 - FDTD_R + ly : y0 + FDTD_R + ly;
@@ -99,20 +99,21 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     const int xn = c8 < FDTD_R ? x0 - FDTD_R + c8 : x0 + TX - FDTD_R + c8;
     const int xf = c8 < FDTD_R ? xn - FDTD_R : xn + FDTD_R;
     const uint32_t sh = fu + (uint32_t)hp * Sb;
-    const float hxn = Buf<T>::ld(R, off(xn, y0 + hr), sh);
+    const float hxn = Buf<T>::ld(ru, off(xn, y0 + hr), sh);
     const uint32_t vyn = off(x, yn), vc = act ? vq : kBufSkip, vcm = act ? elem(x, y) * 4u : kBufSkip;
     float hyn[TZ], hyf[TZ], hxf, second[TZ], mm[TZ];
     {
-        uint32_t so = fu, ss = fs, sm = fm;
+        const Rsrc rs = make_rsrc((IsInc<T>::v ? s.dinc : s.u[A.iu ^ 1]) + base * esz), rm = make_rsrc(s.m + base * 4);
+        uint32_t so = fu, sm = fm;
 #pragma unroll
-        for (int p = 0; p < TZ; ++p, so += Sb, ss += Sb, sm += Smb) {
-            hyn[p] = Buf<T>::ld(R, vyn, so);
-            second[p] = Buf<T>::ld(R, vc, ss);
-            mm[p] = Buf<float>::ld(R, vcm, sm);
+        for (int p = 0; p < TZ; ++p, so += Sb, sm += Smb) {
+            hyn[p] = Buf<T>::ld(ru, vyn, so);
+            second[p] = NT ? Buf<T>::ldnt(rs, vc, so) : Buf<T>::ld(rs, vc, so);
+            mm[p] = NT ? Buf<float>::ldnt(rm, vcm, sm) : Buf<float>::ld(rm, vcm, sm);
         }
     }
     auto prof = [&](int d, int f, int c) -> float {
-        return Buf<float>::ld(R, (uint32_t)c * 4u, s.t_prof + (uint32_t)((d * 4 + f) * s.nmax) * 4u);
+        return Buf<float>::ld(rl, (uint32_t)c * 4u, s.t_prof + (uint32_t)((d * 4 + f) * s.nmax) * 4u);
     };
     // x layers: own psi and zeta, and psi of the 4 columns on each side (psi_index layout)
     const uint32_t Spx = (uint32_t)(s.PY * s.WX) * 4u;
@@ -129,17 +130,17 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             const uint32_t e = (uint32_t)((yp + fy) * s.WX + xp) * 4u;
             return xp < xlo ? e : e + side;
         };
-        hxf = Buf<T>::ld(R, off(xf, y0 + hr), sh);
+        hxf = Buf<T>::ld(ru, off(xf, y0 + hr), sh);
         bx = act && in_band(x, nx, xlo, xhi);
         sx = act && slab_point(x, nx, xlo, xhi);
         vx = sx ? xoff(x, y) : kBufSkip;
         hsx = y0 + hr < ny && slab_point(xn, nx, xlo, xhi);
-        pxh = Buf<float>::ld(R, hsx ? xoff(xn, y0 + hr) : kBufSkip, xpo + (uint32_t)hp * Spx);
+        pxh = Buf<float>::ld(rl, hsx ? xoff(xn, y0 + hr) : kBufSkip, xpo + (uint32_t)hp * Spx);
         uint32_t so = xpo, sz = xze;
 #pragma unroll
         for (int p = 0; p < TZ; ++p, so += Spx, sz += Spx) {
-            pxo[p] = Buf<float>::ld(R, vx, so);
-            zx[p] = Buf<float>::ld(R, vx, sz);
+            pxo[p] = Buf<float>::ld(rl, vx, so);
+            zx[p] = Buf<float>::ld(rl, vx, sz);
         }
 #pragma unroll
         for (int f = 0; f < 4; ++f) ax[f] = prof(0, f, min(x, nx - 1));
@@ -166,10 +167,10 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         uint32_t su = fu, so = ypo, sz = yze;
 #pragma unroll
         for (int p = 0; p < TZ; ++p, su += Sb, so += Spy, sz += Spy) {
-            hyf[p] = Buf<T>::ld(R, vyf, su);
-            pyo[p] = Buf<float>::ld(R, vy, so);
-            pyh[p] = Buf<float>::ld(R, vyh, so);
-            zy[p] = Buf<float>::ld(R, vy, sz);
+            hyf[p] = Buf<T>::ld(ru, vyf, su);
+            pyo[p] = Buf<float>::ld(rl, vy, so);
+            pyh[p] = Buf<float>::ld(rl, vyh, so);
+            zy[p] = Buf<float>::ld(rl, vy, sz);
         }
 #pragma unroll
         for (int f = 0; f < 4; ++f) ay[f] = prof(1, f, min(y, ny - 1));
@@ -195,20 +196,20 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         uint32_t su = z0 >= FDTD_R ? fu - 2 * FDTD_R * Sb : fu, sh2 = fu + (TZ + FDTD_R) * Sb;
 #pragma unroll
         for (int o = 0; o < FDTD_R; ++o, su += Sb, sh2 += Sb) {
-            q[o] = Buf<T>::ld(R, vq, su);
-            q[TZ + 3 * FDTD_R + o] = Buf<T>::ld(R, vq, min(sh2, slast));
+            q[o] = Buf<T>::ld(ru, vq, su);
+            q[TZ + 3 * FDTD_R + o] = Buf<T>::ld(ru, vq, min(sh2, slast));
         }
         uint32_t so = zpo;
 #pragma unroll
         for (int o = 0; o < PN; ++o, so += Spz) {
             pz[o] = 0.0f;
-            if ((zm >> o) & 1u) pz[o] = Buf<float>::ld(R, vz, so);
+            if ((zm >> o) & 1u) pz[o] = Buf<float>::ld(rl, vz, so);
         }
         uint32_t sz = zze + FDTD_R * Spz;
 #pragma unroll
         for (int p = 0; p < TZ; ++p, sz += Spz) {
             zz[p] = 0.0f;
-            if ((zm >> (p + FDTD_R)) & 1u) zz[p] = Buf<float>::ld(R, vz, sz);
+            if ((zm >> (p + FDTD_R)) & 1u) zz[p] = Buf<float>::ld(rl, vz, sz);
         }
         const int zl = min(max(z0 - FDTD_R + (t & 15), 0), nz - 1);
 #pragma unroll
@@ -242,7 +243,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             dx[p] = d1_lds(Uc + p * UP, 1, w1[0]);
             const float v = sx ? psi_update(ax[0], pxo[p], ax[1], dx[p]) : 0.0f;
             PX[p][ly][lx + 4] = v;
-            if (p < n1) Buf<float>::stc(R, vx, xpn + p * Spx, v);
+            if (p < n1) Buf<float>::stc(rl, vx, xpn + p * Spx, v);
         }
         const float v = psi_update(ahx[0], pxh, ahx[1], d1_lds(&U[hp][hr + 8][cn + 4], 1, w1[0]));
         PX[hp][hr][cn] = hsx ? v : 0.0f;
@@ -256,7 +257,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             const float h = hsy ? psi_update(ahy[0], pyh[p], ahy[1], d1_lds(&U[p][rn + 4][lx + 8], UW, w1[1])) : 0.0f;
             PY[p][ly + 4][lx] = v;
             PY[p][rn][lx] = h;
-            if (p < n1) Buf<float>::stc(R, vy, ypn + p * Spy, v);
+            if (p < n1) Buf<float>::stc(rl, vy, ypn + p * Spy, v);
         }
     }
     if (again(zb)) {
@@ -274,12 +275,13 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
                 if (o >= FDTD_R && o < FDTD_R + TZ) dz[o - FDTD_R] = d1;
                 if (!((z1 >> o) & 1u)) continue;
                 pz[o] = psi_update(lane_value(az[0], o), pz[o], lane_value(az[1], o), d1);
-                if (o >= FDTD_R && o < FDTD_R + TZ) Buf<float>::stc(R, vz, zpn + o * Spz, pz[o]);
+                if (o >= FDTD_R && o < FDTD_R + TZ) Buf<float>::stc(rl, vz, zpn + o * Spz, pz[o]);
             }
     }
     if (again(xb | yb)) __syncthreads();
 
     // ---- the update ----
+    const Rsrc rw = make_rsrc(s.u[A.iu ^ 1] + base * esz), rs = IsInc<T>::v ? make_rsrc(s.dinc + base * esz) : rw;
     const int src_tile = uniform(s.sx >= x0 && s.sx < x0 + TX && s.sy >= y0 && s.sy < y0 + TY && s.sz >= z0 &&
                                  s.sz < z0 + TZ);
     float srcamp = 0.0f;
@@ -319,14 +321,14 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
                 const float e = cpml_axis(L[0], dx[p], d1_lds(&PX[p][ly][lx + 4], 1, w1[0]), ax[2],
                                           ax[3], ax[1], ax[0], sx, zx[p], &zn);
                 if (bx) L[0] = e;
-                Buf<float>::stc(R, vx, xze + p * Spx, zn);
+                Buf<float>::stc(rl, vx, xze + p * Spx, zn);
             }
             if (again(yb)) {
                 float zn = 0.0f;
                 const float e = cpml_axis(L[1], dy[p], d1_lds(&PY[p][ly + 4][lx], TX, w1[1]), ay[2],
                                           ay[3], ay[1], ay[0], sy, zy[p], &zn);
                 if (by) L[1] = e;
-                Buf<float>::stc(R, vy, yze + p * Spy, zn);
+                Buf<float>::stc(rl, vy, yze + p * Spy, zn);
             }
             if (bz) {
                 float pl[4], ph[4], zn = 0.0f;
@@ -339,7 +341,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
                 L[2] = cpml_axis(L[2], dz[p], d1_axis(w1[2], pl, ph), lane_value(az[2], p + 4),
                                  lane_value(az[3], p + 4), lane_value(az[1], p + 4), lane_value(az[0], p + 4), sz, zz[p],
                                  &zn);
-                if (sz) Buf<float>::stc(R, vz, zze + (p + 4) * Spz, zn);
+                if (sz) Buf<float>::stc(rl, vz, zze + (p + 4) * Spz, zn);
             }
             lt = (L[0] + L[1]) + L[2];
             const bool none = act && !(bx || by || bz);
@@ -350,14 +352,127 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         }
         const bool src = again(src_tile) && z0 + p == s.sz && x == s.sx && y == s.sy;
         const Upd up = time_update<T>(mm[p], lt, c, second[p], src, srcamp);
-        Buf<T>::stc(R, vc, fw + p * Sb, up.u);
-        if constexpr (IsInc<T>::v) Buf<T>::stc(R, vc, fs + p * Sb, up.d);
+        if constexpr (NT) {
+            Buf<T>::st(rw, vc, fu + p * Sb, up.u);
+            if constexpr (IsInc<T>::v) Buf<T>::st(rs, vc, fu + p * Sb, up.d);
+        } else {
+            Buf<T>::stc(rw, vc, fu + p * Sb, up.u);
+            if constexpr (IsInc<T>::v) Buf<T>::stc(rs, vc, fu + p * Sb, up.d);
+        }
     }
+}
+
+// Boxes of TX x TY x IZ points outside every band and wholly inside the grid
+// (TileItem flags: the shot only): u^{n+1} alone, from the box's column and an
+// LDS box with a 4-point halo along x and y.  Bound by HBM: 512^3 with 20-cell
+// layers, 97 M points in 336 us, 4.6 TB/s of the 16 bytes a point cannot do
+// without, 5.4 TB/s counted (u^n is fetched 1.7 times: whole lines at the bricks'
+// x faces); the z-march takes 585 us for them on the half of the CUs the band
+// kernel leaves it, and 345 us on all.  Boxes of 8 planes hold 54 VGPRs and 20 KB
+// of LDS: eight blocks per CU, the memory's latency hidden by other blocks
+// instead of a register queue along z.
+template <typename T, int IZ, bool NT, typename D>
+__device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const TileStep &A,
+                                          const int *__restrict__ stepc) {
+    constexpr int F = FDTD_R, LW = TX + 2 * F, LH = TY + 2 * F, LP = LW * LH, XH = IZ / 4;
+    __shared__ float U[IZ * LP];   // u^n at (x0 - 4 + c, y0 - 4 + r, z0 + p); corners unused
+    const int t = (int)threadIdx.x, lx = t % TX, ly = t / TX;
+    const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0, P = s.P, esz = (int)sizeof(T);
+    const long base = (long)(s.fz + z0 - F) * s.S;   // descriptors based 4 planes before the box
+    const Rsrc ru = make_rsrc(s.u[A.iu] + base * esz), rw = make_rsrc(s.u[A.iu ^ 1] + base * esz);
+    const Rsrc rs = IsInc<T>::v ? make_rsrc(s.dinc + base * esz) : rw, rm = make_rsrc(s.m + base * 4);
+    const uint32_t Sb = (uint32_t)s.S * (uint32_t)esz, Smb = (uint32_t)s.S * 4u;
+    // offsets of plane z0, and of the column (row y0 + ly, the row of the y halo, the x halo's place) in a plane
+    const uint32_t f0 = (uint32_t)(F * s.S + (s.fy + y0) * P + kFieldLead + x0);
+    const uint32_t fu = f0 * (uint32_t)esz, fm = f0 * 4u;
+    const uint32_t vc = (uint32_t)(ly * P + lx) * (uint32_t)esz, vm = (uint32_t)(ly * P + lx) * 4u;
+    // (lane offsets are unsigned: halos are addressed from the box's first halo row or column)
+    const uint32_t vy = (uint32_t)((ly < F ? ly : ly + TY) * P + lx) * (uint32_t)esz;
+    const uint32_t fy = fu - (uint32_t)(F * P) * (uint32_t)esz;
+    const int c8 = t & 7, hr = (t >> 3) & (TY - 1), hp = uniform(t >> 6);
+    const uint32_t vx = (uint32_t)(hr * P + (c8 < F ? c8 : c8 + TX)) * (uint32_t)esz;
+    const uint32_t fx = fu - (uint32_t)F * (uint32_t)esz + (uint32_t)hp * Sb;
+    float q[IZ + 2 * F], hy[IZ], hx[XH], second[IZ], mm[IZ];
+    {
+        uint32_t so = fu - F * Sb;
+#pragma unroll
+        for (int o = 0; o < IZ + 2 * F; ++o, so += Sb) q[o] = Buf<T>::ld(ru, vc, so);
+        so = fy;
+#pragma unroll
+        for (int p = 0; p < IZ; ++p, so += Sb) hy[p] = Buf<T>::ld(ru, vy, so);
+        so = fx;
+#pragma unroll
+        for (int p = 0; p < XH; ++p, so += 4 * Sb) hx[p] = Buf<T>::ld(ru, vx, so);
+        so = fu;
+        uint32_t sm = fm;
+#pragma unroll
+        for (int p = 0; p < IZ; ++p, so += Sb, sm += Smb) {
+            second[p] = NT ? Buf<T>::ldnt(rs, vc, so) : Buf<T>::ld(rs, vc, so);
+            mm[p] = NT ? Buf<float>::ldnt(rm, vm, sm) : Buf<float>::ld(rm, vm, sm);
+        }
+    }
+    float *const Uc = U + (ly + F) * LW + lx + F;
+    float *const Uy = U + (ly < F ? ly : ly + TY) * LW + lx + F;
+    float *const Ux = U + hp * LP + (hr + F) * LW + (c8 < F ? c8 : c8 + TX);
+#pragma unroll
+    for (int p = 0; p < IZ; ++p) {
+        Uc[p * LP] = q[p + F];
+        Uy[p * LP] = hy[p];
+    }
+#pragma unroll
+    for (int p = 0; p < XH; ++p) Ux[4 * p * LP] = hx[p];
+    __syncthreads();
+    const int src_box = uniform(s.sx >= x0 && s.sx < x0 + TX && s.sy >= y0 && s.sy < y0 + TY && s.sz >= z0 &&
+                                s.sz < z0 + IZ);
+    float srcamp = 0.0f;
+    if (src_box && s.wav != nullptr) {
+        const int n = *stepc + A.k;
+        if (n >= 0 && n < s.src_nt) srcamp = s.wav[n] * s.src_scale;
+    }
+    Coef K;
+    K.cc = s.cc;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
+    uint32_t so = fu;
+#pragma unroll
+    for (int p = 0; p < IZ; ++p, so += Sb) {
+        const float *c0 = Uc + p * LP;
+        float xl[4], xh[4], yl[4], yh[4], zl[4], zh[4];
+#pragma unroll
+        for (int l = 1; l <= 4; ++l) {
+            xl[l - 1] = c0[-l];
+            xh[l - 1] = c0[l];
+            yl[l - 1] = c0[-l * LW];
+            yh[l - 1] = c0[l * LW];
+            zl[l - 1] = q[p + F - l];
+            zh[l - 1] = q[p + F + l];
+        }
+        const float lt = lap_interior(K, q[p + F], xl, xh, yl, yh, zl, zh);
+        const bool src = again(src_box) && z0 + p == s.sz && x0 + lx == s.sx && y0 + ly == s.sy;
+        const Upd up = time_update<T>(mm[p], lt, q[p + F], second[p], src, srcamp);
+        if constexpr (NT) {
+            Buf<T>::st(rw, vc, so, up.u);
+            if constexpr (IsInc<T>::v) Buf<T>::st(rs, vc, so, up.d);
+        } else {
+            Buf<T>::stc(rw, vc, so, up.u);
+            if constexpr (IsInc<T>::v) Buf<T>::stc(rs, vc, so, up.d);
+        }
+    }
+}
+template <typename T, int IZ, bool ONE, bool NT>
+__global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
+                                               TileStep A, const int *__restrict__ stepc, const TileDesc one) {
+    const TileItem wi = work[blockIdx.x];
+    if (wi.flags < 0) return;   // the idle items that pad the list
+    if constexpr (ONE) inner_box<T, IZ, NT>(one, wi, A, stepc);
+    else inner_box<T, IZ, NT>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
 }
 
 // ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
 // before the box's own)
-template <typename T, bool ONE>
+template <typename T, bool ONE, bool NT>
 __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ shots, const TileDesc *__restrict__ descs,
                                                  const TileItem *__restrict__ work, TileStep A,
                                                  const int *__restrict__ stepc, const TileDesc one) {
@@ -377,18 +492,35 @@ __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ sho
     }
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) tile_box<T>(one, wi, A, stepc);
-    else tile_box<T>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    if constexpr (ONE) tile_box<T, NT>(one, wi, A, stepc);
+    else tile_box<T, NT>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
 }
 
+template <typename T, int IZ>
+static void launch_inner_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
+                           const TileDesc *one, hipStream_t st) {
+    const dim3 grid((unsigned)A.nwork);
+    if (one && A.nt) hipLaunchKernelGGL((k_inner<T, IZ, true, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
+    else if (one) hipLaunchKernelGGL((k_inner<T, IZ, true, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
+    else if (A.nt)
+        hipLaunchKernelGGL((k_inner<T, IZ, false, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
+    else
+        hipLaunchKernelGGL((k_inner<T, IZ, false, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
+}
 template <typename T>
 static void launch_tile_t(const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
                           int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
     const dim3 grid((unsigned)(A.nwork + nrec));
-    if (one)
-        hipLaunchKernelGGL((k_tile<T, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
+    if (one && A.nt)
+        hipLaunchKernelGGL((k_tile<T, true, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
+    else if (one)
+        hipLaunchKernelGGL((k_tile<T, true, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
+    else if (A.nt)
+        hipLaunchKernelGGL((k_tile<T, false, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc,
+                           TileDesc{});
     else
-        hipLaunchKernelGGL((k_tile<T, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, TileDesc{});
+        hipLaunchKernelGGL((k_tile<T, false, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc,
+                           TileDesc{});
 }
 
 void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
@@ -397,4 +529,19 @@ void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs,
     if (stor == 1) launch_tile_t<_Float16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
     else if (stor == 2) launch_tile_t<__bf16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
     else launch_tile_t<float>(d_shots, d_descs, work, A, nrec, stepc, one, st);
+}
+
+template <typename T>
+static void launch_inner_z(int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
+                           const TileDesc *one, hipStream_t st) {
+    if (iz == 16) launch_inner_t<T, 16>(d_descs, work, A, stepc, one, st);
+    else if (iz == 8) launch_inner_t<T, 8>(d_descs, work, A, stepc, one, st);
+    else launch_inner_t<T, 4>(d_descs, work, A, stepc, one, st);
+}
+void fdtd_launch_inner(int stor, int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
+                       const int *stepc, const TileDesc *one, hipStream_t st) {
+    if (A.nwork <= 0) return;
+    if (stor == 1) launch_inner_z<_Float16>(iz, d_descs, work, A, stepc, one, st);
+    else if (stor == 2) launch_inner_z<__bf16>(iz, d_descs, work, A, stepc, one, st);
+    else launch_inner_z<float>(iz, d_descs, work, A, stepc, one, st);
 }

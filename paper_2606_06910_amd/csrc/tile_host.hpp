@@ -7,31 +7,51 @@
 #include <vector>
 
 // Boxes of a brick (tile_boxes) on a large grid.  One XCD runs about 128 boxes at a time; measured on the
-// first-order step at 544^3 (us per step): columns of boxes along z 1842, bricks of 32 1868, 128 1859, 256 1742,
-// 512 1749 (counted reads 7.4 GB in columns, 5.8 GB in bricks of 256); three gradients of 100 steps 25.2 ms in
-// columns, 24.3 in bricks.
+// first-order step at 544^3 with cubic bricks (us per step): columns of boxes along z 1842, bricks of 32 boxes
+// 1868, 128 1859, 256 1742, 512 1749 (counted reads 7.4 GB in columns, 5.8 GB in bricks of 256).
 constexpr size_t kTileBrick = 256;
 constexpr size_t kTileAhead = 1024;  // boxes one XCD's list may be ahead of another's
 
-// Boxes of a grid in bricks: a brick is the set of boxes that run on one XCD at about the same time, so
-// it is grown (by doubling its shortest side) towards a cube of `want` boxes, whose faces share the least
-// halo with its neighbours.  `brick` receives each box's brick number.  Each box is marked with the axes
-// whose band (layer and 4 points) it meets.
-inline void tile_boxes(const int n[3], const int lo[3], const int hi[3], int shot, size_t want,
-                       std::vector<TileItem> &v, std::vector<int> &brick) {
-    const int ext[3] = {TILE_X, TILE_Y, TILE_Z};
+// One grid's boxes: its size, its layers, the number its items carry.
+struct TileGrid {
+    int n[3], lo[3], hi[3], shot;
+    size_t boxes() const {
+        return (size_t)((n[0] + TILE_X - 1) / TILE_X) * ((n[1] + TILE_Y - 1) / TILE_Y) * ((n[2] + TILE_Z - 1) / TILE_Z);
+    }
+    // the inner region for boxes iz planes deep: whole boxes inside the grid that meet no band; false if empty
+    bool inner(int iz, int r0[3], int r1[3]) const {
+        const int ext[3] = {TILE_X, TILE_Y, TILE_Z};
+        for (int d = 0; d < 3; ++d) {
+            const int a = lo[d] > 0 ? lo[d] + FDTD_R : 0, b = hi[d] > 0 ? n[d] - hi[d] - FDTD_R : n[d];
+            r0[d] = (a + ext[d] - 1) / ext[d] * ext[d];
+            r1[d] = b / ext[d] * ext[d];
+        }
+        r1[2] = r0[2] + (r1[2] - r0[2]) / iz * iz;
+        return r0[0] < r1[0] && r0[1] < r1[1] && r0[2] < r1[2];
+    }
+};
+
+// Boxes in bricks: a brick is the set of boxes that run on one XCD at about the same time, grown (by doubling
+// one side at a time) to `want` boxes of the least halo.  A halo of 4 to 8 points costs as many rows or planes
+// along y and z but a whole 128-byte line on each side along x, so x sides grow to 8 times the others (us per
+// step, cubes of boxes against this: 300^3 170 -> 161, first-order 544^3 1610 -> 1556).  The region of the grid
+// is [r0, r1) in boxes of ext points, less the inner region [x0, x1) where given; `brick` receives each box's
+// brick number, and each box is marked with the axes whose band (layer and 4 points) it meets.
+inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], const int r1[3], const int *x0,
+                       const int *x1, size_t want, std::vector<TileItem> &v, std::vector<int> &brick) {
+    const int wt[3] = {8, 1, 1};
     int nb[3], b[3] = {1, 1, 1};
-    for (int d = 0; d < 3; ++d) nb[d] = (n[d] + ext[d] - 1) / ext[d];
+    for (int d = 0; d < 3; ++d) nb[d] = (r1[d] - r0[d] + ext[d] - 1) / ext[d];
     while ((size_t)b[0] * b[1] * b[2] < want) {
-        int s = -1;   // shortest side that can still grow
+        int s = -1;   // the side that can still grow and whose faces cost most
         for (int d = 2; d >= 0; --d)
-            if (b[d] < nb[d] && (s < 0 || b[d] * ext[d] < b[s] * ext[s])) s = d;
+            if (b[d] < nb[d] && (s < 0 || b[d] * ext[d] * wt[s] < b[s] * ext[s] * wt[d])) s = d;
         if (s < 0) break;
         b[s] *= 2;
     }
-    auto meets = [&](int d, int c0, int len) {
-        const int c1 = std::min(c0 + len, n[d]);
-        return (lo[d] > 0 && c0 < lo[d] + FDTD_R) || (hi[d] > 0 && c1 > n[d] - hi[d] - FDTD_R);
+    auto meets = [&](int d, int c0) {
+        const int c1 = std::min(c0 + ext[d], g.n[d]);
+        return (g.lo[d] > 0 && c0 < g.lo[d] + FDTD_R) || (g.hi[d] > 0 && c1 > g.n[d] - g.hi[d] - FDTD_R);
     };
     int id = brick.empty() ? 0 : brick.back() + 1;
     for (int X = 0; X < nb[0]; X += b[0])
@@ -40,34 +60,37 @@ inline void tile_boxes(const int n[3], const int lo[3], const int hi[3], int sho
                 for (int tx = X; tx < std::min(X + b[0], nb[0]); ++tx)
                     for (int ty = Y; ty < std::min(Y + b[1], nb[1]); ++ty)
                         for (int tz = Z; tz < std::min(Z + b[2], nb[2]); ++tz) {
-                            const int x0 = tx * ext[0], y0 = ty * ext[1], z0 = tz * ext[2];
-                            v.push_back(TileItem{shot | (meets(0, x0, ext[0]) ? TILE_XB : 0) |
-                                                     (meets(1, y0, ext[1]) ? TILE_YB : 0) |
-                                                     (meets(2, z0, ext[2]) ? TILE_ZB : 0),
-                                                 x0, y0, z0});
+                            const int c[3] = {r0[0] + tx * ext[0], r0[1] + ty * ext[1], r0[2] + tz * ext[2]};
+                            bool skip = x0 != nullptr;
+                            for (int d = 0; skip && d < 3; ++d) skip = c[d] >= x0[d] && c[d] < x1[d];
+                            if (skip) continue;
+                            v.push_back(TileItem{g.shot | (meets(0, c[0]) ? TILE_XB : 0) |
+                                                     (meets(1, c[1]) ? TILE_YB : 0) | (meets(2, c[2]) ? TILE_ZB : 0),
+                                                 c[0], c[1], c[2]});
                             brick.push_back(id);
                         }
 }
 
-// The boxes of several grids (their lo, hi layers) in launch order: each brick goes to the XCD with the
-// least work so far (workgroup b runs on XCD b mod 8); a box costs 4 and 3 more for each axis whose band
-// it meets, about its instruction count.
-struct TileGrid {
-    int n[3], lo[3], hi[3], shot;
-    size_t boxes() const {
-        return (size_t)((n[0] + TILE_X - 1) / TILE_X) * ((n[1] + TILE_Y - 1) / TILE_Y) * ((n[2] + TILE_Z - 1) / TILE_Z);
-    }
-};
-inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids) {
+// The boxes of several grids in launch order: each brick goes to the XCD with the least work so far (workgroup
+// b runs on XCD b mod 8); a box costs 4 and 3 more for each axis whose band it meets, about its instruction
+// count.  iz = 0: every box, TILE_Z planes deep; iz > 0 with `inner`: the inner region's boxes, iz planes deep,
+// or without: the boxes of the rest.
+inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, int iz = 0, bool inner = false) {
     size_t all = 0;
-    for (const TileGrid &g : grids) all += g.boxes();
+    for (const TileGrid &g : grids) all += g.boxes() * TILE_Z / (inner ? iz : TILE_Z);
     size_t want = 8;   // a power of two, at least 24 bricks (three per XCD) where there are so many boxes
     while (want < kTileBrick && 2 * want <= all / 24) want *= 2;
     std::vector<TileItem> v;
     std::vector<int> brick;
     v.reserve(all);
     brick.reserve(all);
-    for (const TileGrid &g : grids) tile_boxes(g.n, g.lo, g.hi, g.shot, want, v, brick);
+    for (const TileGrid &g : grids) {
+        const int ext[3] = {TILE_X, TILE_Y, inner ? iz : TILE_Z}, zero[3] = {0, 0, 0};
+        int r0[3], r1[3];
+        const bool has = iz > 0 && g.inner(iz, r0, r1);
+        if (inner && has) tile_boxes(g, ext, r0, r1, nullptr, nullptr, want, v, brick);
+        if (!inner) tile_boxes(g, ext, zero, g.n, has ? r0 : nullptr, r1, want, v, brick);
+    }
     std::vector<TileItem> seq[8];
     long cost[8] = {};
     for (size_t i = 0; i < v.size();) {

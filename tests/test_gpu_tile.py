@@ -97,6 +97,52 @@ def test_tile_step_equals_naive(case, storage):
     _same(*got)
 
 
+# 1.2e7 points or more: the inner region in a launch of its own (boxes of 8 planes); faces without a layer, where it
+# reaches the grid's edge; an inner region of a few boxes
+LARGE = [
+    ((261, 243, 197), (10, 12, 9, 20, 15, 11)),
+    ((256, 240, 200), (0, 20, 20, 0, 0, 20)),
+    ((225, 233, 230), (0,) * 6),
+    ((97, 200, 640), (20, 20, 90, 90, 20, 20)),
+]
+
+
+@pytest.mark.parametrize("storage", [0, 1, 2])
+@pytest.mark.parametrize("case", LARGE, ids=lambda c: "x".join(map(str, c[0])))
+def test_inner_launch_equals_naive(case, storage):
+    nt = 5
+    got = []
+    for variant in (AUTO, NAIVE):
+        p, ws, tr = _prop([case], nt, [variant], storage)
+        _start(p, ws)
+        p.step(3)
+        p.step(2)
+        got.append(_out(p, tr))
+        p.close()
+    assert np.isfinite(got[0][1]).all() and np.abs(got[0][1]).max() > 0
+    _same(*got)
+
+
+def test_inner_launch_in_a_batch_and_of_16_planes():
+    """Two shots that reach the size together, eager and as a graph, and one large enough for boxes of 16 planes."""
+    for cases, graphs in (([((180, 190, 200), (15,) * 6), ((200, 170, 180), (15, 10, 0, 9, 20, 15))], (False, True)),
+                          ([((480, 460, 456), (20, 20, 20, 20, 0, 20))], (False,))):
+        nt = 4
+        single = []
+        for c in cases:
+            p, ws, tr = _prop([c], nt, [NAIVE])
+            _start(p, ws)
+            p.step(nt)
+            single += _out(p, tr)
+            p.close()
+        for graph in graphs:
+            p, ws, tr = _prop(cases, nt, [AUTO] * len(cases))
+            _start(p, ws)
+            p.step(nt, graph=graph)
+            _same(_out(p, tr), single)
+            p.close()
+
+
 def test_tile_batch_equals_single_shots():
     """All geometries in one context (one launch over every shot), and beside shots of the other variants."""
     nt = 12

@@ -749,17 +749,18 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
             if (ctx->pend > 0 && ctx->hdesc[i].traces) nrec = hi - lo;
         const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc), *one = hi - lo == 1 ? &ctx->htile[lo] : nullptr;
         const ShotH &s0 = ctx->shots[lo];
-        TileStep A{R.iu, ctx->pend, shot < 0 ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt};
+        const bool all = shot < 0 || ctx->shots.size() == 1;
+        TileStep A{R.iu, ctx->pend, all ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt};
         hipEvent_t t0 = tic(ctx);
-        fdtd_launch_inner(stor, ctx->inner_z, descs, (const TileItem *)wsp(ctx, shot < 0 ? ctx->o_inner_all : s0.o_inner),
+        fdtd_launch_inner(stor, ctx->inner_z, descs, (const TileItem *)wsp(ctx, all ? ctx->o_inner_all : s0.o_inner),
                           A, stepc, one, ctx->stream);
         if (A.nwork > 0) {
             toc(ctx, 0, t0);
             t0 = tic(ctx);
         }
         const int cls = A.nwork > 0 ? 4 : 0;
-        A.nwork = shot < 0 ? ctx->ntile_all : s0.ntile;
-        fdtd_launch_tile(stor, dd, descs, (const TileItem *)wsp(ctx, shot < 0 ? ctx->o_tile_all : s0.o_tile), A, nrec,
+        A.nwork = all ? ctx->ntile_all : s0.ntile;
+        fdtd_launch_tile(stor, dd, descs, (const TileItem *)wsp(ctx, all ? ctx->o_tile_all : s0.o_tile), A, nrec,
                          stepc, one, ctx->stream);
         toc(ctx, cls, t0);
     }
@@ -1072,8 +1073,9 @@ static void layout(fdtd_ctx *ctx) {
     ctx->o_fill = take(sizeof(FillJob) * 11 * nshots);
     size_t tile_all = 0;
     for (auto &s : ctx->shots) {
-        s.o_tile = take(sizeof(TileItem) * tile_capacity(s));
-        s.o_inner = take(ctx->inner_z > 0 ? sizeof(TileItem) * tile_capacity(s) : 0);
+        const size_t own = nshots > 1 ? sizeof(TileItem) * tile_capacity(s) : 0;
+        s.o_tile = take(own);
+        s.o_inner = take(ctx->inner_z > 0 ? own : 0);
         tile_all += tile_capacity(s);
     }
     ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
@@ -1220,14 +1222,12 @@ static int write_work_lists(fdtd_ctx *ctx) {
         s.nband = s.nwork = s.ntbwork = s.ntile = s.ninner = 0;
         if (s.tile) {
             const TileGrid g = fdtd_tile_grid(s, (int)i);
-            const std::vector<TileItem> w = tile_list({g}, ctx->inner_z);
-            if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
-            s.ntile = (int)w.size();
-            if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
-            if (ctx->inner_z > 0) {
-                const std::vector<TileItem> in = tile_list({g}, ctx->inner_z, true);
-                if (in.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
+            if (ctx->shots.size() > 1) {   // (a lone shot's lists are those of all shots)
+                const std::vector<TileItem> w = tile_list({g}, ctx->inner_z), in = tile_list({g}, ctx->inner_z, true);
+                if (w.size() > tile_capacity(s) || in.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
+                s.ntile = (int)w.size();
                 s.ninner = (int)in.size();
+                if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
                 if ((rc = upload(s.o_inner, in.data(), sizeof(TileItem) * in.size()))) return rc;
             }
             tile_all.push_back(g);
@@ -1269,12 +1269,9 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<TileItem> tw = tile_list(tile_all, ctx->inner_z);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
-    ctx->ninner_all = 0;
-    if (ctx->inner_z > 0) {
-        const std::vector<TileItem> in = tile_list(tile_all, ctx->inner_z, true);
-        ctx->ninner_all = (int)in.size();
-        if ((rc = upload(ctx->o_inner_all, in.data(), sizeof(TileItem) * in.size()))) return rc;
-    }
+    const std::vector<TileItem> in = tile_list(tile_all, ctx->inner_z, true);
+    ctx->ninner_all = (int)in.size();
+    if ((rc = upload(ctx->o_inner_all, in.data(), sizeof(TileItem) * in.size()))) return rc;
     rc = upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return rc;

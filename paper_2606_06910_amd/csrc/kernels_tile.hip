@@ -49,15 +49,6 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     const int xlo = s.Llo[0], xhi = s.Lhi[0], ylo = s.Llo[1], yhi = s.Lhi[1], zlo = s.Llo[2], zhi = s.Lhi[2];
     // axes whose band the box meets: only these need psi, zeta and the wider u^n halo
     const int xb = wi.flags & TILE_XB, yb = wi.flags & TILE_YB, zb = wi.flags & TILE_ZB;
-    // stencil weights in scalar registers for the whole kernel
-    float w1[3][5], w2[3][5];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int l = 0; l < 5; ++l) {
-            w1[d][l] = s.w1[d][l];
-            w2[d][l] = s.w2[d][l];
-        }
 
     __shared__ float U[TZ][UH][UW];     // u^n at (x0 - 8 + c, y0 - 8 + r, z0 + p); corners unused
     __shared__ float PX[TZ][TY][PXW];   // new psi_x at (x0 - 4 + c, y0 + r, z0 + p), 0 outside the slabs
@@ -236,6 +227,11 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
 
     // ---- new psi of the box grown by 4 along each axis; the box's own is stored ----
     const int np = nz - z0;   // planes of the box inside the grid (TZ or fewer)
+    float w1[3][5];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) w1[d][l] = s.w1[d][l];
     if (again(xb)) {
         const int n1 = again(np);
 #pragma unroll
@@ -278,6 +274,12 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
                 if (o >= FDTD_R && o < FDTD_R + TZ) Buf<float>::stc(rl, vz, zpn + o * Spz, pz[o]);
             }
     }
+    Coef K;
+    K.cc = s.cc;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
     if (again(xb | yb)) __syncthreads();
 
     // ---- the update ----
@@ -289,12 +291,6 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         const int n = *stepc + A.k;
         if (n >= 0 && n < s.src_nt) srcamp = s.wav[n] * s.src_scale;
     }
-    Coef K;
-    K.cc = s.cc;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int l = 0; l < 5; ++l) K.w2[d][l] = w2[d][l];
 #pragma unroll
     for (int p = 0; p < TZ; ++p) {
         if (p >= again(np)) break;
@@ -315,7 +311,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             lt = lap_interior(K, c, xl, xh, yl, yh, zl, zh);
         } else {
             const bool bz = zb && in_band(again(z0 + p), nz, zlo, zhi);
-            float L[3] = {d2_axis(w2[0], c, xl, xh), d2_axis(w2[1], c, yl, yh), d2_axis(w2[2], c, zl, zh)};
+            float L[3] = {d2_axis(K.w2[0], c, xl, xh), d2_axis(K.w2[1], c, yl, yh), d2_axis(K.w2[2], c, zl, zh)};
             if (again(xb)) {
                 float zn = 0.0f;
                 const float e = cpml_axis(L[0], dx[p], d1_lds(&PX[p][ly][lx + 4], 1, w1[0]), ax[2],

@@ -76,6 +76,7 @@ inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], con
 // count.  iz = 0: every box, TILE_Z planes deep; iz > 0 with `inner`: the inner region's boxes, iz planes deep,
 // or without: the boxes of the rest.
 inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, int iz = 0, bool inner = false) {
+    if (inner && iz == 0) return {};
     size_t all = 0;
     for (const TileGrid &g : grids) all += g.boxes() * TILE_Z / (inner ? iz : TILE_Z);
     size_t want = 8;   // a power of two, at least 24 bricks (three per XCD) where there are so many boxes

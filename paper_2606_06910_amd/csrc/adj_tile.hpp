@@ -15,7 +15,16 @@ struct AdjTile {
     int nx, ny, nz, P, PY, S, WX, SY, nmax;
     int Llo[3], Lhi[3];
     float w2[3][5], w1[3][5];
+    // receivers grouped by location: element of a field, receivers ridx[gstart[g]] .. of the group
+    const int *gpos, *gstart, *ridx;
+    const float *resid;      // dJ/dtraces [nt][nrec]
+    int nrec;
 };
 
-void fdtd_launch_adj_tile(const AdjTile *descs, const TileItem *work, int nwork, int n, int m0, int m1, int m2,
-                          hipStream_t st);
+// groups of the receivers that lie in a box of the list
+struct AdjGroups {
+    int lo, hi;
+};
+
+void fdtd_launch_adj_tile(const AdjTile *descs, const TileItem *work, const AdjGroups *grp, int nwork, int n, int m0,
+                          int m1, int m2, hipStream_t st);

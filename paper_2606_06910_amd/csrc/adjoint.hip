@@ -403,7 +403,7 @@ struct AdjLayout {
     // AdjShot entries, increment jobs, checkpoint-restore jobs, the slab-pass and pass-3 block tables
     size_t tab = 0, jobs = 0, rjobs = 0, smap = 0, bmap = 0, bmap2 = 0;
     // one-launch reverse step: the other psi_b, zeta_b buffers (no E, K, W, smap, bmap2), its descriptors and boxes
-    size_t psib2[3] = {}, zetab2[3] = {}, atab = 0, items = 0;
+    size_t psib2[3] = {}, zetab2[3] = {}, atab = 0, items = 0, gpos = 0, grp = 0;
     size_t total = 0;
     int nck = 0;   // checkpoint slots
 };
@@ -475,6 +475,8 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
     L.bmap2 = take(sizeof(int) * (size_t)std::max(tiles ? 0L : blocks2, 1L));
     L.atab = take(tiles ? sizeof(AdjTile) * nctx : 0);
     L.items = take(tiles ? sizeof(TileItem) * tile_list_bound((size_t)boxes) : 0);
+    L.gpos = take(tiles ? (size_t)std::max(s.nrec, 1) * 4 : 0);
+    L.grp = take(tiles ? sizeof(AdjGroups) * tile_list_bound((size_t)boxes) : 0);
     L.total = off;
     return L;
 }
@@ -551,6 +553,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     const bool tiles = adj_tiles(ctx);
     std::vector<AdjTile> atab(tiles ? nsh : 0);
     std::vector<TileGrid> grids;
+    std::map<std::array<int, 4>, AdjGroups> at_box;   // (shot of the sweep, box z, y, x): the groups in the box
     int bbase = 0, bbase2 = 0, maxg = 0;
     long maxrows = 0, maxck = 0;
     for (int q = 0; q < nsh; ++q) {
@@ -560,22 +563,15 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         AdjShot &a = tab[q];
         memset(&a, 0, sizeof a);
         a.s = ctx->hdesc[sh[q]];
-        fdtd_launch_fill_zero(B + L.mu, a256(s.elems * 4) * (size_t)mu_slots(every), st);
+        // the ring, psi_b and zeta_b (both buffers), E, K and W, which lie one after another
+        fdtd_launch_fill_zero(B + L.mu, L.gstart - L.mu, st);
         a.mu = (float *)origin4(s, B + L.mu);
         a.mstride = (long)(a256(s.elems * 4) / 4);
         a.mslots = mu_slots(every);
         for (int d = 0; d < 3; ++d) {
-            fdtd_launch_fill_zero(B + L.psib[d], a256(s.psi_elems[d] * 4), st);
-            fdtd_launch_fill_zero(B + L.zetab[d], a256(s.psi_elems[d] * 4), st);
             a.psib[d] = (float *)(B + L.psib[d]);
             a.zetab[d] = (float *)(B + L.zetab[d]);
-            if (tiles) {
-                fdtd_launch_fill_zero(B + L.psib2[d], a256(s.psi_elems[d] * 4), st);
-                fdtd_launch_fill_zero(B + L.zetab2[d], a256(s.psi_elems[d] * 4), st);
-            } else if (s.Llo[d] + s.Lhi[d] > 0) {
-                fdtd_launch_fill_zero(B + L.E[d], a256(s.elems * 4), st);
-                fdtd_launch_fill_zero(B + L.K[d], a256(s.elems * 4), st);
-                fdtd_launch_fill_zero(B + L.W[d], a256(s.elems * 4), st);
+            if (!tiles && s.Llo[d] + s.Lhi[d] > 0) {
                 a.E[d] = (float *)origin4(s, B + L.E[d]);
                 a.K[d] = (float *)origin4(s, B + L.K[d]);
                 a.W[d] = (float *)origin4(s, B + L.W[d]);
@@ -589,7 +585,8 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         a.G = grad[q];
         a.resid = resid[q];
         a.nrec = s.nrec;
-        // receivers grouped by location, in first-appearance order; receiver order within a group
+        // receivers grouped by location, the groups by box and in it by first appearance; receiver order within a
+        // group
         if (s.nrec > 0) {
             std::vector<int32_t> h((size_t)s.nrec * 3);
             AHIP(ctx, hipMemcpy(h.data(), s.rec, h.size() * 4, hipMemcpyDeviceToHost));
@@ -606,14 +603,27 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
                     members[it->second].push_back(r);
                 }
             }
-            for (auto &m : members) {
-                gstart.push_back((int)ridx.size());
-                ridx.insert(ridx.end(), m.begin(), m.end());
+            std::map<std::array<int32_t, 3>, std::vector<int>> boxes;   // box (z, y, x) -> its groups
+            for (int g = 0; g < (int)members.size(); ++g) {
+                const int32_t *c = &h[3 * members[g][0]];
+                boxes[{c[2] / TILE_Z, c[1] / TILE_Y, c[0] / TILE_X}].push_back(g);
+            }
+            std::vector<int> gpos;
+            for (const auto &b : boxes) {
+                const int lo = (int)gstart.size();
+                for (const int g : b.second) {
+                    const int32_t *c = &h[3 * members[g][0]];
+                    gpos.push_back((int)((long)origin_elems(s) + c[2] * (long)s.S + c[1] * (long)s.P + c[0]));
+                    gstart.push_back((int)ridx.size());
+                    ridx.insert(ridx.end(), members[g].begin(), members[g].end());
+                }
+                at_box[{q, b.first[0], b.first[1], b.first[2]}] = AdjGroups{lo, (int)gstart.size()};
             }
             gstart.push_back((int)ridx.size());
             a.ngroups = (int)members.size();
             AHIP(ctx, hipMemcpyAsync(B + L.gstart, gstart.data(), gstart.size() * 4, hipMemcpyHostToDevice, st));
             AHIP(ctx, hipMemcpyAsync(B + L.ridx, ridx.data(), ridx.size() * 4, hipMemcpyHostToDevice, st));
+            if (tiles) AHIP(ctx, hipMemcpyAsync(B + L.gpos, gpos.data(), gpos.size() * 4, hipMemcpyHostToDevice, st));
             AHIP(ctx, hipStreamSynchronize(st));
         }
         a.gstart = (const int *)(B + L.gstart);
@@ -651,6 +661,11 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
             e.nmax = ds.nmax;
             memcpy(e.w2, ds.w2, sizeof e.w2);
             memcpy(e.w1, ds.w1, sizeof e.w1);
+            e.gpos = (const int *)(B + L.gpos);
+            e.gstart = a.gstart;
+            e.ridx = a.ridx;
+            e.resid = a.resid;
+            e.nrec = a.nrec;
             grids.push_back(fdtd_tile_grid(s, q));
         }
         a.btx = cnt.btx;
@@ -723,10 +738,29 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     const AdjTile *atab_d = (const AdjTile *)(s0h.ck_buf + L0.atab);
     const TileItem *items_d = (const TileItem *)(s0h.ck_buf + L0.items);
     const std::vector<TileItem> items = tile_list(grids);
+    const AdjGroups *grp_d = (const AdjGroups *)(s0h.ck_buf + L0.grp);
+    std::vector<AdjGroups> grp(items.size(), AdjGroups{0, 0});
+    for (size_t i = 0; i < items.size() && !at_box.empty(); ++i) {
+        const TileItem &w = items[i];
+        if (w.flags < 0) continue;
+        const auto it = at_box.find({w.flags & 0xff, w.z0 / TILE_Z, w.y0 / TILE_Y, w.x0 / TILE_X});
+        if (it != at_box.end()) grp[i] = it->second;
+    }
     if (tiles) {
+        AHIP(ctx, hipMemcpyAsync((void *)grp_d, grp.data(), sizeof(AdjGroups) * grp.size(), hipMemcpyHostToDevice, st));
         AHIP(ctx, hipMemcpyAsync((void *)atab_d, atab.data(), sizeof(AdjTile) * atab.size(), hipMemcpyHostToDevice, st));
         AHIP(ctx, hipMemcpyAsync((void *)items_d, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice,
                                  st));
+    }
+    // steps whose every shot is a tile shot write the increments themselves
+    bool fused = true;
+    for (int q = 0; q < nsh; ++q) fused = fused && ctx->shots[sh[q]].tile;
+    TileDesc *td = (TileDesc *)fdtd_ws(ctx, ctx->o_tdesc);
+    for (int q = 0; q < nsh && fused; ++q) {
+        const ShotH &s = ctx->shots[sh[q]];
+        ctx->htile[sh[q]].inc = s.ck_buf + adj_layout(ctx, s, every, s.ck_count).seg;
+        ctx->htile[sh[q]].inc_slot = (long)a256(s.elems * s.esz);
+        AHIP(ctx, hipMemcpyAsync(td + sh[q], &ctx->htile[sh[q]], sizeof(TileDesc), hipMemcpyHostToDevice, st));
     }
     AHIP(ctx, hipStreamSynchronize(st));
     // e of the newest level (in buffer qb) into slot j of half b, every shot in one launch
@@ -766,8 +800,11 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         ctx->pend = 0;
         store_increment(b, 0, ctx->iu);   // e^{s0} = u^{s0} - u^{s0 - 1}
         for (int n = s0; n < s1; ++n) {
+            const int slot = n - s0 + 1;   // of e^{n+1}
+            ctx->inc = fused ? b * (every + 1) + slot : -1;
             fdtd_enqueue_step_shot(ctx, step_shot);
-            store_increment(b, n - s0 + 1, ctx->iu);   // e^{n+1}
+            ctx->inc = -1;
+            if (!fused) store_increment(b, slot, ctx->iu);
         }
         if (sa != st) {
             AHIP(ctx, hipEventRecord(ctx->ev_adj[b], st));
@@ -780,12 +817,14 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         int top = s1 - 1;
         for (int n = s1 - 1; n >= s0; --n) {
             const AdjStep as{n, n % M, (n + 1) % M, (n + 2) % M};
-            if (maxg > 0) hipLaunchKernelGGL(k_adj_resid, dim3((maxg + 255) / 256, nsh), dim3(256), 0, sa, tab_d, as);
+            // (k_adj_tile of step n adds the residuals of step n - 1)
+            if (maxg > 0 && (!tiles || n == nt - 1))
+                hipLaunchKernelGGL(k_adj_resid, dim3((maxg + 255) / 256, nsh), dim3(256), 0, sa, tab_d, as);
             if (nslab > 0) {
                 hipLaunchKernelGGL(k_adj_p1, dim3(nslab), dim3(256), 0, sa, tab_d, smap_d, as);
                 hipLaunchKernelGGL(k_adj_p2, dim3(nslab), dim3(256), 0, sa, tab_d, smap_d, as);
             }
-            if (tiles) fdtd_launch_adj_tile(atab_d, items_d, (int)items.size(), n, as.m0, as.m1, as.m2, sa);
+            if (tiles) fdtd_launch_adj_tile(atab_d, items_d, grp_d, (int)items.size(), n, as.m0, as.m1, as.m2, sa);
             else hipLaunchKernelGGL(k_adj_p3, dim3((unsigned)bbase2), dim3(256), 0, sa, tab_d, bmap2_d, as);
             if (top - n + 1 == chunk || n == s0) {
                 const AdjGrad ag{b, s0, n, top - n + 1};
@@ -814,6 +853,9 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     fdtd_clear_graphs(ctx);
     for (int q = 0; q < nsh; ++q) {
         ctx->hdesc[sh[q]] = saved[q];
+        ctx->htile[sh[q]].inc = nullptr;
+        if (fused)
+            AHIP(ctx, hipMemcpyAsync(td + sh[q], &ctx->htile[sh[q]], sizeof(TileDesc), hipMemcpyHostToDevice, st));
         AHIP(ctx, hipMemcpyAsync(dd + sh[q], &ctx->hdesc[sh[q]], sizeof(DevShot), hipMemcpyHostToDevice, st));
     }
     AHIP(ctx, hipStreamSynchronize(st));

@@ -750,7 +750,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc), *one = hi - lo == 1 ? &ctx->htile[lo] : nullptr;
         const ShotH &s0 = ctx->shots[lo];
         const bool all = shot < 0 || ctx->shots.size() == 1;
-        TileStep A{R.iu, ctx->pend, all ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt};
+        TileStep A{R.iu, ctx->pend, all ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt, ctx->inc};
         hipEvent_t t0 = tic(ctx);
         fdtd_launch_inner(stor, ctx->inner_z, descs, (const TileItem *)wsp(ctx, all ? ctx->o_inner_all : s0.o_inner),
                           A, stepc, one, ctx->stream);
@@ -1022,8 +1022,19 @@ static void copy_state(fdtd_ctx *ctx, int i, char *ck, bool save) {
 }
 
 static void save_checkpoint(fdtd_ctx *ctx, int i, int k) {
+    // the layout of copy_state in one launch: eight copies take longer to start than to run on small shots
     ShotH &s = ctx->shots[i];
-    copy_state(ctx, i, s.ck_buf + (size_t)k * fdtd_state_bytes(s), true);
+    PackJob j{};
+    j.dst = s.ck_buf + (size_t)k * fdtd_state_bytes(s);
+    j.src[0] = wsp(ctx, s.o_u[ctx->iu]);
+    j.src[1] = s.esz == 2 ? wsp(ctx, s.o_d) : wsp(ctx, s.o_u[ctx->ium1]);
+    j.n16[0] = j.n16[1] = align256(s.elems * s.esz) / 16;
+    for (int d = 0; d < 3; ++d) {
+        j.src[2 + 2 * d] = wsp(ctx, fdtd_psi_off(s, d, ctx->iu));
+        j.src[3 + 2 * d] = wsp(ctx, s.o_zeta[d]);
+        j.n16[2 + 2 * d] = j.n16[3 + 2 * d] = align256(s.psi_elems[d] * 4) / 16;
+    }
+    fdtd_launch_pack(j, ctx->stream);
 }
 
 // workspace layout

@@ -111,6 +111,8 @@ struct TileDesc {
     int sx, sy, sz, src_nt;
     float src_scale;
     const float *wav;
+    char *inc;       // increment slots of an adjoint sweep (FP32 fields), first byte, and
+    long inc_slot;   // the bytes of one
 };
 
 // Strided box copy (ghost pack/unpack).  Rows (ex elements) are copied in
@@ -158,6 +160,13 @@ struct WorkItem {
 #define TILE_Z 4
 struct TileStep {
     int iu, k, nwork, rec_lo, nt;
+    int inc = -1;   // >= 0: u^{n+1} - u^n goes to this slot of TileDesc::inc, laid out as the field
+};
+// Up to 8 ranges copied one after another to dst, each starting on a multiple of 256 bytes there.
+struct PackJob {
+    const char *src[8];
+    unsigned long long n16[8];   // pieces of 16 bytes
+    char *dst;
 };
 // One box: shot (low byte) and the axes whose band it meets (negative: an idle item); first point.
 #define TILE_XB 0x100

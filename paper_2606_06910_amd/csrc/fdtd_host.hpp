@@ -94,6 +94,7 @@ struct fdtd_ctx {
     int inner_z = 0;          // planes of a box of k_inner; 0: k_tile takes every box
     bool tile_nt = false;     // tile shots too large for any cache to hold a level from step to step
     size_t fill_max16 = 0;    // longest range of the reset's fill list
+    int inc = -1;             // adjoint sweeps: the slot for a tile shot's increment (TileStep::inc)
     int pend = 0;             // steps enqueued since the device step counter was last advanced
     // multi-shot z-march launches: one per distinct (ry, zchunk) plan
     struct Group {

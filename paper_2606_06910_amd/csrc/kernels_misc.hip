@@ -9,6 +9,7 @@
 //                    loopback stands in for the neighbour of one GPU's
 //                    pencil-yz share, paper section "Multi-GPU Decomposition
 //                    and Halo Exchange")
+//  k_pack            the arrays of a state copied one after another (checkpoints)
 //  k_finite          flag any NaN/Inf in a field
 #include "fdtd_dev.hpp"
 
@@ -147,6 +148,16 @@ __global__ __launch_bounds__(256) void k_copy_jobs(const CopyJob *__restrict__ j
     }
 }
 
+// grid: (blocks, 8 ranges); range r starts on the next multiple of 256 bytes after range r - 1
+__global__ __launch_bounds__(256) void k_pack(const PackJob j) {
+    size_t off = 0;
+    for (int r = 0; r < (int)blockIdx.y; ++r) off += (j.n16[r] + 15) & ~(size_t)15;
+    const uint4 *s = (const uint4 *)j.src[blockIdx.y];
+    uint4 *d = (uint4 *)j.dst + off;
+    const size_t n = j.n16[blockIdx.y], stride = (size_t)gridDim.x * 256;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) d[i] = s[i];
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_finite(const T *__restrict__ u, int nx, int ny, int P, int S,
                                                unsigned int *__restrict__ bad) {
@@ -227,6 +238,12 @@ void fdtd_launch_get_prev(int stor, const void *u, const void *d, float *dst, in
 void fdtd_launch_set_prev(int stor, const void *u, void *d, const float *src, int nx, int ny, int nz, int P, int S,
                           float sc, hipStream_t st) {
     MISC_DISPATCH(stor, sp, u, d, src, nx, ny, nz, P, S, sc, st);
+}
+void fdtd_launch_pack(const PackJob &j, hipStream_t st) {
+    size_t n = 0;
+    for (const auto v : j.n16) n = v > n ? v : n;
+    const size_t gx = (n + 1023) / 1024;   // four pieces per thread of the longest range
+    if (n > 0) hipLaunchKernelGGL(k_pack, dim3((unsigned)(gx < 2048 ? gx : 2048), 8), dim3(256), 0, st, j);
 }
 void fdtd_launch_copy_jobs(const void *jobs, int njobs, long max_rows, hipStream_t st) {
     if (njobs <= 0 || max_rows <= 0) return;

@@ -29,6 +29,8 @@
 #include "fdtd_launch.hpp"
 #include "tile_dev.hpp"
 
+#include <type_traits>
+
 namespace {
 constexpr int UW = TX + 4 * FDTD_R, UH = TY + 4 * FDTD_R;   // LDS plane of u^n: 8 columns and rows on each side
 constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, new psi_y columns: 4 on each side
@@ -36,8 +38,11 @@ constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, n
 typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
 }  // namespace
 
-// one box (D: TileDesc in the constant or the kernel-argument address space)
-template <typename T, bool NT, typename D>
+// one box (D: TileDesc in the constant or the kernel-argument address space).  INC: the
+// increment u^{n+1} - u^n is stored too (an adjoint sweep keeps it), 4 bytes per
+// point here against 12 in a pass of its own; a template flag, because as a test in
+// the kernel it cost plain steps 1 % (160^3).
+template <typename T, bool NT, bool INC, typename D>
 __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const TileStep &A,
                                          const int *__restrict__ stepc) {
     const int t = (int)threadIdx.x;
@@ -284,6 +289,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
 
     // ---- the update ----
     const Rsrc rw = make_rsrc(s.u[A.iu ^ 1] + base * esz), rs = IsInc<T>::v ? make_rsrc(s.dinc + base * esz) : rw;
+    const Rsrc ri = INC ? make_rsrc(s.inc + A.inc * s.inc_slot + base * esz) : rw;
     const int src_tile = uniform(s.sx >= x0 && s.sx < x0 + TX && s.sy >= y0 && s.sy < y0 + TY && s.sz >= z0 &&
                                  s.sz < z0 + TZ);
     float srcamp = 0.0f;
@@ -355,6 +361,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             Buf<T>::stc(rw, vc, fu + p * Sb, up.u);
             if constexpr (IsInc<T>::v) Buf<T>::stc(rs, vc, fu + p * Sb, up.d);
         }
+        if constexpr (INC) Buf<T>::st(ri, vc, fu + p * Sb, up.u - c);
     }
 }
 
@@ -367,7 +374,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
 // kernel leaves it, and 345 us on all.  Boxes of 8 planes hold 54 VGPRs and 20 KB
 // of LDS: eight blocks per CU, the memory's latency hidden by other blocks
 // instead of a register queue along z.
-template <typename T, int IZ, bool NT, typename D>
+template <typename T, int IZ, bool NT, bool INC, typename D>
 __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const TileStep &A,
                                           const int *__restrict__ stepc) {
     constexpr int F = FDTD_R, LW = TX + 2 * F, LH = TY + 2 * F, LP = LW * LH, XH = IZ / 4;
@@ -431,6 +438,7 @@ __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const 
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
+    const Rsrc ri = INC ? make_rsrc(s.inc + A.inc * s.inc_slot + base * esz) : rw;
     uint32_t so = fu;
 #pragma unroll
     for (int p = 0; p < IZ; ++p, so += Sb) {
@@ -455,20 +463,21 @@ __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const 
             Buf<T>::stc(rw, vc, so, up.u);
             if constexpr (IsInc<T>::v) Buf<T>::stc(rs, vc, so, up.d);
         }
+        if constexpr (INC) Buf<T>::st(ri, vc, so, up.u - q[p + F]);
     }
 }
-template <typename T, int IZ, bool ONE, bool NT>
+template <typename T, int IZ, bool ONE, bool NT, bool INC>
 __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
                                                TileStep A, const int *__restrict__ stepc, const TileDesc one) {
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) inner_box<T, IZ, NT>(one, wi, A, stepc);
-    else inner_box<T, IZ, NT>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    if constexpr (ONE) inner_box<T, IZ, NT, INC>(one, wi, A, stepc);
+    else inner_box<T, IZ, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
 }
 
 // ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
 // before the box's own)
-template <typename T, bool ONE, bool NT>
+template <typename T, bool ONE, bool NT, bool INC>
 __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ shots, const TileDesc *__restrict__ descs,
                                                  const TileItem *__restrict__ work, TileStep A,
                                                  const int *__restrict__ stepc, const TileDesc one) {
@@ -488,35 +497,38 @@ __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ sho
     }
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) tile_box<T, NT>(one, wi, A, stepc);
-    else tile_box<T, NT>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    if constexpr (ONE) tile_box<T, NT, INC>(one, wi, A, stepc);
+    else tile_box<T, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+}
+
+// launch f(ONE, NT, INC as std::bool_constant); only FP32 fields have increments
+template <typename T, typename F>
+static void with_flags(bool one, bool nt, bool inc, F f) {
+    auto b = [&](auto ONE, auto NT) {
+        if constexpr (!IsInc<T>::v) {
+            if (inc) return f(ONE, NT, std::true_type{});
+        }
+        f(ONE, NT, std::false_type{});
+    };
+    auto a = [&](auto ONE) { nt ? b(ONE, std::true_type{}) : b(ONE, std::false_type{}); };
+    one ? a(std::true_type{}) : a(std::false_type{});
 }
 
 template <typename T, int IZ>
 static void launch_inner_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
                            const TileDesc *one, hipStream_t st) {
-    const dim3 grid((unsigned)A.nwork);
-    if (one && A.nt) hipLaunchKernelGGL((k_inner<T, IZ, true, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
-    else if (one) hipLaunchKernelGGL((k_inner<T, IZ, true, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
-    else if (A.nt)
-        hipLaunchKernelGGL((k_inner<T, IZ, false, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
-    else
-        hipLaunchKernelGGL((k_inner<T, IZ, false, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
+    with_flags<T>(one, A.nt, A.inc >= 0, [&](auto ONE, auto NT, auto INC) {
+        hipLaunchKernelGGL((k_inner<T, IZ, ONE.value, NT.value, INC.value>), dim3((unsigned)A.nwork), dim3(256), 0, st,
+                           d_descs, work, A, stepc, one ? *one : TileDesc{});
+    });
 }
 template <typename T>
 static void launch_tile_t(const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
                           int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
-    const dim3 grid((unsigned)(A.nwork + nrec));
-    if (one && A.nt)
-        hipLaunchKernelGGL((k_tile<T, true, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
-    else if (one)
-        hipLaunchKernelGGL((k_tile<T, true, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc, *one);
-    else if (A.nt)
-        hipLaunchKernelGGL((k_tile<T, false, true>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc,
-                           TileDesc{});
-    else
-        hipLaunchKernelGGL((k_tile<T, false, false>), grid, dim3(256), 0, st, d_shots, d_descs, work, A, stepc,
-                           TileDesc{});
+    with_flags<T>(one, A.nt, A.inc >= 0, [&](auto ONE, auto NT, auto INC) {
+        hipLaunchKernelGGL((k_tile<T, ONE.value, NT.value, INC.value>), dim3((unsigned)(A.nwork + nrec)), dim3(256), 0,
+                           st, d_shots, d_descs, work, A, stepc, one ? *one : TileDesc{});
+    });
 }
 
 void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
@@ -527,17 +539,11 @@ void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs,
     else launch_tile_t<float>(d_shots, d_descs, work, A, nrec, stepc, one, st);
 }
 
-template <typename T>
-static void launch_inner_z(int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
-                           const TileDesc *one, hipStream_t st) {
-    if (iz == 16) launch_inner_t<T, 16>(d_descs, work, A, stepc, one, st);
-    else if (iz == 8) launch_inner_t<T, 8>(d_descs, work, A, stepc, one, st);
-    else launch_inner_t<T, 4>(d_descs, work, A, stepc, one, st);
-}
 void fdtd_launch_inner(int stor, int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
                        const int *stepc, const TileDesc *one, hipStream_t st) {
     if (A.nwork <= 0) return;
-    if (stor == 1) launch_inner_z<_Float16>(iz, d_descs, work, A, stepc, one, st);
-    else if (stor == 2) launch_inner_z<__bf16>(iz, d_descs, work, A, stepc, one, st);
-    else launch_inner_z<float>(iz, d_descs, work, A, stepc, one, st);
+    if (stor == 1) launch_inner_t<_Float16, 8>(d_descs, work, A, stepc, one, st);
+    else if (stor == 2) launch_inner_t<__bf16, 8>(d_descs, work, A, stepc, one, st);
+    else if (iz == 16) launch_inner_t<float, 16>(d_descs, work, A, stepc, one, st);
+    else launch_inner_t<float, 8>(d_descs, work, A, stepc, one, st);
 }

@@ -272,6 +272,54 @@ def test_adjoint_in_one_launch_equals_passes(case):
     assert np.array_equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("rec", ["dense", "corners"])
+def test_residuals_in_the_reverse_step(rec):
+    """Residuals added by the one-launch reverse step against the pass of their own: more receiver locations in a box
+    than threads, with repeated ones, and receivers on the corners of boxes and of the grid."""
+    import torch
+
+    nt, n, lay = 9, (65, 33, 34), (10, 7, 5, 8, 6, 3)
+    if rec == "dense":
+        g = np.stack(np.meshgrid(np.arange(28, 65), np.arange(7, 10), np.arange(3, 9), indexing="ij"), -1).reshape(-1, 3)
+        r = np.concatenate([g, g[::7], g[:5]])
+        r = r[np.random.default_rng(0).permutation(len(r))]
+    else:
+        r = np.array([(x, y, z) for x in (0, 31, 32, 64) for y in (0, 7, 8, 32) for z in (0, 3, 4, 33)])
+    close = ((24, 20, 30), (4, 4, 4, 4, 8, 8))
+    got = []
+    for cases in ([(n, lay)], [(n, lay), close]):
+        p, ws, _ = _prop(cases, nt, [ZMARCH] * len(cases))
+        p.set_receivers(0, r.astype(np.int32))
+        tr = p.record(0, nt)
+        for i in range(len(cases)):
+            p.set_checkpointing(i, 4, nt)
+        p.reset()
+        p.step(nt)
+        g = torch.Generator().manual_seed(3)
+        got.append([tr.cpu().numpy(), p.adjoint(0, nt, torch.randn(nt, len(r), generator=g)).cpu().numpy()])
+        p.close()
+    assert np.abs(got[0][1]).max() > 0
+    _same(*got)
+
+
+def test_increments_of_the_inner_launch():
+    """A gradient whose recomputed steps take two launches, against one recomputed by the naive kernel."""
+    import torch
+
+    nt = 5
+    got = []
+    for variant in (AUTO, NAIVE):
+        p, ws, _ = _prop([LARGE[0]], nt, [variant])
+        p.set_checkpointing(0, 3, nt)
+        _start(p, ws)
+        p.step(nt)
+        g = torch.Generator().manual_seed(4)
+        got.append([p.adjoint(0, nt, torch.randn(nt, 12, generator=g)).cpu().numpy()])
+        p.close()
+    assert np.abs(got[0][0]).max() > 0
+    _same(*got)
+
+
 @pytest.mark.parametrize("case", [
     ((9, 9, 9), (4, 4, 4, 4, 4, 4)),
     ((64, 32, 24), (10, 10, 8, 8, 6, 6)),

@@ -278,35 +278,37 @@ TileGrid fdtd_tile_grid(const ShotH &s, int shot) {
 }
 // Whether a shot takes the tile kernels (reported as the variant they replace): the
 // automatic variant, no ghost faces, a z window of k_tile (TILE_Z + 8 planes) that
-// meets one z layer at most, layer arrays within 32 bits of offset, and in 16-bit
-// storage fewer than kTileShot16 points.  Measured, us per step of a cube with
-// 20-cell layers (10 below 128^3), the other kernels against these, FP32: 64^3
-// 18.8 / 8.5, 96^3 33 / 11, 128^3 57 / 22, 160^3 100 / 30, 200^3 135 / 53, 256^3 157
-// / 106, 300^3 225 / 158, 384^3 350 / 277, 512^3 674 / 617, 576^3 918 / 835, 640^3
-// 1168 / 1173, 768^3 1953 / 1887; FP16: 256^3 159 / 115, 384^3 336 / 291, 512^3 695
-// / 643, 640^3 1230 / 1153, 768^3 1764 / 1879.
+// meets one z layer at most, and layer arrays within 32 bits of offset.  Measured,
+// us per step of a cube with 20-cell layers (10 below 128^3), the other kernels
+// against these, FP32: 64^3 18.8 / 8.5, 96^3 33 / 11, 128^3 57 / 22, 160^3 100 / 30,
+// 200^3 135 / 53, 256^3 157 / 106, 300^3 225 / 158, 384^3 350 / 277, 512^3 674 / 617,
+// 576^3 918 / 835, 640^3 1168 / 1173, 768^3 1953 / 1887; FP16: 200^3 137 / 54, 256^3
+// 158 / 106, 384^3 337 / 275, 512^3 696 / 586, 640^3 1231 / 1040, 768^3 1765 / 1645,
+// 896^3 2666 / 2704, 1000^3 3679 / 3455.
 static bool tile_rule(const ShotH &s) {
     if (s.c.variant != FDTD_VARIANT_AUTO || s.gy || s.gz) return false;
-    if (s.esz == 2 && (long)s.nx * s.ny * s.nz >= kTileShot16) return false;
     if (s.Llo[2] > 0 && s.Lhi[2] > 0 && s.nz - s.Llo[2] - s.Lhi[2] < TILE_Z + 2 * FDTD_R) return false;
     size_t b = (size_t)3 * 4 * s.nmax * 4;
     for (int d = 0; d < 3; ++d) b += 3 * (s.psi_elems[d] * 4 + 256);
     return b < (size_t)1 << 31;
 }
-// How the tile shots of a context of `points` points in all are stepped: inner_z,
-// the depth of k_inner's boxes (0: k_tile takes every box, one launch), and nt,
-// the non-temporal hint.  A launch of its own for the points outside the bands
+// How the tile shots of a context of `points` points in all are stepped: k_inner's
+// boxes (z = 0: k_tile takes every box, one launch), and nt, k_tile's non-temporal
+// hint.  A launch of its own for the points outside the bands
 // (54 instead of 115 VGPRs, 8 instead of 4 waves per SIMD) costs one launch more;
 // us per step without it / with boxes of 8 / of 16 planes, FP32: 160^3 30.3 / 34.7
 // / 35.8, 200^3 52.9 / 56.1 / 57.1, 256^3 106 / 106 / 106, 384^3 294 / 277 / 278,
-// 512^3 650 / 617 / 613, 768^3 - / 1908 / 1887; FP16: 256^3 114 / 114 / 114, 384^3
-// 309 / 287 / 292, 512^3 689 / 640 / 646.  The hint, once the shots outgrow the
+// 512^3 650 / 617 / 613, 768^3 - / 1908 / 1887.  In 16-bit storage the boxes are 64
+// points wide, two to a lane (whole lines; 32 wide 512^3 took 640 us, the 64 wide
+// ones 586), and leave more of a small grid to k_tile: FP16 without / with, 232^3 75 /
+// 79, 256^3 114 / 106, 300^3 - / 166.  The hint, once the shots outgrow the
 // 256 MiB last-level cache: FP32 200^3 52.9 -> 59.9, 256^3 108.5 -> 105.5, 512^3 640
-// -> 617; never in 16-bit storage, where a box row is half a line and its stores
-// have to meet their other half in L2 (512^3 640 -> 687).
-static void tile_plan(long points, int storage, int &inner_z, bool &nt) {
-    const bool large = points >= 12000000;
-    inner_z = !large ? 0 : (storage == FDTD_F32 && points >= 100000000 ? 16 : 8);
+// -> 617; not in 16-bit storage, where a row of k_tile's box is half a line and its
+// stores have to meet their other half in L2 (512^3 640 -> 687).
+static void tile_plan(long points, int storage, InnerBox &inner, bool &nt) {
+    const bool large = points >= (storage == FDTD_F32 ? 12000000 : 16000000);
+    inner.x = storage == FDTD_F32 ? TILE_X : 2 * TILE_X;
+    inner.z = !large ? 0 : (storage == FDTD_F32 && points >= 100000000 ? 16 : 8);
     nt = large && storage == FDTD_F32;
 }
 static size_t tile_capacity(const ShotH &s) {
@@ -752,7 +754,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         const bool all = shot < 0 || ctx->shots.size() == 1;
         TileStep A{R.iu, ctx->pend, all ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt, ctx->inc};
         hipEvent_t t0 = tic(ctx);
-        fdtd_launch_inner(stor, ctx->inner_z, descs, (const TileItem *)wsp(ctx, all ? ctx->o_inner_all : s0.o_inner),
+        fdtd_launch_inner(stor, ctx->inner, descs, (const TileItem *)wsp(ctx, all ? ctx->o_inner_all : s0.o_inner),
                           A, stepc, one, ctx->stream);
         if (A.nwork > 0) {
             toc(ctx, 0, t0);
@@ -1086,11 +1088,11 @@ static void layout(fdtd_ctx *ctx) {
     for (auto &s : ctx->shots) {
         const size_t own = nshots > 1 ? sizeof(TileItem) * tile_capacity(s) : 0;
         s.o_tile = take(own);
-        s.o_inner = take(ctx->inner_z > 0 ? own : 0);
+        s.o_inner = take(ctx->inner.z > 0 ? own : 0);
         tile_all += tile_capacity(s);
     }
     ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
-    ctx->o_inner_all = take(ctx->inner_z > 0 ? sizeof(TileItem) * tile_all : 0);
+    ctx->o_inner_all = take(ctx->inner.z > 0 ? sizeof(TileItem) * tile_all : 0);
     ctx->need = off;
 }
 
@@ -1188,7 +1190,7 @@ int fdtd_create(const fdtd_shot_config *shots, int32_t nshots, void *hip_stream,
         sh.tile = tile_rule(sh);
         if (sh.tile) tile_points += (long)sh.nx * sh.ny * sh.nz;
     }
-    tile_plan(tile_points, ctx->storage, ctx->inner_z, ctx->tile_nt);
+    tile_plan(tile_points, ctx->storage, ctx->inner, ctx->tile_nt);
     for (auto &sh : ctx->shots)
         if (sh.tb_bufs && nshots != 1) {
             delete ctx;
@@ -1234,7 +1236,7 @@ static int write_work_lists(fdtd_ctx *ctx) {
         if (s.tile) {
             const TileGrid g = fdtd_tile_grid(s, (int)i);
             if (ctx->shots.size() > 1) {   // (a lone shot's lists are those of all shots)
-                const std::vector<TileItem> w = tile_list({g}, ctx->inner_z), in = tile_list({g}, ctx->inner_z, true);
+                const std::vector<TileItem> w = tile_list({g}, ctx->inner), in = tile_list({g}, ctx->inner, true);
                 if (w.size() > tile_capacity(s) || in.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
                 s.ntile = (int)w.size();
                 s.ninner = (int)in.size();
@@ -1277,10 +1279,10 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<BandItem> bw = xcd_order(band_all);
     ctx->nband_all = (int)bw.size();
     if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
-    const std::vector<TileItem> tw = tile_list(tile_all, ctx->inner_z);
+    const std::vector<TileItem> tw = tile_list(tile_all, ctx->inner);
     ctx->ntile_all = (int)tw.size();
     if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
-    const std::vector<TileItem> in = tile_list(tile_all, ctx->inner_z, true);
+    const std::vector<TileItem> in = tile_list(tile_all, ctx->inner, true);
     ctx->ninner_all = (int)in.size();
     if ((rc = upload(ctx->o_inner_all, in.data(), sizeof(TileItem) * in.size()))) return rc;
     rc = upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());

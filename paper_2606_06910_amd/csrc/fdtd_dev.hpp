@@ -162,6 +162,10 @@ struct TileStep {
     int iu, k, nwork, rec_lo, nt;
     int inc = -1;   // >= 0: u^{n+1} - u^n goes to this slot of TileDesc::inc, laid out as the field
 };
+// Extents of k_inner's boxes (x, TILE_Y, z); z = 0: none, k_tile takes every box.
+struct InnerBox {
+    int x = TILE_X, z = 0;
+};
 // Up to 8 ranges copied one after another to dst, each starting on a multiple of 256 bytes there.
 struct PackJob {
     const char *src[8];
@@ -481,24 +485,41 @@ template <> struct Buf<__bf16> {
 // to FP32.  The scalar offset must stay in range as for Buf.  (The 64-bit
 // load is reinterpreted whole: taking its two elements one by one makes the
 // compiler emit a single-dword load and repeat it in both.)
-template <typename T> struct Buf2;
+template <typename T> struct Buf2 {
+    static __device__ __forceinline__ float2 widen(uint32_t v) {
+        return make_float2((float)__builtin_bit_cast(T, (unsigned short)(v & 0xffffu)),
+                           (float)__builtin_bit_cast(T, (unsigned short)(v >> 16)));
+    }
+    static __device__ __forceinline__ uint32_t narrow(float2 v) {
+        return (uint32_t)__builtin_bit_cast(unsigned short, (T)v.x) |
+               (uint32_t)__builtin_bit_cast(unsigned short, (T)v.y) << 16;
+    }
+    static __device__ __forceinline__ float2 ld(Rsrc r, uint32_t vo, uint32_t so) {
+        return widen(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+    }
+    static __device__ __forceinline__ float2 ldnt(Rsrc r, uint32_t vo, uint32_t so) {
+        return widen(__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, kLoadNT));
+    }
+    static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
+        __builtin_amdgcn_raw_buffer_store_b32(narrow(v), r, vo, so, kStoreNT);
+    }
+    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
+        __builtin_amdgcn_raw_buffer_store_b32(narrow(v), r, vo, so, 0);
+    }
+};
 template <> struct Buf2<float> {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ float2 ld(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
     }
-};
-template <> struct Buf2<_Float16> {
-    static __device__ __forceinline__ float2 ld(Rsrc r, uint32_t vo, uint32_t so) {
-        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
-        return make_float2((float)__builtin_bit_cast(_Float16, (unsigned short)(v & 0xffffu)),
-                           (float)__builtin_bit_cast(_Float16, (unsigned short)(v >> 16)));
+    static __device__ __forceinline__ float2 ldnt(Rsrc r, uint32_t vo, uint32_t so) {
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, kLoadNT));
     }
-};
-template <> struct Buf2<__bf16> {
-    static __device__ __forceinline__ float2 ld(Rsrc r, uint32_t vo, uint32_t so) {
-        const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0);
-        return make_float2((float)__builtin_bit_cast(__bf16, (unsigned short)(v & 0xffffu)),
-                           (float)__builtin_bit_cast(__bf16, (unsigned short)(v >> 16)));
+    static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vo, so, kStoreNT);
+    }
+    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vo, so, 0);
     }
 };
 

@@ -16,7 +16,6 @@ constexpr int kMaxRec = 65536;  // receivers per shot with temporal blocking
 constexpr int kTimingClasses = 6;   // update, psi, record, exchange, band update, temporal block
 constexpr int kBandTX = BAND_TX, kBandZ = 32;   // band-kernel tile width and z chunk
 constexpr int kCUs = 256;   // compute units of an MI355X (the default z-march plan shares them)
-constexpr long kTileShot16 = 300000000;   // 16-bit shots below this many points take the tile kernels by default
 constexpr long kSmallShot = 150L * 150 * 150;   // a lone shot below this many points runs naive by default
 
 struct ShotH {
@@ -91,7 +90,7 @@ struct fdtd_ctx {
     size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0, o_tile_all = 0, o_tdesc = 0, o_fill = 0;
     int nwork_all = 0, nband_all = 0, ntile_all = 0, ninner_all = 0, nfill = 0;
     size_t o_inner_all = 0;
-    int inner_z = 0;          // planes of a box of k_inner; 0: k_tile takes every box
+    InnerBox inner;               // k_inner's boxes; z = 0: k_tile takes every box
     bool tile_nt = false;     // tile shots too large for any cache to hold a level from step to step
     size_t fill_max16 = 0;    // longest range of the reset's fill list
     int inc = -1;             // adjoint sweeps: the slot for a tile shot's increment (TileStep::inc)

@@ -36,7 +36,7 @@ struct TBArgsHost {
 };
 
 // the inner region's boxes of tile shots, iz planes deep (TileGrid::inner)
-void fdtd_launch_inner(int stor, int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
+void fdtd_launch_inner(int stor, InnerBox ib, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
                        const int *stepc, const TileDesc *one, hipStream_t st);
 
 // copy the ranges of a PackJob in one launch

@@ -365,7 +365,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     }
 }
 
-// Boxes of TX x TY x IZ points outside every band and wholly inside the grid
+// FP32 boxes of TX x TY x IZ points outside every band and wholly inside the grid
 // (TileItem flags: the shot only): u^{n+1} alone, from the box's column and an
 // LDS box with a 4-point halo along x and y.  Bound by HBM: 512^3 with 20-cell
 // layers, 97 M points in 336 us, 4.6 TB/s of the 16 bytes a point cannot do
@@ -374,44 +374,42 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
 // kernel leaves it, and 345 us on all.  Boxes of 8 planes hold 54 VGPRs and 20 KB
 // of LDS: eight blocks per CU, the memory's latency hidden by other blocks
 // instead of a register queue along z.
-template <typename T, int IZ, bool NT, bool INC, typename D>
+template <int IZ, bool INC, typename D>
 __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const TileStep &A,
                                           const int *__restrict__ stepc) {
     constexpr int F = FDTD_R, LW = TX + 2 * F, LH = TY + 2 * F, LP = LW * LH, XH = IZ / 4;
     __shared__ float U[IZ * LP];   // u^n at (x0 - 4 + c, y0 - 4 + r, z0 + p); corners unused
     const int t = (int)threadIdx.x, lx = t % TX, ly = t / TX;
-    const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0, P = s.P, esz = (int)sizeof(T);
+    const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0, P = s.P;
     const long base = (long)(s.fz + z0 - F) * s.S;   // descriptors based 4 planes before the box
-    const Rsrc ru = make_rsrc(s.u[A.iu] + base * esz), rw = make_rsrc(s.u[A.iu ^ 1] + base * esz);
-    const Rsrc rs = IsInc<T>::v ? make_rsrc(s.dinc + base * esz) : rw, rm = make_rsrc(s.m + base * 4);
-    const uint32_t Sb = (uint32_t)s.S * (uint32_t)esz, Smb = (uint32_t)s.S * 4u;
+    const Rsrc ru = make_rsrc(s.u[A.iu] + base * 4), rw = make_rsrc(s.u[A.iu ^ 1] + base * 4);
+    const Rsrc rm = make_rsrc(s.m + base * 4);
+    const uint32_t Sb = (uint32_t)s.S * 4u;
     // offsets of plane z0, and of the column (row y0 + ly, the row of the y halo, the x halo's place) in a plane
-    const uint32_t f0 = (uint32_t)(F * s.S + (s.fy + y0) * P + kFieldLead + x0);
-    const uint32_t fu = f0 * (uint32_t)esz, fm = f0 * 4u;
-    const uint32_t vc = (uint32_t)(ly * P + lx) * (uint32_t)esz, vm = (uint32_t)(ly * P + lx) * 4u;
+    const uint32_t fu = (uint32_t)(F * s.S + (s.fy + y0) * P + kFieldLead + x0) * 4u;
+    const uint32_t vc = (uint32_t)(ly * P + lx) * 4u;
     // (lane offsets are unsigned: halos are addressed from the box's first halo row or column)
-    const uint32_t vy = (uint32_t)((ly < F ? ly : ly + TY) * P + lx) * (uint32_t)esz;
-    const uint32_t fy = fu - (uint32_t)(F * P) * (uint32_t)esz;
+    const uint32_t vy = (uint32_t)((ly < F ? ly : ly + TY) * P + lx) * 4u;
+    const uint32_t fy = fu - (uint32_t)(F * P) * 4u;
     const int c8 = t & 7, hr = (t >> 3) & (TY - 1), hp = uniform(t >> 6);
-    const uint32_t vx = (uint32_t)(hr * P + (c8 < F ? c8 : c8 + TX)) * (uint32_t)esz;
-    const uint32_t fx = fu - (uint32_t)F * (uint32_t)esz + (uint32_t)hp * Sb;
+    const uint32_t vx = (uint32_t)(hr * P + (c8 < F ? c8 : c8 + TX)) * 4u;
+    const uint32_t fx = fu - (uint32_t)F * 4u + (uint32_t)hp * Sb;
     float q[IZ + 2 * F], hy[IZ], hx[XH], second[IZ], mm[IZ];
     {
         uint32_t so = fu - F * Sb;
 #pragma unroll
-        for (int o = 0; o < IZ + 2 * F; ++o, so += Sb) q[o] = Buf<T>::ld(ru, vc, so);
+        for (int o = 0; o < IZ + 2 * F; ++o, so += Sb) q[o] = Buf<float>::ld(ru, vc, so);
         so = fy;
 #pragma unroll
-        for (int p = 0; p < IZ; ++p, so += Sb) hy[p] = Buf<T>::ld(ru, vy, so);
+        for (int p = 0; p < IZ; ++p, so += Sb) hy[p] = Buf<float>::ld(ru, vy, so);
         so = fx;
 #pragma unroll
-        for (int p = 0; p < XH; ++p, so += 4 * Sb) hx[p] = Buf<T>::ld(ru, vx, so);
+        for (int p = 0; p < XH; ++p, so += 4 * Sb) hx[p] = Buf<float>::ld(ru, vx, so);
         so = fu;
-        uint32_t sm = fm;
 #pragma unroll
-        for (int p = 0; p < IZ; ++p, so += Sb, sm += Smb) {
-            second[p] = NT ? Buf<T>::ldnt(rs, vc, so) : Buf<T>::ld(rs, vc, so);
-            mm[p] = NT ? Buf<float>::ldnt(rm, vm, sm) : Buf<float>::ld(rm, vm, sm);
+        for (int p = 0; p < IZ; ++p, so += Sb) {
+            second[p] = Buf<float>::ldnt(rw, vc, so);
+            mm[p] = Buf<float>::ldnt(rm, vc, so);
         }
     }
     float *const Uc = U + (ly + F) * LW + lx + F;
@@ -438,7 +436,7 @@ __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const 
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
-    const Rsrc ri = INC ? make_rsrc(s.inc + A.inc * s.inc_slot + base * esz) : rw;
+    const Rsrc ri = INC ? make_rsrc(s.inc + A.inc * s.inc_slot + base * 4) : rw;
     uint32_t so = fu;
 #pragma unroll
     for (int p = 0; p < IZ; ++p, so += Sb) {
@@ -455,24 +453,130 @@ __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const 
         }
         const float lt = lap_interior(K, q[p + F], xl, xh, yl, yh, zl, zh);
         const bool src = again(src_box) && z0 + p == s.sz && x0 + lx == s.sx && y0 + ly == s.sy;
-        const Upd up = time_update<T>(mm[p], lt, q[p + F], second[p], src, srcamp);
-        if constexpr (NT) {
-            Buf<T>::st(rw, vc, so, up.u);
-            if constexpr (IsInc<T>::v) Buf<T>::st(rs, vc, so, up.d);
-        } else {
-            Buf<T>::stc(rw, vc, so, up.u);
-            if constexpr (IsInc<T>::v) Buf<T>::stc(rs, vc, so, up.d);
-        }
-        if constexpr (INC) Buf<T>::st(ri, vc, so, up.u - q[p + F]);
+        const Upd up = time_update<float>(mm[p], lt, q[p + F], second[p], src, srcamp);
+        Buf<float>::st(rw, vc, so, up.u);
+        if constexpr (INC) Buf<float>::st(ri, vc, so, up.u - q[p + F]);
     }
 }
-template <typename T, int IZ, bool ONE, bool NT, bool INC>
+// The same in 16-bit storage: boxes of 2 TX x TY x IZ points, two neighbours along x to
+// a lane.  With one point to a lane the kernel was bound by the instructions of its
+// 16-bit loads and stores, each half a line wide; a pair takes one access where two
+// points took two, and a row of the box is one whole line, which the non-temporal
+// stores need.  611 x 387 x 453 BF16, 16-cell layers: 68 M points in 280 us (boxes 32
+// wide) -> 178 us for 69 M (12 bytes a point: 4.6 TB/s); 768^3 FP16 332 M points in
+// 858 us.  94 VGPRs and 37 KB of LDS (FP32, read eight bytes at a time): four blocks per CU.
+template <typename T, int IZ, typename D>
+__device__ __forceinline__ void inner_pair(const D &s, const TileItem &wi, const TileStep &A,
+                                           const int *__restrict__ stepc) {
+    constexpr int F = FDTD_R, LW = 2 * TX + 2 * F, LH = TY + 2 * F, LP = LW * LH;
+    static_assert(IZ * TY * F == 256, "one x-halo pair per thread");
+    __shared__ float2 U[IZ * LP / 2];   // u^n at (x0 - 4 + c, y0 - 4 + r, z0 + p); corners unused
+    const int t = (int)threadIdx.x, lx = t % TX, ly = t / TX;
+    const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0, P = s.P, esz = (int)sizeof(T);
+    const long base = (long)(s.fz + z0 - F) * s.S;   // descriptors based 4 planes before the box
+    const Rsrc ru = make_rsrc(s.u[A.iu] + base * esz), rw = make_rsrc(s.u[A.iu ^ 1] + base * esz);
+    const Rsrc rs = make_rsrc(s.dinc + base * esz), rm = make_rsrc(s.m + base * 4);
+    const uint32_t Sb = (uint32_t)s.S * (uint32_t)esz, Smb = (uint32_t)s.S * 4u;
+    const uint32_t f0 = (uint32_t)(F * s.S + (s.fy + y0) * P + kFieldLead + x0);
+    const uint32_t fu = f0 * (uint32_t)esz, fm = f0 * 4u;
+    const uint32_t vc = (uint32_t)(ly * P + 2 * lx) * (uint32_t)esz, vm = 2u * vc;
+    const uint32_t vy = (uint32_t)((ly < F ? ly : ly + TY) * P + 2 * lx) * (uint32_t)esz;
+    const uint32_t fy = fu - (uint32_t)(F * P) * (uint32_t)esz;
+    // x halo: pair c4 of row hr of plane hp
+    const int c4 = t & 3, hr = (t >> 2) & (TY - 1), hp = t / (4 * TY), hc = c4 < 2 ? 2 * c4 : 2 * c4 + 2 * TX;
+    const uint32_t vx = (uint32_t)(hp * s.S + hr * P + hc) * (uint32_t)esz, fx = fu - (uint32_t)F * (uint32_t)esz;
+    float2 q[IZ + 2 * F], hy[IZ], hx, second[IZ], mm[IZ];
+    {
+        uint32_t so = fu - F * Sb;
+#pragma unroll
+        for (int o = 0; o < IZ + 2 * F; ++o, so += Sb) q[o] = Buf2<T>::ld(ru, vc, so);
+        so = fy;
+#pragma unroll
+        for (int p = 0; p < IZ; ++p, so += Sb) hy[p] = Buf2<T>::ld(ru, vy, so);
+        hx = Buf2<T>::ld(ru, vx, fx);
+        so = fu;
+        uint32_t sm = fm;
+#pragma unroll
+        for (int p = 0; p < IZ; ++p, so += Sb, sm += Smb) {
+            second[p] = Buf2<T>::ldnt(rs, vc, so);
+            mm[p] = Buf2<float>::ldnt(rm, vm, sm);
+        }
+    }
+    float2 *const Uc = U + ((ly + F) * LW + 2 * lx + F) / 2;
+    float2 *const Uy = U + ((ly < F ? ly : ly + TY) * LW + 2 * lx + F) / 2;
+#pragma unroll
+    for (int p = 0; p < IZ; ++p) {
+        Uc[p * LP / 2] = q[p + F];
+        Uy[p * LP / 2] = hy[p];
+    }
+    U[(hp * LP + (hr + F) * LW + hc) / 2] = hx;
+    __syncthreads();
+    const int src_box = uniform(s.sx >= x0 && s.sx < x0 + 2 * TX && s.sy >= y0 && s.sy < y0 + TY && s.sz >= z0 &&
+                                s.sz < z0 + IZ);
+    float srcamp = 0.0f;
+    if (src_box && s.wav != nullptr) {
+        const int n = *stepc + A.k;
+        if (n >= 0 && n < s.src_nt) srcamp = s.wav[n] * s.src_scale;
+    }
+    Coef K;
+    K.cc = s.cc;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
+    uint32_t so = fu;
+#pragma unroll
+    for (int p = 0; p < IZ; ++p, so += Sb) {
+        const float2 *c0 = Uc + p * LP / 2;
+        float xr[2 * F + 2];   // x - 4 .. x + 5
+        float2 yl[4], yh[4];
+#pragma unroll
+        for (int l = 0; l < F + 1; ++l) {
+            const float2 v = l == F / 2 ? q[p + F] : c0[l - F / 2];
+            xr[2 * l] = v.x;
+            xr[2 * l + 1] = v.y;
+        }
+#pragma unroll
+        for (int l = 1; l <= 4; ++l) {
+            yl[l - 1] = c0[-l * LW / 2];
+            yh[l - 1] = c0[l * LW / 2];
+        }
+        float2 un, dn;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            auto at = [&](const float2 &v) { return k ? v.y : v.x; };
+            float xl[4], xh[4], ya[4], yb[4], zl[4], zh[4];
+#pragma unroll
+            for (int l = 1; l <= 4; ++l) {
+                xl[l - 1] = xr[F + k - l];
+                xh[l - 1] = xr[F + k + l];
+                ya[l - 1] = at(yl[l - 1]);
+                yb[l - 1] = at(yh[l - 1]);
+                zl[l - 1] = at(q[p + F - l]);
+                zh[l - 1] = at(q[p + F + l]);
+            }
+            const float c = at(q[p + F]);
+            const float lt = lap_interior(K, c, xl, xh, ya, yb, zl, zh);
+            const bool src = again(src_box) && z0 + p == s.sz && x0 + 2 * lx + k == s.sx && y0 + ly == s.sy;
+            const Upd up = time_update<T>(at(mm[p]), lt, c, at(second[p]), src, srcamp);
+            (k ? un.y : un.x) = up.u;
+            (k ? dn.y : dn.x) = up.d;
+        }
+        Buf2<T>::st(rw, vc, so, un);
+        Buf2<T>::st(rs, vc, so, dn);
+    }
+}
+
+template <typename T, int IZ, bool ONE, bool INC>
 __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
                                                TileStep A, const int *__restrict__ stepc, const TileDesc one) {
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) inner_box<T, IZ, NT, INC>(one, wi, A, stepc);
-    else inner_box<T, IZ, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    if constexpr (IsInc<T>::v) {
+        if constexpr (ONE) inner_pair<T, IZ>(one, wi, A, stepc);
+        else inner_pair<T, IZ>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    } else if constexpr (ONE) inner_box<IZ, INC>(one, wi, A, stepc);
+    else inner_box<IZ, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
 }
 
 // ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
@@ -517,9 +621,9 @@ static void with_flags(bool one, bool nt, bool inc, F f) {
 template <typename T, int IZ>
 static void launch_inner_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
                            const TileDesc *one, hipStream_t st) {
-    with_flags<T>(one, A.nt, A.inc >= 0, [&](auto ONE, auto NT, auto INC) {
-        hipLaunchKernelGGL((k_inner<T, IZ, ONE.value, NT.value, INC.value>), dim3((unsigned)A.nwork), dim3(256), 0, st,
-                           d_descs, work, A, stepc, one ? *one : TileDesc{});
+    with_flags<T>(one, true, A.inc >= 0, [&](auto ONE, auto, auto INC) {
+        hipLaunchKernelGGL((k_inner<T, IZ, ONE.value, INC.value>), dim3((unsigned)A.nwork), dim3(256), 0, st, d_descs,
+                           work, A, stepc, one ? *one : TileDesc{});
     });
 }
 template <typename T>
@@ -539,11 +643,11 @@ void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs,
     else launch_tile_t<float>(d_shots, d_descs, work, A, nrec, stepc, one, st);
 }
 
-void fdtd_launch_inner(int stor, int iz, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
+void fdtd_launch_inner(int stor, InnerBox ib, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
                        const int *stepc, const TileDesc *one, hipStream_t st) {
     if (A.nwork <= 0) return;
     if (stor == 1) launch_inner_t<_Float16, 8>(d_descs, work, A, stepc, one, st);
     else if (stor == 2) launch_inner_t<__bf16, 8>(d_descs, work, A, stepc, one, st);
-    else if (iz == 16) launch_inner_t<float, 16>(d_descs, work, A, stepc, one, st);
+    else if (ib.z == 16) launch_inner_t<float, 16>(d_descs, work, A, stepc, one, st);
     else launch_inner_t<float, 8>(d_descs, work, A, stepc, one, st);
 }

@@ -18,15 +18,17 @@ struct TileGrid {
     size_t boxes() const {
         return (size_t)((n[0] + TILE_X - 1) / TILE_X) * ((n[1] + TILE_Y - 1) / TILE_Y) * ((n[2] + TILE_Z - 1) / TILE_Z);
     }
-    // the inner region for boxes iz planes deep: whole boxes inside the grid that meet no band; false if empty
-    bool inner(int iz, int r0[3], int r1[3]) const {
-        const int ext[3] = {TILE_X, TILE_Y, TILE_Z};
+    // the inner region for k_inner's boxes of ib.x x TILE_Y x ib.z points: whole boxes inside the grid that meet no
+    // band, first points on multiples of ib.x (16-bit stores of half a line are slow: 768^3 FP16 2090 -> 1645 us per
+    // step) and of k_tile's boxes; false if empty
+    bool inner(InnerBox ib, int r0[3], int r1[3]) const {
+        const int ext[3] = {ib.x, TILE_Y, TILE_Z};
         for (int d = 0; d < 3; ++d) {
             const int a = lo[d] > 0 ? lo[d] + FDTD_R : 0, b = hi[d] > 0 ? n[d] - hi[d] - FDTD_R : n[d];
             r0[d] = (a + ext[d] - 1) / ext[d] * ext[d];
             r1[d] = b / ext[d] * ext[d];
         }
-        r1[2] = r0[2] + (r1[2] - r0[2]) / iz * iz;
+        r1[2] = r0[2] + (r1[2] - r0[2]) / ib.z * ib.z;
         return r0[0] < r1[0] && r0[1] < r1[1] && r0[2] < r1[2];
     }
 };
@@ -73,12 +75,13 @@ inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], con
 
 // The boxes of several grids in launch order: each brick goes to the XCD with the least work so far (workgroup
 // b runs on XCD b mod 8); a box costs 4 and 3 more for each axis whose band it meets, about its instruction
-// count.  iz = 0: every box, TILE_Z planes deep; iz > 0 with `inner`: the inner region's boxes, iz planes deep,
-// or without: the boxes of the rest.
-inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, int iz = 0, bool inner = false) {
-    if (inner && iz == 0) return {};
+// count.  ib.z = 0: every box, TILE_Z planes deep; ib.z > 0 with `inner`: the inner region's boxes, or without:
+// the boxes of the rest.
+inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, InnerBox ib = {}, bool inner = false) {
+    if (inner && ib.z == 0) return {};
+    const int ext[3] = {inner ? ib.x : TILE_X, TILE_Y, inner ? ib.z : TILE_Z}, zero[3] = {0, 0, 0};
     size_t all = 0;
-    for (const TileGrid &g : grids) all += g.boxes() * TILE_Z / (inner ? iz : TILE_Z);
+    for (const TileGrid &g : grids) all += g.boxes() * TILE_X * TILE_Z / (ext[0] * ext[2]);
     size_t want = 8;   // a power of two, at least 24 bricks (three per XCD) where there are so many boxes
     while (want < kTileBrick && 2 * want <= all / 24) want *= 2;
     std::vector<TileItem> v;
@@ -86,9 +89,8 @@ inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, int i
     v.reserve(all);
     brick.reserve(all);
     for (const TileGrid &g : grids) {
-        const int ext[3] = {TILE_X, TILE_Y, inner ? iz : TILE_Z}, zero[3] = {0, 0, 0};
         int r0[3], r1[3];
-        const bool has = iz > 0 && g.inner(iz, r0, r1);
+        const bool has = ib.z > 0 && g.inner(ib, r0, r1);
         if (inner && has) tile_boxes(g, ext, r0, r1, nullptr, nullptr, want, v, brick);
         if (!inner) tile_boxes(g, ext, zero, g.n, has ? r0 : nullptr, r1, want, v, brick);
     }

@@ -123,6 +123,23 @@ def test_inner_launch_equals_naive(case, storage):
     _same(*got)
 
 
+# 1.6e7 points or more, where 16-bit storage takes it too: boxes of two points to a lane; regions of a few boxes, of one
+# along x, at the grid's edge, and none
+LARGE16 = [
+    ((283, 243, 237), (10, 12, 9, 20, 15, 11)),
+    ((256, 256, 257), (0, 20, 20, 0, 0, 20)),
+    ((320, 229, 230), (0,) * 6),
+    ((160, 170, 640), (20, 20, 70, 70, 20, 20)),
+    ((129, 250, 512), (20, 2, 20, 20, 20, 20)),
+]
+
+
+@pytest.mark.parametrize("storage", [1, 2])
+@pytest.mark.parametrize("case", LARGE16, ids=lambda c: "x".join(map(str, c[0])))
+def test_inner_launch_of_pairs_equals_naive(case, storage):
+    test_inner_launch_equals_naive(case, storage)
+
+
 def test_inner_launch_in_a_batch_and_of_16_planes():
     """Two shots that reach the size together, eager and as a graph, and one large enough for boxes of 16 planes."""
     for cases, graphs in (([((180, 190, 200), (15,) * 6), ((200, 170, 180), (15, 10, 0, 9, 20, 15))], (False, True)),

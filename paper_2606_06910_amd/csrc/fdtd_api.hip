@@ -301,7 +301,7 @@ static bool tile_rule(const ShotH &s) {
 // 512^3 650 / 617 / 613, 768^3 - / 1908 / 1887.  In 16-bit storage the boxes are 64
 // points wide, two to a lane (whole lines; 32 wide 512^3 took 640 us, the 64 wide
 // ones 586), and leave more of a small grid to k_tile: FP16 without / with, 232^3 75 /
-// 79, 256^3 114 / 106, 300^3 - / 166.  The hint, once the shots outgrow the
+// 79, 256^3 114 / 106, 300^3 - / 166; and k_face is used.  The hint, once the shots outgrow the
 // 256 MiB last-level cache: FP32 200^3 52.9 -> 59.9, 256^3 108.5 -> 105.5, 512^3 640
 // -> 617; not in 16-bit storage, where a row of k_tile's box is half a line and its
 // stores have to meet their other half in L2 (512^3 640 -> 687).
@@ -309,6 +309,7 @@ static void tile_plan(long points, int storage, InnerBox &inner, bool &nt) {
     const bool large = points >= (storage == FDTD_F32 ? 12000000 : 16000000);
     inner.x = storage == FDTD_F32 ? TILE_X : 2 * TILE_X;
     inner.z = !large ? 0 : (storage == FDTD_F32 && points >= 100000000 ? 16 : 8);
+    inner.face = large && storage != FDTD_F32;
     nt = large && storage == FDTD_F32;
 }
 static size_t tile_capacity(const ShotH &s) {
@@ -743,7 +744,7 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         any_plain = any_plain || !s.tile;
         any_tile = any_tile || s.tile;
     }
-    // tile shots: their whole step in one launch; its extra blocks record the step
+    // tile shots: their whole step in one launch (three on large grids); extra blocks of k_tile record the step
     // before while no record launch has come in between (pend steps)
     if (any_tile) {
         int nrec = 0;
@@ -752,19 +753,25 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc), *one = hi - lo == 1 ? &ctx->htile[lo] : nullptr;
         const ShotH &s0 = ctx->shots[lo];
         const bool all = shot < 0 || ctx->shots.size() == 1;
-        TileStep A{R.iu, ctx->pend, all ? ctx->ninner_all : s0.ninner, lo, ctx->tile_nt, ctx->inc};
+        TileStep A{R.iu, ctx->pend, 0, lo, ctx->tile_nt, ctx->inc};
+        auto part = [&](int k) {
+            A.nwork = all ? ctx->npart_all[k] : s0.npart[k];
+            return (const TileItem *)wsp(ctx, all ? ctx->o_part_all[k] : s0.o_part[k]);
+        };
         hipEvent_t t0 = tic(ctx);
-        fdtd_launch_inner(stor, ctx->inner, descs, (const TileItem *)wsp(ctx, all ? ctx->o_inner_all : s0.o_inner),
-                          A, stepc, one, ctx->stream);
-        if (A.nwork > 0) {
+        if (ctx->inner.z > 0) {
+            const TileItem *w = part(TILE_INNER);
+            fdtd_launch_inner(stor, ctx->inner, descs, w, A, stepc, one, ctx->stream);
             toc(ctx, 0, t0);
             t0 = tic(ctx);
         }
-        const int cls = A.nwork > 0 ? 4 : 0;
-        A.nwork = all ? ctx->ntile_all : s0.ntile;
-        fdtd_launch_tile(stor, dd, descs, (const TileItem *)wsp(ctx, all ? ctx->o_tile_all : s0.o_tile), A, nrec,
-                         stepc, one, ctx->stream);
-        toc(ctx, cls, t0);
+        if (ctx->inner.face) {
+            const TileItem *w = part(TILE_FACES);
+            fdtd_launch_face(stor, descs, w, A, stepc, one, ctx->stream);
+        }
+        const TileItem *w = part(TILE_EDGES);
+        fdtd_launch_tile(stor, dd, descs, w, A, nrec, stepc, one, ctx->stream);
+        toc(ctx, ctx->inner.z > 0 ? 4 : 0, t0);
     }
     if (!any_plain) return;
     hipStream_t side = ctx->stream;
@@ -1039,6 +1046,10 @@ static void save_checkpoint(fdtd_ctx *ctx, int i, int k) {
     fdtd_launch_pack(j, ctx->stream);
 }
 
+static bool has_part(const fdtd_ctx *ctx, int k) {
+    return k == TILE_INNER ? ctx->inner.z > 0 : (k == TILE_EDGES || ctx->inner.face);
+}
+
 // workspace layout
 static void layout(fdtd_ctx *ctx) {
     const size_t nshots = ctx->shots.size();
@@ -1087,12 +1098,11 @@ static void layout(fdtd_ctx *ctx) {
     size_t tile_all = 0;
     for (auto &s : ctx->shots) {
         const size_t own = nshots > 1 ? sizeof(TileItem) * tile_capacity(s) : 0;
-        s.o_tile = take(own);
-        s.o_inner = take(ctx->inner.z > 0 ? own : 0);
+        for (int k = 0; k < 3; ++k) s.o_part[k] = take(has_part(ctx, k) ? own : 0);
         tile_all += tile_capacity(s);
     }
-    ctx->o_tile_all = take(sizeof(TileItem) * tile_all);
-    ctx->o_inner_all = take(ctx->inner.z > 0 ? sizeof(TileItem) * tile_all : 0);
+    for (int k = 0; k < 3; ++k)
+        ctx->o_part_all[k] = take(has_part(ctx, k) ? sizeof(TileItem) * tile_all : 0);
     ctx->need = off;
 }
 
@@ -1232,16 +1242,16 @@ static int write_work_lists(fdtd_ctx *ctx) {
     int rc;
     for (size_t i = 0; i < ctx->shots.size(); ++i) {
         ShotH &s = ctx->shots[i];
-        s.nband = s.nwork = s.ntbwork = s.ntile = s.ninner = 0;
+        s.nband = s.nwork = s.ntbwork = 0;
         if (s.tile) {
             const TileGrid g = fdtd_tile_grid(s, (int)i);
             if (ctx->shots.size() > 1) {   // (a lone shot's lists are those of all shots)
-                const std::vector<TileItem> w = tile_list({g}, ctx->inner), in = tile_list({g}, ctx->inner, true);
-                if (w.size() > tile_capacity(s) || in.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
-                s.ntile = (int)w.size();
-                s.ninner = (int)in.size();
-                if ((rc = upload(s.o_tile, w.data(), sizeof(TileItem) * w.size()))) return rc;
-                if ((rc = upload(s.o_inner, in.data(), sizeof(TileItem) * in.size()))) return rc;
+                for (int k = 0; k < 3; ++k) {
+                    const std::vector<TileItem> w = tile_list({g}, ctx->inner, (TilePart)k);
+                    if (w.size() > tile_capacity(s)) FAIL(ctx, FDTD_EINVAL, "box list overflow");
+                    s.npart[k] = (int)w.size();
+                    if ((rc = upload(s.o_part[k], w.data(), sizeof(TileItem) * w.size()))) return rc;
+                }
             }
             tile_all.push_back(g);
             continue;
@@ -1279,12 +1289,11 @@ static int write_work_lists(fdtd_ctx *ctx) {
     const std::vector<BandItem> bw = xcd_order(band_all);
     ctx->nband_all = (int)bw.size();
     if ((rc = upload(ctx->o_band_all, bw.data(), sizeof(BandItem) * bw.size()))) return rc;
-    const std::vector<TileItem> tw = tile_list(tile_all, ctx->inner);
-    ctx->ntile_all = (int)tw.size();
-    if ((rc = upload(ctx->o_tile_all, tw.data(), sizeof(TileItem) * tw.size()))) return rc;
-    const std::vector<TileItem> in = tile_list(tile_all, ctx->inner, true);
-    ctx->ninner_all = (int)in.size();
-    if ((rc = upload(ctx->o_inner_all, in.data(), sizeof(TileItem) * in.size()))) return rc;
+    for (int k = 0; k < 3; ++k) {
+        const std::vector<TileItem> w = tile_list(tile_all, ctx->inner, (TilePart)k);
+        ctx->npart_all[k] = (int)w.size();
+        if ((rc = upload(ctx->o_part_all[k], w.data(), sizeof(TileItem) * w.size()))) return rc;
+    }
     rc = upload(ctx->o_work_all, all.data(), sizeof(WorkItem) * all.size());
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return rc;

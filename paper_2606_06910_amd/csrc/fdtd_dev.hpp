@@ -162,9 +162,11 @@ struct TileStep {
     int iu, k, nwork, rec_lo, nt;
     int inc = -1;   // >= 0: u^{n+1} - u^n goes to this slot of TileDesc::inc, laid out as the field
 };
-// Extents of k_inner's boxes (x, TILE_Y, z); z = 0: none, k_tile takes every box.
+// Extents of k_inner's boxes (x, TILE_Y, z; z = 0: none, k_tile takes every box) and
+// whether k_face takes those others that meet one band at most.
 struct InnerBox {
     int x = TILE_X, z = 0;
+    bool face = false;
 };
 // Up to 8 ranges copied one after another to dst, each starting on a multiple of 256 bytes there.
 struct PackJob {

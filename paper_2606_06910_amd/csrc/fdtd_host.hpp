@@ -36,8 +36,8 @@ struct ShotH {
     size_t o_u[4] = {0, 0, 0, 0}, o_d = 0, o_m = 0, o_psi[3] = {0, 0, 0}, o_zeta[3] = {0, 0, 0}, o_prof = 0;
     // tile shots (k_tile does the whole step): the other psi buffers and the box list
     bool tile = false;
-    size_t o_psi2[3] = {0, 0, 0}, o_tile = 0, o_inner = 0;
-    int ntile = 0, ninner = 0;
+    size_t o_psi2[3] = {0, 0, 0}, o_part[3] = {0, 0, 0};   // (o_part: box lists, by TilePart)
+    int npart[3] = {0, 0, 0};
     size_t o_work = 0, o_xbuf = 0, xbuf_bytes = 0;
     size_t o_jobs[2][4] = {};
     int njobs[2][4] = {};
@@ -87,9 +87,10 @@ struct fdtd_ctx {
     bool single_stream = false;         // never create the side stream (everything on `stream`)
     char *ws = nullptr;
     size_t ws_bytes = 0, need = 0;
-    size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0, o_tile_all = 0, o_tdesc = 0, o_fill = 0;
-    int nwork_all = 0, nband_all = 0, ntile_all = 0, ninner_all = 0, nfill = 0;
-    size_t o_inner_all = 0;
+    size_t o_stepc = 0, o_scratch = 0, o_desc = 0, o_work_all = 0, o_band_all = 0, o_tdesc = 0, o_fill = 0;
+    int nwork_all = 0, nband_all = 0, nfill = 0;
+    size_t o_part_all[3] = {0, 0, 0};   // the tile shots' box lists, by TilePart
+    int npart_all[3] = {0, 0, 0};
     InnerBox inner;               // k_inner's boxes; z = 0: k_tile takes every box
     bool tile_nt = false;     // tile shots too large for any cache to hold a level from step to step
     size_t fill_max16 = 0;    // longest range of the reset's fill list

@@ -41,6 +41,10 @@ void fdtd_launch_inner(int stor, InnerBox ib, const TileDesc *d_descs, const Til
 
 // copy the ranges of a PackJob in one launch
 void fdtd_launch_pack(const PackJob &j, hipStream_t st);
+// their other boxes that meet one band at most
+void fdtd_launch_face(int stor, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
+                      const TileDesc *one, hipStream_t st);
+
 void fdtd_launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 // zero every range of a device-resident FillJob list in one launch; max_n16 = longest range
 void fdtd_launch_fill_jobs(const void *jobs, int njobs, size_t max_n16, hipStream_t st);

@@ -1,6 +1,7 @@
 // kernels_tile.hip -- one leapfrog step of a shot in one launch (k_tile), or on
-// large grids two: k_inner for the boxes outside every band, k_tile for the rest
-// (gfx950).
+// large grids two or three: k_inner for the boxes outside every band, in 16-bit
+// storage k_face for the other boxes that meet one band at most, k_tile for the
+// rest (gfx950).
 //
 // A block of k_tile owns a box of TILE_X x TILE_Y x TILE_Z points, inside or outside the
 // layers, and does the whole step there: psi, zeta and u^{n+1} (paper, section
@@ -36,15 +37,17 @@ constexpr int UW = TX + 4 * FDTD_R, UH = TY + 4 * FDTD_R;   // LDS plane of u^n:
 constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, new psi_y columns: 4 on each side
 // the descriptors read as constant memory: no store of the kernel changes them, so they may be loaded at once
 typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
+constexpr int AX_ANY = TILE_XB | TILE_YB | TILE_ZB;
 }  // namespace
 
 // one box (D: TileDesc in the constant or the kernel-argument address space).  INC: the
 // increment u^{n+1} - u^n is stored too (an adjoint sweep keeps it), 4 bytes per
 // point here against 12 in a pass of its own; a template flag, because as a test in
-// the kernel it cost plain steps 1 % (160^3).
-template <typename T, bool NT, bool INC, typename D>
+// the kernel it cost plain steps 1 % (160^3).  AX: the axes whose band the box meets
+// (TILE_XB etc.), or AX_ANY, where the item says which.
+template <typename T, int AX, bool NT, bool INC, typename D>
 __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const TileStep &A,
-                                         const int *__restrict__ stepc) {
+                                         const int *__restrict__ stepc, float *lds) {
     const int t = (int)threadIdx.x;
     const int nx = s.nx, ny = s.ny, nz = s.nz;
     const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0;
@@ -53,11 +56,15 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     const bool act = x < nx && y < ny;
     const int xlo = s.Llo[0], xhi = s.Lhi[0], ylo = s.Llo[1], yhi = s.Lhi[1], zlo = s.Llo[2], zhi = s.Lhi[2];
     // axes whose band the box meets: only these need psi, zeta and the wider u^n halo
-    const int xb = wi.flags & TILE_XB, yb = wi.flags & TILE_YB, zb = wi.flags & TILE_ZB;
+    const int axes = AX == AX_ANY ? wi.flags : AX;
+    const int xb = axes & TILE_XB, yb = axes & TILE_YB, zb = axes & TILE_ZB;
+    auto on = [](int b) { return AX == AX_ANY ? again(b) : b; };
 
-    __shared__ float U[TZ][UH][UW];     // u^n at (x0 - 8 + c, y0 - 8 + r, z0 + p); corners unused
-    __shared__ float PX[TZ][TY][PXW];   // new psi_x at (x0 - 4 + c, y0 + r, z0 + p), 0 outside the slabs
-    __shared__ float PY[TZ][PYH][TX];   // new psi_y at (x0 + c, y0 - 4 + r, z0 + p)
+    // u^n at (x0 - 8 + c, y0 - 8 + r, z0 + p), corners unused; new psi_x at (x0 - 4 + c, y0 + r, z0 + p) and new psi_y
+    // at (x0 + c, y0 - 4 + r, z0 + p), 0 outside the slabs (one place for both where a box has one of them at most)
+    auto U = (float (*)[UH][UW])lds;
+    auto PX = (float (*)[TY][PXW])(lds + TZ * UH * UW);
+    auto PY = (float (*)[PYH][TX])(lds + TZ * UH * UW + (AX == AX_ANY ? TZ * TY * PXW : 0));
 
     // One descriptor per field, based 8 planes before the box, and one for the layer arrays and profiles (32-bit
     // offsets reach them all, the tile rule sees to it): position at a lane offset, plane by plane a running
@@ -223,8 +230,8 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     }
     const int cn = c8 < FDTD_R ? c8 : c8 + TX;   // column of xn in PX
     U[hp][hr + 8][cn + 4] = hxn;
-    if (again(xb)) U[hp][hr + 8][c8 < FDTD_R ? cn : cn + 8] = hxf;
-    if (again(yb)) {
+    if (on(xb)) U[hp][hr + 8][c8 < FDTD_R ? cn : cn + 8] = hxf;
+    if (on(yb)) {
 #pragma unroll
         for (int p = 0; p < TZ; ++p) U[p][ly < FDTD_R ? rn : rn + 8][lx + 8] = hyf[p];
     }
@@ -237,7 +244,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int l = 0; l < 5; ++l) w1[d][l] = s.w1[d][l];
-    if (again(xb)) {
+    if (on(xb)) {
         const int n1 = again(np);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) {
@@ -249,7 +256,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         const float v = psi_update(ahx[0], pxh, ahx[1], d1_lds(&U[hp][hr + 8][cn + 4], 1, w1[0]));
         PX[hp][hr][cn] = hsx ? v : 0.0f;
     }
-    if (again(yb)) {
+    if (on(yb)) {
         const int n1 = again(np);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) {
@@ -261,7 +268,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
             if (p < n1) Buf<float>::stc(rl, vy, ypn + p * Spy, v);
         }
     }
-    if (again(zb)) {
+    if (on(zb)) {
         const uint32_t z1 = (uint32_t)again((int)zm);
 #pragma unroll
         for (int o = 0; o < PN; ++o)
@@ -285,7 +292,7 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
     for (int d = 0; d < 3; ++d)
 #pragma unroll
         for (int l = 0; l < 5; ++l) K.w2[d][l] = s.w2[d][l];
-    if (again(xb | yb)) __syncthreads();
+    if (on(xb | yb)) __syncthreads();
 
     // ---- the update ----
     const Rsrc rw = make_rsrc(s.u[A.iu ^ 1] + base * esz), rs = IsInc<T>::v ? make_rsrc(s.dinc + base * esz) : rw;
@@ -313,19 +320,19 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
         }
         const float c = q[p + 8];
         float lt;
-        if (!again(xb | yb | zb)) {
+        if (!on(xb | yb | zb)) {
             lt = lap_interior(K, c, xl, xh, yl, yh, zl, zh);
         } else {
             const bool bz = zb && in_band(again(z0 + p), nz, zlo, zhi);
             float L[3] = {d2_axis(K.w2[0], c, xl, xh), d2_axis(K.w2[1], c, yl, yh), d2_axis(K.w2[2], c, zl, zh)};
-            if (again(xb)) {
+            if (on(xb)) {
                 float zn = 0.0f;
                 const float e = cpml_axis(L[0], dx[p], d1_lds(&PX[p][ly][lx + 4], 1, w1[0]), ax[2],
                                           ax[3], ax[1], ax[0], sx, zx[p], &zn);
                 if (bx) L[0] = e;
                 Buf<float>::stc(rl, vx, xze + p * Spx, zn);
             }
-            if (again(yb)) {
+            if (on(yb)) {
                 float zn = 0.0f;
                 const float e = cpml_axis(L[1], dy[p], d1_lds(&PY[p][ly + 4][lx], TX, w1[1]), ay[2],
                                           ay[3], ay[1], ay[0], sy, zy[p], &zn);
@@ -581,10 +588,36 @@ __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ desc
 
 // ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
 // before the box's own)
+// Boxes that meet one band at most, in 16-bit storage: tile_box built for each case
+// holds 79 VGPRs and 27 KB of LDS where the build for any box holds 116 and 31, so
+// six blocks share a CU and not four.  In 16-bit storage k_tile is bound by latency
+// and instruction issue, and that pays: 768^3 FP16 35.9 -> 34.9 ms for 20 steps, 611 x
+// 387 x 453 BF16 20.4 -> 19.8 ms for 40.  In FP32 it does not (512^3 283 us for k_tile
+// alone, 227 + 56 for both; 24 batched shots 864, 544 + 337): its boxes already move
+// 4.5 to 5 TB/s, counted, at four blocks per CU.
+template <typename T, typename D>
+__device__ __forceinline__ void face_box(const D &s, const TileItem &wi, const TileStep &A,
+                                         const int *__restrict__ stepc, float *lds) {
+    const int ax = uniform(wi.flags & AX_ANY);
+    if (ax == 0) tile_box<T, 0, false, false>(s, wi, A, stepc, lds);
+    else if (ax == TILE_XB) tile_box<T, TILE_XB, false, false>(s, wi, A, stepc, lds);
+    else if (ax == TILE_YB) tile_box<T, TILE_YB, false, false>(s, wi, A, stepc, lds);
+    else tile_box<T, TILE_ZB, false, false>(s, wi, A, stepc, lds);
+}
+template <typename T, bool ONE>
+__global__ __launch_bounds__(256, 6) void k_face(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
+                                                 TileStep A, const int *__restrict__ stepc, const TileDesc one) {
+    __shared__ float lds[TZ * UH * UW + TZ * PYH * TX];
+    const TileItem wi = work[blockIdx.x];
+    if (wi.flags < 0) return;   // the idle items that pad the list
+    if constexpr (ONE) face_box<T>(one, wi, A, stepc, lds);
+    else face_box<T>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc, lds);
+}
 template <typename T, bool ONE, bool NT, bool INC>
 __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ shots, const TileDesc *__restrict__ descs,
                                                  const TileItem *__restrict__ work, TileStep A,
                                                  const int *__restrict__ stepc, const TileDesc one) {
+    __shared__ float lds[TZ * UH * UW + TZ * TY * PXW + TZ * PYH * TX];
     const int t = (int)threadIdx.x;
     if ((int)blockIdx.x >= A.nwork) {
         // receivers of the step before this one (the newest level is complete now)
@@ -601,8 +634,8 @@ __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ sho
     }
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) tile_box<T, NT, INC>(one, wi, A, stepc);
-    else tile_box<T, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    if constexpr (ONE) tile_box<T, AX_ANY, NT, INC>(one, wi, A, stepc, lds);
+    else tile_box<T, AX_ANY, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc, lds);
 }
 
 // launch f(ONE, NT, INC as std::bool_constant); only FP32 fields have increments
@@ -635,9 +668,23 @@ static void launch_tile_t(const DevShot *d_shots, const TileDesc *d_descs, const
     });
 }
 
+template <typename T>
+static void launch_face_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
+                          const TileDesc *one, hipStream_t st) {
+    const dim3 grid((unsigned)A.nwork);
+    if (one) hipLaunchKernelGGL((k_face<T, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
+    else hipLaunchKernelGGL((k_face<T, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
+}
+void fdtd_launch_face(int stor, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
+                      const TileDesc *one, hipStream_t st) {
+    if (A.nwork <= 0) return;
+    if (stor == 1) launch_face_t<_Float16>(d_descs, work, A, stepc, one, st);
+    else launch_face_t<__bf16>(d_descs, work, A, stepc, one, st);
+}
+
 void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
                       const TileStep &A, int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
-    if (A.nwork <= 0) return;
+    if (A.nwork + nrec <= 0) return;
     if (stor == 1) launch_tile_t<_Float16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
     else if (stor == 2) launch_tile_t<__bf16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
     else launch_tile_t<float>(d_shots, d_descs, work, A, nrec, stepc, one, st);

@@ -12,6 +12,9 @@
 constexpr size_t kTileBrick = 256;
 constexpr size_t kTileAhead = 1024;  // boxes one XCD's list may be ahead of another's
 
+// The boxes of one launch: those of the inner region (k_inner), the others that meet one band at most (k_face) and
+// the rest (k_tile).
+enum TilePart { TILE_INNER, TILE_FACES, TILE_EDGES };
 // One grid's boxes: its size, its layers, the number its items carry.
 struct TileGrid {
     int n[3], lo[3], hi[3], shot;
@@ -40,7 +43,8 @@ struct TileGrid {
 // is [r0, r1) in boxes of ext points, less the inner region [x0, x1) where given; `brick` receives each box's
 // brick number, and each box is marked with the axes whose band (layer and 4 points) it meets.
 inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], const int r1[3], const int *x0,
-                       const int *x1, size_t want, std::vector<TileItem> &v, std::vector<int> &brick) {
+                       const int *x1, TilePart part, size_t want, std::vector<TileItem> &v,
+                       std::vector<int> &brick) {
     const int wt[3] = {8, 1, 1};
     int nb[3], b[3] = {1, 1, 1};
     for (int d = 0; d < 3; ++d) nb[d] = (r1[d] - r0[d] + ext[d] - 1) / ext[d];
@@ -66,8 +70,11 @@ inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], con
                             bool skip = x0 != nullptr;
                             for (int d = 0; skip && d < 3; ++d) skip = c[d] >= x0[d] && c[d] < x1[d];
                             if (skip) continue;
-                            v.push_back(TileItem{g.shot | (meets(0, c[0]) ? TILE_XB : 0) |
-                                                     (meets(1, c[1]) ? TILE_YB : 0) | (meets(2, c[2]) ? TILE_ZB : 0),
+                            const bool m[3] = {meets(0, c[0]), meets(1, c[1]), meets(2, c[2])};
+                            const bool edge = m[0] + m[1] + m[2] > 1;
+                            if ((part == TILE_FACES && edge) || (part == TILE_EDGES && !edge)) continue;
+                            v.push_back(TileItem{g.shot | (m[0] ? TILE_XB : 0) | (m[1] ? TILE_YB : 0) |
+                                                     (m[2] ? TILE_ZB : 0),
                                                  c[0], c[1], c[2]});
                             brick.push_back(id);
                         }
@@ -75,10 +82,10 @@ inline void tile_boxes(const TileGrid &g, const int ext[3], const int r0[3], con
 
 // The boxes of several grids in launch order: each brick goes to the XCD with the least work so far (workgroup
 // b runs on XCD b mod 8); a box costs 4 and 3 more for each axis whose band it meets, about its instruction
-// count.  ib.z = 0: every box, TILE_Z planes deep; ib.z > 0 with `inner`: the inner region's boxes, or without:
-// the boxes of the rest.
-inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, InnerBox ib = {}, bool inner = false) {
-    if (inner && ib.z == 0) return {};
+// count.  A part that has no launch of its own is empty, its boxes in the next.
+inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, InnerBox ib = {}, TilePart part = TILE_EDGES) {
+    if ((part == TILE_INNER && ib.z == 0) || (part == TILE_FACES && !ib.face)) return {};
+    const bool inner = part == TILE_INNER;
     const int ext[3] = {inner ? ib.x : TILE_X, TILE_Y, inner ? ib.z : TILE_Z}, zero[3] = {0, 0, 0};
     size_t all = 0;
     for (const TileGrid &g : grids) all += g.boxes() * TILE_X * TILE_Z / (ext[0] * ext[2]);
@@ -91,8 +98,9 @@ inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, Inner
     for (const TileGrid &g : grids) {
         int r0[3], r1[3];
         const bool has = ib.z > 0 && g.inner(ib, r0, r1);
-        if (inner && has) tile_boxes(g, ext, r0, r1, nullptr, nullptr, want, v, brick);
-        if (!inner) tile_boxes(g, ext, zero, g.n, has ? r0 : nullptr, r1, want, v, brick);
+        // (TILE_INNER: no box is left out)
+        if (inner && has) tile_boxes(g, ext, r0, r1, nullptr, nullptr, part, want, v, brick);
+        if (!inner) tile_boxes(g, ext, zero, g.n, has ? r0 : nullptr, r1, ib.face ? part : TILE_INNER, want, v, brick);
     }
     std::vector<TileItem> seq[8];
     long cost[8] = {};
@@ -118,4 +126,4 @@ inline std::vector<TileItem> tile_list(const std::vector<TileGrid> &grids, Inner
     return out;
 }
 // most items tile_list can give for grids of so many boxes in all (a brick holds less than 2 kTileBrick)
-inline size_t tile_list_bound(size_t boxes) { return boxes + 8 * (kTileAhead + 2 * kTileBrick); }
+inline size_t tile_list_bound(size_t boxes) { return boxes + 8 * std::min(kTileAhead + 2 * kTileBrick, boxes); }

@@ -8,13 +8,17 @@
 // and step from memory) and a step is one launch instead of two.  Operation for
 // operation the two stages' arithmetic, so the bits are theirs.
 //
+// On large grids the boxes out of every layer's reach and inside the grid by their
+// halo take a launch of their own, built without layers and edges (IN: 67 VGPRs
+// instead of 108, five blocks per CU instead of four).
+//
 // What bounds it: on small grids the chain of one block, as in k_tile; on large
-// ones the halos' traffic (544^3: 5.8 GB read and 2.9 GB written per step, 5.2
-// TB/s; the step cannot do without 6 GB) and 142 VALU instructions per plane of
-// 64 points.  108 VGPRs, 31 KB of LDS: four blocks per CU.  Before (two stages,
-// one thread per point below 256^3, z-marching above) and after, us per step:
-// 64^3 13.1 -> 9.3, 96^3 26 -> 16, 131 x 118 x 97 41 -> 26, 256^3 297 -> 204,
-// 384^3 729 -> 594, 544^3 1921 -> 1668, 640^3 2948 -> 2893.
+// ones the halos' traffic (544^3: 4.3 GB read and 2.9 GB written per step, counted,
+// 4.7 TB/s; the step cannot do without 5.8 GB; the interior's 118 M points take 950
+// us, the other 43 M 565) and 142 VALU instructions per plane of 64 points.
+// 31 KB of LDS.  Before (two stages, one thread per point below 256^3, z-marching
+// above) and after, us per step: 64^3 13.1 -> 9.3, 96^3 26 -> 16, 131 x 118 x 97 41
+// -> 25, 256^3 297 -> 207, 384^3 729 -> 569, 544^3 1921 -> 1508, 640^3 2948 -> 2463.
 #include "pv_tile.hpp"
 #include "tile_dev.hpp"
 
@@ -32,11 +36,11 @@ template <bool NT> __device__ __forceinline__ float once(Rsrc r, uint32_t vo, ui
 }  // namespace
 
 // NT: the non-temporal hint on every store and on the loads of psi_p, on grids that no cache holds from one
-// step to the next
-template <bool NT>
-__global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileItem *__restrict__ work) {
+// step to the next; IN: boxes whose p halo lies in the frame and v halo in the grid, away from every layer
+template <bool NT, bool IN>
+__global__ __launch_bounds__(256, IN ? 5 : 4) void k_pv_tile(const PvTile g, const TileItem *__restrict__ work) {
     const int t = (int)threadIdx.x;
-    if ((int)blockIdx.x >= g.nwork) {
+    if (!IN && (int)blockIdx.x >= g.nwork) {
         // receivers of the step before this one
         const float *p = g.in[0] + kFieldLead + 4 * (long)g.S + 4 * (long)g.P;
         for (int r = ((int)blockIdx.x - g.nwork) * 256 + t; r < g.nrec; r += 256 * ((int)gridDim.x - g.nwork))
@@ -49,10 +53,12 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     const int x0 = wi.x0, y0 = wi.y0, z0 = wi.z0;
     const int lx = t % TX, ly = t / TX;
     const int x = x0 + lx, y = y0 + ly;
-    const bool act = x < nx && y < ny;
+    const bool act = IN || (x < nx && y < ny);
     const int xlo = g.lo[0], xhi = g.hi[0], ylo = g.lo[1], yhi = g.hi[1], zlo = g.lo[2], zhi = g.hi[2];
     // axes along which the box or its v halo meets a layer (psi_v, psi_p)
-    const int xb = wi.flags & TILE_XB, yb = wi.flags & TILE_YB, zb = wi.flags & TILE_ZB;
+    const int axes = IN ? 0 : wi.flags;
+    const int xb = axes & TILE_XB, yb = axes & TILE_YB, zb = axes & TILE_ZB;
+    auto on = [](int b) { return IN ? b : again(b); };
 
     __shared__ float U[TZ][UH][UW];     // p at (x0 - 8 + c, y0 - 8 + r, z0 + p); corners unused
     __shared__ float VX[TZ][TY][VXW];   // new v_x at (x0 - 4 + c, y0 + r, z0 + p), 0 outside the grid
@@ -64,9 +70,9 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     auto elem = [&](int xp, int yp) { return (uint32_t)((yp + F) * P + xp + F) * 4u; };
     // positions outside the zero frame read zero
     auto off = [&](int xp, int yp) -> uint32_t {
-        return xp >= -F && xp < nx + F && yp >= -F && yp < ny + F ? elem(xp, yp) : kBufSkip;
+        return IN || (xp >= -F && xp < nx + F && yp >= -F && yp < ny + F) ? elem(xp, yp) : kBufSkip;
     };
-    auto in_grid = [&](int xp, int yp) { return xp >= 0 && xp < nx && yp >= 0 && yp < ny; };
+    auto in_grid = [&](int xp, int yp) { return IN || (xp >= 0 && xp < nx && yp >= 0 && yp < ny); };
 
     // ---- loads: p on the box grown by 8, v on the box grown by 4 ----
     constexpr int QN = TZ + 4 * F, VN = TZ + 2 * F;
@@ -77,8 +83,8 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
         // (planes outside the frame are read as the nearest frame plane: no tap of any point of the grid)
         uint32_t so = f0 - F * Sb;
 #pragma unroll
-        for (int o = F; o < QN; ++o, so += Sb) q[o] = Buf<float>::ld(rp, vq, o < 3 * F ? so : min(so, slast));
-        so = z0 >= F ? f0 - 2 * F * Sb : f0;
+        for (int o = F; o < QN; ++o, so += Sb) q[o] = Buf<float>::ld(rp, vq, IN || o < 3 * F ? so : min(so, slast));
+        so = IN || z0 >= F ? f0 - 2 * F * Sb : f0;
 #pragma unroll
         for (int o = 0; o < F; ++o, so += Sb) q[o] = Buf<float>::ld(rp, vq, so);
     }
@@ -112,7 +118,7 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
         }
         so = f0 - F * Sb;
 #pragma unroll
-        for (int o = 0; o < VN; ++o, so += Sb) vz[o] = Buf<float>::ld(rz, vc, min(so, slast));
+        for (int o = 0; o < VN; ++o, so += Sb) vz[o] = Buf<float>::ld(rz, vc, IN ? so : min(so, slast));
     }
     const Rsrc rpr = make_rsrc(g.prof);
     auto prof = [&](int d, int f, int c) -> float {
@@ -150,7 +156,7 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
         }
     }
     // z: bit o of zm: plane z0 - 4 + o lies in a layer; of zg: it lies in the grid
-    const uint32_t zg = plane_bits<VN>(z0 - F, 0, nz);
+    const uint32_t zg = IN ? (1u << VN) - 1u : plane_bits<VN>(z0 - F, 0, nz);
     uint32_t zm = 0;
     if (zb) {
         zm = (plane_bits<VN>(z0 - F, 0, zlo) | plane_bits<VN>(z0 - F, nz - zhi, nz));
@@ -180,7 +186,7 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
 #pragma unroll
     for (int l = 0; l < 5; ++l) w[l] = g.w[l];
     const float nlam = -g.lam;
-    const int np = nz - z0;   // planes of the box inside the grid (TZ or fewer)
+    const int np = IN ? TZ : nz - z0;   // planes of the box inside the grid (TZ or fewer)
     // kinv grad + psi, psi <- b psi + a grad first; grad outside the layer
     auto stretched = [](float grad, float &psi, float b, float a, float kinv) {
         psi = fmaf(b, psi, a * grad);
@@ -198,14 +204,14 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
                 if (o >= F && o < F + TZ) put<NT>(rq, vc, f0 + (o - F) * Sb, pz[o]);
             }
             vz[o] = (zg >> o) & 1u ? fmaf(nlam, gr, vz[o]) : 0.0f;
-            if (o >= F && o < F + TZ && o - F < again(np)) put<NT>(ro, vc, f0 + (o - F) * Sb, vz[o]);
+            if (o >= F && o < F + TZ && o - F < on(np)) put<NT>(ro, vc, f0 + (o - F) * Sb, vz[o]);
         }
     }
     __syncthreads();
     // ---- v_x, v_y on the box grown by 4; the box's own is stored ----
     {
         const Rsrc ro = make_rsrc(g.out[1]), rq = make_rsrc(g.out[4]);
-        const int n1 = again(np), b1 = again(xb);
+        const int n1 = on(np), b1 = on(xb);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) {
             float gr = d1_lds(Uc + p * UP, 1, w);
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     }
     {
         const Rsrc ro = make_rsrc(g.out[2]), rq = make_rsrc(g.out[5]);
-        const int n1 = again(np), b1 = again(yb);
+        const int n1 = on(np), b1 = on(yb);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) {
             float gr = d1_lds(Uc + p * UP, UW, w), gn = d1_lds(&U[p][rn + F][lx + 2 * F], UW, w);
@@ -246,19 +252,19 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     }
     // psi_p of the box
     float ox[TZ], oy[TZ], oz[TZ];
-    if (again(xb)) {
+    if (on(xb)) {
         const Rsrc r = make_rsrc(g.psp[0]);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) ox[p] = once<NT>(r, sx ? vc : kBufSkip, f0 + p * Sb);
     }
-    if (again(yb)) {
+    if (on(yb)) {
         const Rsrc r = make_rsrc(g.psp[1]);
 #pragma unroll
         for (int p = 0; p < TZ; ++p) oy[p] = once<NT>(r, sy ? vc : kBufSkip, f0 + p * Sb);
     }
-    if (again(zb)) {
+    if (on(zb)) {
         const Rsrc r = make_rsrc(g.psp[2]);
-        const uint32_t z1 = (uint32_t)again((int)zm);
+        const uint32_t z1 = (uint32_t)on((int)zm);
 #pragma unroll
         for (int p = 0; p < TZ; ++p)
             if ((z1 >> (p + F)) & 1u) oz[p] = once<NT>(r, vc, f0 + p * Sb);
@@ -272,20 +278,20 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     if (src) sw = g.wav[g.step];
 #pragma unroll
     for (int p = 0; p < TZ; ++p) {
-        if (p >= again(np)) break;
+        if (p >= on(np)) break;
         float gx = d1_lds(&VX[p][ly][lx + F], 1, w), gy = d1_lds(&VY[p][ly + F][lx], TX, w),
               gz = d1_lds(&vz[p + F], 1, w);
-        if (again(xb)) {
+        if (on(xb)) {
             const float s1 = stretched(gx, ox[p], ax[0], ax[1], ax[2]);
             if (sx) gx = s1;
             put<NT>(qx, sx ? vc : kBufSkip, f0 + p * Sb, ox[p]);
         }
-        if (again(yb)) {
+        if (on(yb)) {
             const float s1 = stretched(gy, oy[p], ay[0], ay[1], ay[2]);
             if (sy) gy = s1;
             put<NT>(qy, sy ? vc : kBufSkip, f0 + p * Sb, oy[p]);
         }
-        if (((uint32_t)again((int)zm) >> (p + F)) & 1u) {
+        if (((uint32_t)on((int)zm) >> (p + F)) & 1u) {
             gz = stretched(gz, oz[p], lane_value(az[0], p + F), lane_value(az[1], p + F), lane_value(az[2], p + F));
             put<NT>(qz, vc, f0 + p * Sb, oz[p]);
         }
@@ -299,11 +305,14 @@ __global__ __launch_bounds__(256, 4) void k_pv_tile(const PvTile g, const TileIt
     }
 }
 
-void pv_launch_tile(const PvTile &g, const TileItem *work, hipStream_t st) {
+void pv_launch_tile(const PvTile &g, const TileItem *work, const TileItem *inner, int nin, hipStream_t st) {
     const int rb = g.nrec > 0 ? (g.nrec + 255) / 256 : 0;
     // the hint pays once the 17 fields (68 bytes per point) outgrow the 256 MiB last-level cache by half: us per
     // step without / with it, 128^3 28.7 / 34.7, 192^3 90 / 87, 256^3 214 / 204, 384^3 632 / 594, 544^3 1742 / 1668
     const bool nt = (double)g.n[0] * g.n[1] * g.n[2] >= 6e6;
-    if (nt) hipLaunchKernelGGL(k_pv_tile<true>, dim3((unsigned)(g.nwork + rb)), dim3(256), 0, st, g, work);
-    else hipLaunchKernelGGL(k_pv_tile<false>, dim3((unsigned)(g.nwork + rb)), dim3(256), 0, st, g, work);
+    if (nin > 0) hipLaunchKernelGGL((k_pv_tile<true, true>), dim3((unsigned)nin), dim3(256), 0, st, g, inner);
+    const dim3 grid((unsigned)(g.nwork + rb));
+    if (g.nwork + rb == 0) return;
+    if (nt) hipLaunchKernelGGL((k_pv_tile<true, false>), grid, dim3(256), 0, st, g, work);
+    else hipLaunchKernelGGL((k_pv_tile<false, false>), grid, dim3(256), 0, st, g, work);
 }

@@ -36,6 +36,9 @@ constexpr int kLead = 128;   // leading pad of every field (elements)
 constexpr int kNF = 10;      // p, v_x, v_y, v_z, psi_v x3, psi_p x3
 constexpr int kRY = 1;       // z-march: rows per thread
 constexpr int kNW = 8;       // z-march: waves per workgroup
+// points from which the boxes out of every layer's reach get a launch of their own (us per step without / with:
+// 224^3 129 / 133, 256^3 209 / 207, 320^3 349 / 349, 384^3 583 / 569, 544^3 1562 / 1508, 640^3 2535 / 2463)
+constexpr double kPvInner = 3e7;
 constexpr int kTY = kRY * kNW;          // tile rows (tile: 64 x kTY)
 constexpr int kLW = 64 + 2 * kR;        // LDS row length with the x halo
 constexpr int kLH = kTY + 2 * kR;       // LDS rows with the y halo
@@ -454,8 +457,8 @@ struct fdtd_pv_ctx {
     // one-launch step (k_pv_tile): p, v and psi_v in two buffers each (fields 0 .. 6 and kNF .. kNF + 6, `par`
     // says which hold the state), and its box list
     bool tile = false;
-    int par = 0, nwork = 0;
-    size_t o_prof = 0, o_work = 0;
+    int par = 0, nwork = 0, ninner = 0;
+    size_t o_prof = 0, o_work = 0, o_inner = 0;
     std::vector<float> prof;
     char *ws = nullptr;
     int src[3] = {-1, -1, -1};
@@ -475,6 +478,7 @@ struct fdtd_pv_ctx {
             g.lo[d] = lo[d];
             g.hi[d] = hi[d];
         }
+        g.least = kR;   // the boxes' v halo in the grid, their p halo in its frame
         return g;
     }
     int cur(int f, int parity) const { return parity && f < 7 ? kNF + f : f; }   // buffer of field f
@@ -560,7 +564,9 @@ int fdtd_pv_create(const fdtd_pv_config *cfg, void *hip_stream, fdtd_pv_ctx **ou
     ctx->o_work = ctx->o_prof + ctx->prof_bytes;
     ctx->total = ctx->o_work;
     if (ctx->tile) {
-        ctx->total += a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
+        const size_t list = a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
+        ctx->o_inner = ctx->o_work + list;
+        ctx->total += 2 * list;
     }
     ctx->prof.assign((size_t)3 * 3 * ctx->nmax, 0.0f);
     for (int d = 0; d < 3; ++d) {
@@ -593,10 +599,15 @@ int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
     PVHIP(ctx, hipGetLastError());
     PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_prof, ctx->prof.data(), ctx->prof.size() * 4, hipMemcpyHostToDevice,
                               ctx->st));
-    std::vector<TileItem> work;
+    std::vector<TileItem> work, inner;
     if (ctx->tile) {
-        work = tile_list({ctx->grid()});
+        const InnerBox ib{TILE_X, (double)ctx->n[0] * ctx->n[1] * ctx->n[2] >= kPvInner ? TILE_Z : 0};
+        work = tile_list({ctx->grid()}, ib);
+        inner = tile_list({ctx->grid()}, ib, TILE_INNER);
         ctx->nwork = (int)work.size();
+        ctx->ninner = (int)inner.size();
+        PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_inner, inner.data(), sizeof(TileItem) * inner.size(),
+                                  hipMemcpyHostToDevice, ctx->st));
         PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_work, work.data(), sizeof(TileItem) * work.size(),
                                   hipMemcpyHostToDevice, ctx->st));
     }
@@ -688,7 +699,8 @@ static int pv_step_tile(fdtd_pv_ctx *ctx, int nsteps) {
         g.step = (int)ctx->step;
         g.row = row;
         g.nrec = row ? ctx->nrec : 0;
-        pv_launch_tile(g, (const TileItem *)(ctx->ws + ctx->o_work), ctx->st);
+        pv_launch_tile(g, (const TileItem *)(ctx->ws + ctx->o_work), (const TileItem *)(ctx->ws + ctx->o_inner),
+                       ctx->ninner, ctx->st);
         const long r = ctx->step - ctx->rec0;
         row = ctx->nrec > 0 && r < ctx->cap ? ctx->traces + (size_t)r * ctx->nrec : nullptr;
         ctx->par ^= 1;

@@ -20,4 +20,5 @@ struct PvTile {
     float w[5];
 };
 
-void pv_launch_tile(const PvTile &g, const TileItem *work, hipStream_t st);
+// work: the boxes of k_pv_tile (g.nwork of them); inner: nin boxes without any layer in reach
+void pv_launch_tile(const PvTile &g, const TileItem *work, const TileItem *inner, int nin, hipStream_t st);

@@ -18,6 +18,7 @@ enum TilePart { TILE_INNER, TILE_FACES, TILE_EDGES };
 // One grid's boxes: its size, its layers, the number its items carry.
 struct TileGrid {
     int n[3], lo[3], hi[3], shot;
+    int least = 0;   // the inner region keeps off a face as if its layer were so thick at least
     size_t boxes() const {
         return (size_t)((n[0] + TILE_X - 1) / TILE_X) * ((n[1] + TILE_Y - 1) / TILE_Y) * ((n[2] + TILE_Z - 1) / TILE_Z);
     }
@@ -27,7 +28,8 @@ struct TileGrid {
     bool inner(InnerBox ib, int r0[3], int r1[3]) const {
         const int ext[3] = {ib.x, TILE_Y, TILE_Z};
         for (int d = 0; d < 3; ++d) {
-            const int a = lo[d] > 0 ? lo[d] + FDTD_R : 0, b = hi[d] > 0 ? n[d] - hi[d] - FDTD_R : n[d];
+            const int l = std::max(lo[d], least), h = std::max(hi[d], least);
+            const int a = l > 0 ? l + FDTD_R : 0, b = h > 0 ? n[d] - h - FDTD_R : n[d];
             r0[d] = (a + ext[d] - 1) / ext[d] * ext[d];
             r1[d] = b / ext[d] * ext[d];
         }

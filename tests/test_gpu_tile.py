@@ -376,3 +376,15 @@ def test_pv_in_one_launch_equals_stages(case):
         s.close()
     assert np.isfinite(got[0][2]).all() and np.abs(got[0][2]).max() > 0
     _same(*got)
+
+
+@pytest.mark.parametrize("case", [
+    ((361, 343, 257), (10, 12, 9, 20, 15, 11)),
+    ((320, 320, 300), (0, 20, 20, 0, 0, 20)),
+    ((321, 313, 310), (0,) * 6),
+    ((320, 312, 312), (1,) * 6),
+    ((100, 480, 640), (28, 29, 90, 80, 3, 5)),     # one box along x
+], ids=lambda c: "x".join(map(str, c[0])))
+def test_pv_inner_launch_equals_stages(case):
+    """Large enough for a launch of its own for the boxes out of every layer's reach."""
+    test_pv_in_one_launch_equals_stages(case)

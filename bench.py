@@ -3,7 +3,7 @@
 Workload (the headline one): 512^3 grid with 20-cell CPML on all faces, seeded
 layered model (8-12 layers, 1500-4500 m/s, Gaussian-smoothed), Ricker 10 Hz
 at the centre, h = 10 m, dt at Courant number 0.5.  A step is one leapfrog
-step of the whole grid: psi pre-pass, wavefield update (interior + layers),
+step of the whole grid: layer memory, wavefield update (interior + layers),
 source and receiver gather.  Metric: million output points per second,
 nx*ny*nz*steps / time, plus the HBM roofline of the dominant kernel.
 
@@ -90,6 +90,48 @@ def step_bytes(n, cpml, field_bytes=4):
     """Algorithmic bytes of a whole step (16 B/point + 16 B per layer point-axis in FP32)."""
     N = n[0] * n[1] * n[2]
     return (3 * field_bytes + 4) * N + 16 * slab_points(n, cpml)
+
+
+def inner_points(n, cpml, storage=0, total=None):
+    """Points of one shot that k_inner updates when the shots of its context
+    have `total` points (this one alone by default): whole boxes that meet no
+    band, 32 (FP32) or 64 (16-bit) points wide, 8 rows, 8 or 16 planes deep;
+    none below the size from which the interior has a launch of its own."""
+    total = n[0] * n[1] * n[2] if total is None else total
+    if total < (16000000 if storage else 12000000):
+        return 0
+    depth = 16 if storage == 0 and total >= 100000000 else 8
+    out = 1
+    for d, ext in enumerate((64 if storage else 32, 8, 4)):
+        lo, hi = cpml[2 * d], cpml[2 * d + 1]
+        a = -(-(lo + 4 if lo > 0 else 0) // ext) * ext
+        w = ((n[d] - hi - 4 if hi > 0 else n[d]) // ext) * ext - a
+        out *= max(0, w // depth * depth if d == 2 else w)
+    return out
+
+
+def tile_kernel_bytes(shapes, cpml, storage=0):
+    """Algorithmic bytes of the launches of one step of the tile kernels, by
+    timing class: the interior's launch and the others', or the one launch that
+    does everything (psi and zeta read and written once per layer point and axis)."""
+    total = sum(a * b * c for a, b, c in shapes)
+    fb = 2 if storage else 4
+    whole = sum(step_bytes(sh, cpml, fb) for sh in shapes)
+    inner = (3 * fb + 4) * sum(inner_points(sh, cpml, storage, total) for sh in shapes)
+    return {"update": inner, "band": whole - inner} if inner else {"update": whole}
+
+
+def on_tile_kernels(tm):
+    """Whether timed steps ran on the tile kernels, which have no psi pass (grids with layers)."""
+    return tm["psi"][1] == 0 and tm["update"][1] > 0
+
+
+def tile_names(storage, split):
+    t = ("float", "_Float16", "__bf16")[storage]
+    if not split:
+        return {"update": "k_tile<%s> (the whole step)" % t}
+    return {"update": "k_inner<%s> (whole boxes outside the layer bands)" % t,
+            "band": "k_tile<%s>%s (the other boxes)" % (t, " and k_face" if storage else "")}
 
 
 def adjoint_step_bytes(n, cpml, every):
@@ -211,25 +253,29 @@ def time_gpu(w, K, W, variant, storage=0, graph=True, tblock_k=1):
 
 
 COUNTERS = os.path.join(ROOT, "profiles", "zmarch_layered512_counters.txt")
+TILE_COUNTERS = os.path.join(ROOT, "profiles", "tile_layered512_counters.txt")
 ZMARCH_SOURCES = ("paper_2606_06910_amd/csrc/kernels_step.hip", "paper_2606_06910_amd/csrc/fdtd_dev.hpp")
+TILE_SOURCES = ("paper_2606_06910_amd/csrc/kernels_tile.hip", "paper_2606_06910_amd/csrc/tile_dev.hpp",
+                "paper_2606_06910_amd/csrc/tile_host.hpp", "paper_2606_06910_amd/csrc/fdtd_dev.hpp")
 
 
-def sources_digest():
-    """sha256 over the z-march kernel's source files (identifies the kernel the counters were taken on)."""
+def sources_digest(sources=ZMARCH_SOURCES):
+    """sha256 over a kernel's source files (identifies the kernel the counters were taken on)."""
     import hashlib
 
     h = hashlib.sha256()
-    for f in ZMARCH_SOURCES:
+    for f in sources:
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
 
-def measured_traffic(n, plan, path=None):
-    """HBM bytes per z-march launch from a committed counter summary
-    (FETCH_SIZE and WRITE_SIZE KiB per dispatch times their copy-kernel
+def measured_traffic(n, plan, path=None, sources=ZMARCH_SOURCES):
+    """HBM bytes per launch of the update kernel from a committed counter
+    summary (FETCH_SIZE and WRITE_SIZE KiB per dispatch times their copy-kernel
     calibration factors), or None when that summary is missing or was taken on
-    other kernel sources, another grid or another plan."""
+    other kernel sources, another grid or another plan (of the z-march; the
+    tile kernels' summary names none)."""
     path = COUNTERS if path is None else path
     try:
         kv = {}
@@ -238,10 +284,10 @@ def measured_traffic(n, plan, path=None):
                 if ":" in line and not line.startswith("#"):
                     k, v = line.split(":", 1)
                     kv[k.strip()] = v.strip()
-        if kv.get("sources_sha256") != sources_digest():
+        if kv.get("sources_sha256") != sources_digest(sources) or kv.get("grid") != "%dx%dx%d" % tuple(n):
             return None
-        if kv.get("grid") != "%dx%dx%d" % tuple(n) or kv.get("tile_ry") != str(plan[1]) or \
-                kv.get("tile_cols", "1") != str(plan[3] if len(plan) > 3 else 1):
+        if sources == ZMARCH_SOURCES and (kv.get("tile_ry") != str(plan[1]) or
+                                          kv.get("tile_cols", "1") != str(plan[3] if len(plan) > 3 else 1)):
             return None
         fetch = float(kv["fetch_kib_per_launch"]) * 1024 * float(kv["fetch_factor"])
         write = float(kv["write_kib_per_launch"]) * 1024 * float(kv["write_factor"])
@@ -281,8 +327,8 @@ def precision_leg(K=200):
         torch.cuda.synchronize()
         out[name] = {"mpts": round(n ** 3 * K / (e0.elapsed_time(e1) / 1e3) / 1e6, 1)}
         # per-kernel durations (eager, kernels one after another) and the
-        # z-march's roofline: 16 B (FP32) or 12 B (16-bit: u^n, d^n in and out,
-        # m in) per point outside the bands
+        # roofline of the interior's kernel: 16 B (FP32) or 12 B (16-bit: u^n,
+        # d^n in and out, m in) per point
         p.reset()
         p.set_timing(True)
         p.step(8)
@@ -290,16 +336,14 @@ def precision_leg(K=200):
         p.step(40)
         tm = {kn: p.timing(c) for c, kn in enumerate(KERNEL_CLASSES)}
         p.set_timing(False)
-        fb = 4 if st == 0 else 2
-        per_pt = 16 if st == 0 else 12
-        nb = per_pt * band_split((n, n, n), (20,) * 6)[0]
         out[name]["kernel_ms"] = {k: round(v[0], 5) for k, v in tm.items() if v[1] > 0}
-        traffic = None
-        if st == 1:
-            traffic = measured_traffic((n, n, n), p.plan(0), os.path.join(ROOT, "profiles",
-                                                                          "zmarch_f16_blob768_counters.txt"))
-        out[name]["roofline"] = roofline(nb, tm["update"][0], "k_zmarch<%s> (points outside the layer bands)" %
-                                         {0: "float", 1: "_Float16", 2: "__bf16"}[st], traffic)
+        if on_tile_kernels(tm):
+            kb = tile_kernel_bytes([(n, n, n)], (20,) * 6, st)
+            out[name]["roofline"] = roofline(kb["update"], tm["update"][0], tile_names(st, len(kb) > 1)["update"])
+        else:
+            nb = (16 if st == 0 else 12) * band_split((n, n, n), (20,) * 6)[0]
+            out[name]["roofline"] = roofline(nb, tm["update"][0], "k_zmarch<%s> (points outside the layer bands)" %
+                                             {0: "float", 1: "_Float16", 2: "__bf16"}[st])
         p.close()
     del v
     torch.cuda.empty_cache()
@@ -343,8 +387,8 @@ def _timed_steps(p, steps, graph):
 def small_leg():
     """The 64^3 workload (10-cell layers, 200 steps): a few MB, launch-bound;
     Mpts/s with every step launched eagerly and with the HIP-graph time loop,
-    for the automatic variant (the naive kernel at this size) and for the
-    z-march."""
+    for the automatic variant (one k_tile launch per step; its plan reports the
+    variant it replaces) and for the z-march."""
     import numpy as np
     import torch
 
@@ -518,7 +562,7 @@ def batched_leg(K=600, nshots=24):
     setup(pb, range(nshots))
     ms_b = timed(pb, K)
     # per-kernel durations (eager, the kernels of a step one after another) and
-    # the rooflines of the z-march and the band kernel over all shots
+    # the roofline of the one that takes longest, over all shots
     pb.reset()
     pb.set_timing(True)
     pb.step(8)
@@ -532,8 +576,11 @@ def batched_leg(K=600, nshots=24):
           "band": sum(band_kernel_bytes(sh, cp) for sh in shapes),
           "psi": sum(psi_kernel_bytes(sh, cp) for sh in shapes)}
     kms = {k: round(v[0], 5) for k, v in tm.items() if v[1] > 0}
-    dom = max(("update", "band"), key=lambda k: kms.get(k, 0.0))
     names = {"update": "k_zmarch (points outside the layer bands, all shots)", "band": "k_band (band points, all shots)"}
+    if on_tile_kernels(tm):
+        kb = tile_kernel_bytes(shapes, cp)
+        names = tile_names(0, len(kb) > 1)
+    dom = max(("update", "band"), key=lambda k: kms.get(k, 0.0))
     ms_s = 0.0
     for i in range(nshots):
         p = Propagator([shots[i]])
@@ -660,10 +707,11 @@ def pv_leg(sizes=(320, 480, 544, 640, 800), K=64, W=4):
     step, six memory variables) on its single-GPU throughput grids: N^3 with
     20-cell layers on every face, lambda = 0.05, 64 steps from an initial
     pulse, FP32.  Mpts/s, and the step's algorithmic bytes over its time
-    (48 B per point: p read, v read and written in the velocity stage; v read,
-    p read and written in the pressure stage; plus a read and write of a
-    memory variable per layer point and axis in each stage).  The paper's
-    numbers for the same grids (another GPU) ride along as context."""
+    (32 B per point: p and v read and written once, both stages in one launch;
+    48 B where a field takes 2 GiB or more and the stages are launches of their
+    own: v read twice, p written after both; plus a read and write of a memory
+    variable per layer point and axis in each stage).  The paper's numbers for
+    the same grids (another GPU) ride along as context."""
     import torch
 
     from paper_2606_06910_amd import PVPropagator
@@ -688,7 +736,8 @@ def pv_leg(sizes=(320, 480, 544, 640, 800), K=64, W=4):
         del s
         torch.cuda.empty_cache()
         slab = slab_points((N, N, N), (20,) * 6)
-        nbytes = 48 * N ** 3 + 16 * slab
+        field = 4 * ((N + 67) // 64 * 64) * (N + 8) ** 2
+        nbytes = (32 if field < 1 << 31 else 48) * N ** 3 + 16 * slab
         mpts = N ** 3 * K / (ms / 1e3) / 1e6
         out["n%d" % N] = {"mpts": round(mpts, 1), "ms_per_step": round(ms / K, 4),
                           "algorithmic_gbs": round(nbytes / (ms / K / 1e3) / 1e9, 1),
@@ -967,14 +1016,18 @@ def main():
     N = w.npts
     value = N * K / (ms / 1e3) / 1e6
     upd = tm["update"]
-    upd_bytes = interior_kernel_bytes(w.n, w.cpml)
+    if on_tile_kernels(tm):
+        kb = tile_kernel_bytes([w.n], w.cpml)
+        kernel = tile_names(0, len(kb) > 1)["update"]
+        traffic = measured_traffic(w.n, plan, TILE_COUNTERS, TILE_SOURCES) if len(kb) > 1 else None
+    else:
+        kb = {"update": interior_kernel_bytes(w.n, w.cpml), "band": band_kernel_bytes(w.n, w.cpml),
+              "psi": psi_kernel_bytes(w.n, w.cpml)}
+        kernel = "%s (update of the points outside the layer bands)" % zmarch_instance(plan)
+        traffic = measured_traffic(w.n, plan)
+    upd_bytes = kb["update"]
     achieved = upd_bytes / (upd[0] / 1e3) / 1e9
-    kgbs = {}
-    for name, nbytes in (("update", upd_bytes), ("band", band_kernel_bytes(w.n, w.cpml)),
-                         ("psi", psi_kernel_bytes(w.n, w.cpml))):
-        if tm[name][1] > 0:
-            kgbs[name] = round(nbytes / (tm[name][0] / 1e3) / 1e9, 1)
-    traffic = measured_traffic(w.n, plan)
+    kgbs = {k: round(v / (tm[k][0] / 1e3) / 1e9, 1) for k, v in kb.items() if tm[k][1] > 0}
     out = {
         "metric": "Mpts/s (output points/sec) + % HBM peak, FP32 vs FP16-storage at stated error",
         "value": round(value, 1),
@@ -997,7 +1050,7 @@ def main():
                                        if traffic else None),
                      "copy_ceiling_gbs": COPY_CEILING_GBS,
                      "stream_ceiling_gbs": STREAM_CEILING_GBS,
-                     "kernel": "%s (update of the points outside the layer bands)" % zmarch_instance(plan),
+                     "kernel": kernel,
                      "kernel_ms": round(upd[0], 5), "algorithmic_bytes_per_launch": upd_bytes},
         "step_algorithmic_gbs": round(step_bytes(w.n, w.cpml) / (ms / K / 1e3) / 1e9, 1),
         "kernel_ms": {k: round(v[0], 5) for k, v in tm.items() if v[1] > 0},

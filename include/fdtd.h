@@ -64,11 +64,10 @@ enum fdtd_face { FDTD_FACE_DIRICHLET = 0, FDTD_FACE_GHOST = 1 };
 enum fdtd_variant {
     FDTD_VARIANT_AUTO = 0,   /* z-march (or the tuned choice, see fdtd_autotune);
                                 naive for a single-shot context below 150^3 points.
-                                A shot without ghost faces (of up to 3e8 points in
-                                16-bit storage) runs each step as one launch, or
-                                two on large grids, under the plan reported for it,
-                                with the same bits; fdtd_set_plan takes it off that
-                                path */
+                                A shot without ghost faces runs each step as one
+                                launch, or up to three on large grids, under the
+                                plan reported for it, with the same bits;
+                                fdtd_set_plan takes it off that path */
     FDTD_VARIANT_NAIVE = 1,  /* one thread per point, all layer logic inline       */
     FDTD_VARIANT_ZMARCH = 2, /* LDS-staged xy tiles, z-marching register queue      */
     FDTD_VARIANT_TBLOCK = 3  /* tblock_k steps per launch (temporal blocking)       */

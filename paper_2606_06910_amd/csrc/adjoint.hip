@@ -467,6 +467,7 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
     }
     L.gstart = take((size_t)(s.nrec + 1) * 4);
     L.ridx = take((size_t)std::max(s.nrec, 1) * 4);
+    L.gpos = take(tiles ? (size_t)std::max(s.nrec, 1) * 4 : 0);
     L.tab = take(sizeof(AdjShot) * nctx);
     L.jobs = take(sizeof(DiffJob) * (size_t)(2 * (every + 1) * 2) * nctx);
     L.rjobs = take(sizeof(CopyJob) * (size_t)L.nck * 2 * 8 * nctx);
@@ -475,7 +476,6 @@ static AdjLayout adj_layout(const fdtd_ctx *ctx, const ShotH &s, int every, int 
     L.bmap2 = take(sizeof(int) * (size_t)std::max(tiles ? 0L : blocks2, 1L));
     L.atab = take(tiles ? sizeof(AdjTile) * nctx : 0);
     L.items = take(tiles ? sizeof(TileItem) * tile_list_bound((size_t)boxes) : 0);
-    L.gpos = take(tiles ? (size_t)std::max(s.nrec, 1) * 4 : 0);
     L.grp = take(tiles ? sizeof(AdjGroups) * tile_list_bound((size_t)boxes) : 0);
     L.total = off;
     return L;
@@ -539,7 +539,6 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         ctx->hdesc[sh[q]].trace_cap = 0;
         AHIP(ctx, hipMemcpyAsync(dd + sh[q], &ctx->hdesc[sh[q]], sizeof(DevShot), hipMemcpyHostToDevice, st));
     }
-    AHIP(ctx, hipStreamSynchronize(st));
 
     // adjoint state to zero (W_d stays zero outside the slabs), receiver
     // groups, the AdjShot table, the wave and block maps, the level-copy and
@@ -554,6 +553,14 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     std::vector<AdjTile> atab(tiles ? nsh : 0);
     std::vector<TileGrid> grids;
     std::map<std::array<int, 4>, AdjGroups> at_box;   // (shot of the sweep, box z, y, x): the groups in the box
+    // each shot's tables (the first one's hold those of the sweep), one copy per shot: they lie one after another
+    // from `gstart` on, and live here until the copies are done
+    std::vector<std::vector<char>> up(nsh);
+    auto put = [&](int q, size_t base, size_t off, const void *src, size_t bytes) {
+        if (bytes == 0) return;
+        if (up[q].size() < off - base + bytes) up[q].resize(off - base + bytes);
+        memcpy(up[q].data() + (off - base), src, bytes);
+    };
     int bbase = 0, bbase2 = 0, maxg = 0;
     long maxrows = 0, maxck = 0;
     for (int q = 0; q < nsh; ++q) {
@@ -621,10 +628,9 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
             }
             gstart.push_back((int)ridx.size());
             a.ngroups = (int)members.size();
-            AHIP(ctx, hipMemcpyAsync(B + L.gstart, gstart.data(), gstart.size() * 4, hipMemcpyHostToDevice, st));
-            AHIP(ctx, hipMemcpyAsync(B + L.ridx, ridx.data(), ridx.size() * 4, hipMemcpyHostToDevice, st));
-            if (tiles) AHIP(ctx, hipMemcpyAsync(B + L.gpos, gpos.data(), gpos.size() * 4, hipMemcpyHostToDevice, st));
-            AHIP(ctx, hipStreamSynchronize(st));
+            put(q, L.gstart, L.gstart, gstart.data(), gstart.size() * 4);
+            put(q, L.gstart, L.ridx, ridx.data(), ridx.size() * 4);
+            if (tiles) put(q, L.gstart, L.gpos, gpos.data(), gpos.size() * 4);
         }
         a.gstart = (const int *)(B + L.gstart);
         a.ridx = (const int *)(B + L.ridx);
@@ -725,16 +731,6 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     const int *bmap_d = (const int *)(s0h.ck_buf + L0.bmap);
     const int *bmap2_d = (const int *)(s0h.ck_buf + L0.bmap2);
     const unsigned nslab = (unsigned)smap.size();
-    AHIP(ctx, hipMemcpyAsync((void *)tab_d, tab.data(), sizeof(AdjShot) * nsh, hipMemcpyHostToDevice, st));
-    AHIP(ctx, hipMemcpyAsync((void *)jobs_d, jobs.data(), sizeof(DiffJob) * jobs.size(), hipMemcpyHostToDevice, st));
-    AHIP(ctx, hipMemcpyAsync((void *)rjobs_d, rjobs.data(), sizeof(CopyJob) * rjobs.size(), hipMemcpyHostToDevice,
-                             st));
-    if (!smap.empty())
-        AHIP(ctx, hipMemcpyAsync((void *)smap_d, smap.data(), sizeof(SlabBlock) * smap.size(), hipMemcpyHostToDevice,
-                                 st));
-    AHIP(ctx, hipMemcpyAsync((void *)bmap_d, bmap.data(), sizeof(int) * bmap.size(), hipMemcpyHostToDevice, st));
-    if (!bmap2.empty())
-        AHIP(ctx, hipMemcpyAsync((void *)bmap2_d, bmap2.data(), sizeof(int) * bmap2.size(), hipMemcpyHostToDevice, st));
     const AdjTile *atab_d = (const AdjTile *)(s0h.ck_buf + L0.atab);
     const TileItem *items_d = (const TileItem *)(s0h.ck_buf + L0.items);
     const std::vector<TileItem> items = tile_list(grids);
@@ -746,11 +742,23 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
         const auto it = at_box.find({w.flags & 0xff, w.z0 / TILE_Z, w.y0 / TILE_Y, w.x0 / TILE_X});
         if (it != at_box.end()) grp[i] = it->second;
     }
+    auto put0 = [&](size_t off, const auto &v) { put(0, L0.gstart, off, v.data(), sizeof(v[0]) * v.size()); };
+    put0(L0.tab, tab);
+    put0(L0.jobs, jobs);
+    put0(L0.rjobs, rjobs);
+    put0(L0.smap, smap);
+    put0(L0.bmap, bmap);
+    put0(L0.bmap2, bmap2);
     if (tiles) {
-        AHIP(ctx, hipMemcpyAsync((void *)grp_d, grp.data(), sizeof(AdjGroups) * grp.size(), hipMemcpyHostToDevice, st));
-        AHIP(ctx, hipMemcpyAsync((void *)atab_d, atab.data(), sizeof(AdjTile) * atab.size(), hipMemcpyHostToDevice, st));
-        AHIP(ctx, hipMemcpyAsync((void *)items_d, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice,
-                                 st));
+        put0(L0.atab, atab);
+        put0(L0.items, items);
+        put0(L0.grp, grp);
+    }
+    for (int q = 0; q < nsh; ++q) {
+        const ShotH &s = ctx->shots[sh[q]];
+        if (!up[q].empty())
+            AHIP(ctx, hipMemcpyAsync(s.ck_buf + adj_layout(ctx, s, every, s.ck_count).gstart, up[q].data(), up[q].size(),
+                                     hipMemcpyHostToDevice, st));
     }
     // steps whose every shot is a tile shot write the increments themselves
     bool fused = true;

@@ -520,11 +520,6 @@ static int upload_desc(fdtd_ctx *ctx) {
     memcpy(both.data() + at, ctx->htile.data(), nt);
     HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), both.data(), both.size(), hipMemcpyHostToDevice, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    for (const ShotH &s : ctx->shots)
-        if (s.tile) {
-            fdtd_clear_graphs(ctx);   // a launch over one tile shot carries its descriptor as it was
-            break;
-        }
     return FDTD_OK;
 }
 
@@ -750,7 +745,8 @@ static void enqueue_psi_update(fdtd_ctx *ctx, int shot, const Roles &R) {
         int nrec = 0;
         for (int i = lo; i < hi; ++i)
             if (ctx->pend > 0 && ctx->hdesc[i].traces) nrec = hi - lo;
-        const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc), *one = hi - lo == 1 ? &ctx->htile[lo] : nullptr;
+        const bool one = hi - lo == 1;
+        const TileDesc *descs = (const TileDesc *)wsp(ctx, ctx->o_tdesc) + (one ? lo : 0);
         const ShotH &s0 = ctx->shots[lo];
         const bool all = shot < 0 || ctx->shots.size() == 1;
         TileStep A{R.iu, ctx->pend, 0, lo, ctx->tile_nt, ctx->inc};

@@ -20,10 +20,10 @@ void fdtd_launch_band(int stor, const DevShot *d_shots, const BandItem *work, in
 // receivers of the step numbered `adv` - 1 past the device step counter, which then advances by adv
 void fdtd_launch_record(int stor, const DevShot *d_shots, int nshots, const Roles &R, int *stepc, int adv,
                         hipStream_t st);
-// whole step of tile shots (one: the host copy of the descriptor of a launch over one shot); nrec extra blocks
+// whole step of tile shots (one: a launch over one shot, whose descriptor d_descs is); nrec extra blocks
 // record the shots from A.rec_lo on
 void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
-                      const TileStep &A, int nrec, const int *stepc, const TileDesc *one, hipStream_t st);
+                      const TileStep &A, int nrec, const int *stepc, bool one, hipStream_t st);
 // temporal blocking: args points to a host TBArgs (kernels_tblock.hip); K = 2 or 4
 void fdtd_launch_tblock(const DevShot *d_shots, const WorkItem *work, int nwork, int K, const void *args, int zchunk,
                         const int *stepc, hipStream_t st);
@@ -37,13 +37,13 @@ struct TBArgsHost {
 
 // the inner region's boxes of tile shots, iz planes deep (TileGrid::inner)
 void fdtd_launch_inner(int stor, InnerBox ib, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
-                       const int *stepc, const TileDesc *one, hipStream_t st);
+                       const int *stepc, bool one, hipStream_t st);
 
 // copy the ranges of a PackJob in one launch
 void fdtd_launch_pack(const PackJob &j, hipStream_t st);
 // their other boxes that meet one band at most
 void fdtd_launch_face(int stor, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
-                      const TileDesc *one, hipStream_t st);
+                      bool one, hipStream_t st);
 
 void fdtd_launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 // zero every range of a device-resident FillJob list in one launch; max_n16 = longest range

@@ -38,15 +38,21 @@ constexpr int PXW = TX + 2 * FDTD_R, PYH = TY + 2 * FDTD_R; // new psi_x rows, n
 // the descriptors read as constant memory: no store of the kernel changes them, so they may be loaded at once
 typedef __attribute__((address_space(4))) const TileDesc ConstDesc;
 constexpr int AX_ANY = TILE_XB | TILE_YB | TILE_ZB;
+// The descriptor of a box's shot.  ONE: a launch over one shot, descs its descriptor, which then loads beside the
+// list item and not after it.  Always read from the device, where a new source or model goes: captured steps stay
+// valid.
+template <bool ONE> __device__ __forceinline__ const ConstDesc &shot_desc(const TileDesc *descs, const TileItem &wi) {
+    return *(const ConstDesc *)(uintptr_t)(descs + (ONE ? 0 : wi.flags & 0xff));
+}
 }  // namespace
 
-// one box (D: TileDesc in the constant or the kernel-argument address space).  INC: the
+// one box.  INC: the
 // increment u^{n+1} - u^n is stored too (an adjoint sweep keeps it), 4 bytes per
 // point here against 12 in a pass of its own; a template flag, because as a test in
 // the kernel it cost plain steps 1 % (160^3).  AX: the axes whose band the box meets
 // (TILE_XB etc.), or AX_ANY, where the item says which.
-template <typename T, int AX, bool NT, bool INC, typename D>
-__device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const TileStep &A,
+template <typename T, int AX, bool NT, bool INC>
+__device__ __forceinline__ void tile_box(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                          const int *__restrict__ stepc, float *lds) {
     const int t = (int)threadIdx.x;
     const int nx = s.nx, ny = s.ny, nz = s.nz;
@@ -381,8 +387,8 @@ __device__ __forceinline__ void tile_box(const D &s, const TileItem &wi, const T
 // kernel leaves it, and 345 us on all.  Boxes of 8 planes hold 54 VGPRs and 20 KB
 // of LDS: eight blocks per CU, the memory's latency hidden by other blocks
 // instead of a register queue along z.
-template <int IZ, bool INC, typename D>
-__device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const TileStep &A,
+template <int IZ, bool INC>
+__device__ __forceinline__ void inner_box(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                           const int *__restrict__ stepc) {
     constexpr int F = FDTD_R, LW = TX + 2 * F, LH = TY + 2 * F, LP = LW * LH, XH = IZ / 4;
     __shared__ float U[IZ * LP];   // u^n at (x0 - 4 + c, y0 - 4 + r, z0 + p); corners unused
@@ -472,8 +478,8 @@ __device__ __forceinline__ void inner_box(const D &s, const TileItem &wi, const 
 // stores need.  611 x 387 x 453 BF16, 16-cell layers: 68 M points in 280 us (boxes 32
 // wide) -> 178 us for 69 M (12 bytes a point: 4.6 TB/s); 768^3 FP16 332 M points in
 // 858 us.  94 VGPRs and 37 KB of LDS (FP32, read eight bytes at a time): four blocks per CU.
-template <typename T, int IZ, typename D>
-__device__ __forceinline__ void inner_pair(const D &s, const TileItem &wi, const TileStep &A,
+template <typename T, int IZ>
+__device__ __forceinline__ void inner_pair(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                            const int *__restrict__ stepc) {
     constexpr int F = FDTD_R, LW = 2 * TX + 2 * F, LH = TY + 2 * F, LP = LW * LH;
     static_assert(IZ * TY * F == 256, "one x-halo pair per thread");
@@ -576,18 +582,14 @@ __device__ __forceinline__ void inner_pair(const D &s, const TileItem &wi, const
 
 template <typename T, int IZ, bool ONE, bool INC>
 __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
-                                               TileStep A, const int *__restrict__ stepc, const TileDesc one) {
+                                               TileStep A, const int *__restrict__ stepc) {
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (IsInc<T>::v) {
-        if constexpr (ONE) inner_pair<T, IZ>(one, wi, A, stepc);
-        else inner_pair<T, IZ>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
-    } else if constexpr (ONE) inner_box<IZ, INC>(one, wi, A, stepc);
-    else inner_box<IZ, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc);
+    const ConstDesc &s = shot_desc<ONE>(descs, wi);
+    if constexpr (IsInc<T>::v) inner_pair<T, IZ>(s, wi, A, stepc);
+    else inner_box<IZ, INC>(s, wi, A, stepc);
 }
 
-// ONE: a launch over one shot, whose descriptor travels with the kernel's arguments (one dependent load less
-// before the box's own)
 // Boxes that meet one band at most, in 16-bit storage: tile_box built for each case
 // holds 79 VGPRs and 27 KB of LDS where the build for any box holds 116 and 31, so
 // six blocks share a CU and not four.  In 16-bit storage k_tile is bound by latency
@@ -595,8 +597,8 @@ __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ desc
 // 387 x 453 BF16 20.4 -> 19.8 ms for 40.  In FP32 it does not (512^3 283 us for k_tile
 // alone, 227 + 56 for both; 24 batched shots 864, 544 + 337): its boxes already move
 // 4.5 to 5 TB/s, counted, at four blocks per CU.
-template <typename T, typename D>
-__device__ __forceinline__ void face_box(const D &s, const TileItem &wi, const TileStep &A,
+template <typename T>
+__device__ __forceinline__ void face_box(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                          const int *__restrict__ stepc, float *lds) {
     const int ax = uniform(wi.flags & AX_ANY);
     if (ax == 0) tile_box<T, 0, false, false>(s, wi, A, stepc, lds);
@@ -606,17 +608,16 @@ __device__ __forceinline__ void face_box(const D &s, const TileItem &wi, const T
 }
 template <typename T, bool ONE>
 __global__ __launch_bounds__(256, 6) void k_face(const TileDesc *__restrict__ descs, const TileItem *__restrict__ work,
-                                                 TileStep A, const int *__restrict__ stepc, const TileDesc one) {
+                                                 TileStep A, const int *__restrict__ stepc) {
     __shared__ float lds[TZ * UH * UW + TZ * PYH * TX];
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) face_box<T>(one, wi, A, stepc, lds);
-    else face_box<T>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc, lds);
+    face_box<T>(shot_desc<ONE>(descs, wi), wi, A, stepc, lds);
 }
 template <typename T, bool ONE, bool NT, bool INC>
 __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ shots, const TileDesc *__restrict__ descs,
                                                  const TileItem *__restrict__ work, TileStep A,
-                                                 const int *__restrict__ stepc, const TileDesc one) {
+                                                 const int *__restrict__ stepc) {
     __shared__ float lds[TZ * UH * UW + TZ * TY * PXW + TZ * PYH * TX];
     const int t = (int)threadIdx.x;
     if ((int)blockIdx.x >= A.nwork) {
@@ -634,8 +635,7 @@ __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ sho
     }
     const TileItem wi = work[blockIdx.x];
     if (wi.flags < 0) return;   // the idle items that pad the list
-    if constexpr (ONE) tile_box<T, AX_ANY, NT, INC>(one, wi, A, stepc, lds);
-    else tile_box<T, AX_ANY, NT, INC>(*(const ConstDesc *)(uintptr_t)(descs + (wi.flags & 0xff)), wi, A, stepc, lds);
+    tile_box<T, AX_ANY, NT, INC>(shot_desc<ONE>(descs, wi), wi, A, stepc, lds);
 }
 
 // launch f(ONE, NT, INC as std::bool_constant); only FP32 fields have increments
@@ -653,37 +653,37 @@ static void with_flags(bool one, bool nt, bool inc, F f) {
 
 template <typename T, int IZ>
 static void launch_inner_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
-                           const TileDesc *one, hipStream_t st) {
+                           bool one, hipStream_t st) {
     with_flags<T>(one, true, A.inc >= 0, [&](auto ONE, auto, auto INC) {
         hipLaunchKernelGGL((k_inner<T, IZ, ONE.value, INC.value>), dim3((unsigned)A.nwork), dim3(256), 0, st, d_descs,
-                           work, A, stepc, one ? *one : TileDesc{});
+                           work, A, stepc);
     });
 }
 template <typename T>
 static void launch_tile_t(const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
-                          int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
+                          int nrec, const int *stepc, bool one, hipStream_t st) {
     with_flags<T>(one, A.nt, A.inc >= 0, [&](auto ONE, auto NT, auto INC) {
         hipLaunchKernelGGL((k_tile<T, ONE.value, NT.value, INC.value>), dim3((unsigned)(A.nwork + nrec)), dim3(256), 0,
-                           st, d_shots, d_descs, work, A, stepc, one ? *one : TileDesc{});
+                           st, d_shots, d_descs, work, A, stepc);
     });
 }
 
 template <typename T>
 static void launch_face_t(const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
-                          const TileDesc *one, hipStream_t st) {
+                          bool one, hipStream_t st) {
     const dim3 grid((unsigned)A.nwork);
-    if (one) hipLaunchKernelGGL((k_face<T, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc, *one);
-    else hipLaunchKernelGGL((k_face<T, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc, TileDesc{});
+    if (one) hipLaunchKernelGGL((k_face<T, true>), grid, dim3(256), 0, st, d_descs, work, A, stepc);
+    else hipLaunchKernelGGL((k_face<T, false>), grid, dim3(256), 0, st, d_descs, work, A, stepc);
 }
 void fdtd_launch_face(int stor, const TileDesc *d_descs, const TileItem *work, const TileStep &A, const int *stepc,
-                      const TileDesc *one, hipStream_t st) {
+                      bool one, hipStream_t st) {
     if (A.nwork <= 0) return;
     if (stor == 1) launch_face_t<_Float16>(d_descs, work, A, stepc, one, st);
     else launch_face_t<__bf16>(d_descs, work, A, stepc, one, st);
 }
 
 void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs, const TileItem *work,
-                      const TileStep &A, int nrec, const int *stepc, const TileDesc *one, hipStream_t st) {
+                      const TileStep &A, int nrec, const int *stepc, bool one, hipStream_t st) {
     if (A.nwork + nrec <= 0) return;
     if (stor == 1) launch_tile_t<_Float16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
     else if (stor == 2) launch_tile_t<__bf16>(d_shots, d_descs, work, A, nrec, stepc, one, st);
@@ -691,7 +691,7 @@ void fdtd_launch_tile(int stor, const DevShot *d_shots, const TileDesc *d_descs,
 }
 
 void fdtd_launch_inner(int stor, InnerBox ib, const TileDesc *d_descs, const TileItem *work, const TileStep &A,
-                       const int *stepc, const TileDesc *one, hipStream_t st) {
+                       const int *stepc, bool one, hipStream_t st) {
     if (A.nwork <= 0) return;
     if (stor == 1) launch_inner_t<_Float16, 8>(d_descs, work, A, stepc, one, st);
     else if (stor == 2) launch_inner_t<__bf16, 8>(d_descs, work, A, stepc, one, st);

@@ -388,3 +388,43 @@ def test_pv_in_one_launch_equals_stages(case):
 def test_pv_inner_launch_equals_stages(case):
     """Large enough for a launch of its own for the boxes out of every layer's reach."""
     test_pv_in_one_launch_equals_stages(case)
+
+
+@pytest.mark.parametrize("cases", [GEOMETRIES[:1], GEOMETRIES[:2]], ids=["one", "two"])
+def test_graph_replays_take_a_new_source_and_model(cases):
+    """A survey's loop on one context: new source, new model, or both, reset, the same graph; each pass against eager
+    steps of a context made for it."""
+    import torch
+
+    nt = 12
+    p, ws, tr = _prop(cases, nt, [AUTO] * len(cases))
+
+    def model(q, i, k):
+        q.set_velocity(i, torch.from_numpy(ws[i][0] * np.float32(1.0 - 0.02 * k)).cuda())
+
+    def source(q, i, k):
+        q.inject_source(i, (2 + k, 3, 4 + k), torch.from_numpy(ws[i][4] * np.float32(1 + k)).cuda())
+
+    for k, (new_source, new_model) in enumerate([(0, 0), (1, 0), (0, 1), (1, 1), (0, 0)]):
+        ks = k if new_source else (ks if k else 0)
+        km = k if new_model else (km if k else 0)
+        q, _, tq = _prop(cases, nt, [AUTO] * len(cases))
+        for i in range(len(cases)):
+            if new_source:
+                source(p, i, ks)
+            if new_model:
+                model(p, i, km)
+            if ks:
+                source(q, i, ks)
+            if km:
+                model(q, i, km)
+            tr[i].zero_()
+        p.reset()
+        p.step(nt, graph=True)
+        q.reset()
+        q.step(nt)
+        got = _out(p, tr)
+        assert np.abs(got[0]).max() > 0
+        _same(got, _out(q, tq))
+        q.close()
+    p.close()

@@ -1,0 +1,116 @@
+"""The library's host code on the CPU, against a stand-in for the HIP runtime
+(hip_stub.cpp) that counts launches and graph instantiations: what a call
+enqueues, and what it keeps, where the results alone do not show it."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import numpy as np
+import pytest
+
+from paper_2606_06910_amd import _lib, build_lib
+
+TESTS = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    """libfdtd built for the host alone and linked with the stand-in."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    d = tmp_path_factory.mktemp("host")
+    src = [os.path.join(build_lib.CSRC, s) for s in build_lib.SOURCES] + [os.path.join(TESTS, "hip_stub.cpp")]
+
+    def obj(s):
+        o = str(d / (os.path.basename(s) + ".o"))
+        subprocess.run([hipcc, "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-w", "-I", build_lib.CSRC, "-c", "-o",
+                        o, s], check=True, capture_output=True)
+        return o
+
+    with ThreadPoolExecutor(4) as ex:
+        objs = list(ex.map(obj, src))
+    # each object names the embedded device code it was built without
+    fat = sorted(set(re.findall(r"__hip_fatbin_\w+", subprocess.run(["nm", "-u"] + objs, check=True, capture_output=True,
+                                                                   text=True).stdout)))
+    (d / "fat.c").write_text("".join("const unsigned %s[4] = {0};\n" % f for f in fat))
+    so = str(d / "libfdtd_host.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-o", so, str(d / "fat.c")] + objs + ["-lstdc++", "-lm"], check=True,
+                   capture_output=True)
+    L = ctypes.CDLL(so)
+    L.stub_launches.restype = L.stub_blocks.restype = L.stub_instantiated.restype = ctypes.c_long
+    L.fdtd_last_error.restype = L.fdtd_pv_last_error.restype = ctypes.c_char_p
+    return L
+
+
+def _ptr(a):
+    return ctypes.c_void_p(a.ctypes.data)
+
+
+def _aligned(nbytes):
+    a = np.zeros(nbytes + 256, np.uint8)
+    off = (-a.ctypes.data) % 256
+    return a[off:off + nbytes]
+
+
+class Ctx:
+    """One second-order context on host memory; shots: (n, cpml) each."""
+
+    def __init__(self, L, shots, variant=0, storage=0, nt=64, nrec=5, less=0):
+        self.L, self.keep = L, []
+        arr = (_lib.ShotConfig * len(shots))()
+        for s, (n, cpml) in zip(arr, shots):
+            s.n[:], s.h[:], s.cpml[:] = n, (10.0,) * 3, cpml
+            s.dt, s.exchange_every, s.R, s.kappa_max, s.alpha_frac = 1e-4, 1, 1e-8, 5.0, 0.05
+            s.storage, s.variant, s.tblock_k, s.field_scale = storage, variant, 1, 1024.0 if storage else 0.0
+        self.c = ctypes.c_void_p()
+        assert L.fdtd_create(arr, len(shots), None, ctypes.byref(self.c)) == 0
+        nb = ctypes.c_size_t()
+        assert L.fdtd_workspace_size(self.c, ctypes.byref(nb)) == 0
+        self.ws = _aligned(nb.value)
+        self.bound = L.fdtd_bind_workspace(self.c, _ptr(self.ws), ctypes.c_size_t(nb.value - less))
+        if self.bound != 0:
+            return
+        for i, (n, _) in enumerate(shots):
+            self.model(i, n)
+            self.source(i, (4, 4, 4), nt)
+            rec, tr = self.hold(np.full((nrec, 3), 5, np.int32)), self.hold(np.zeros((nt, nrec), np.float32))
+            assert L.fdtd_set_receivers(self.c, i, _ptr(rec), nrec) == 0
+            assert L.fdtd_record_receivers(self.c, i, _ptr(tr), nt) == 0
+
+    def hold(self, a):
+        self.keep.append(a)
+        return a
+
+    def model(self, i, n):
+        v = self.hold(np.full(n[::-1], 2000.0, np.float32))
+        assert self.L.fdtd_set_velocity(self.c, i, _ptr(v)) == 0
+
+    def source(self, i, at, nt=64):
+        w = self.hold(np.ones(nt, np.float32))
+        assert self.L.fdtd_inject_source(self.c, i, *at, _ptr(w), nt, ctypes.c_float(1.0)) == 0
+
+    def close(self):
+        self.L.fdtd_destroy(self.c)
+
+
+@pytest.mark.parametrize("shots", [[((40, 36, 33), (8,) * 6)], [((40, 36, 33), (8,) * 6), ((33, 40, 36), (6,) * 6)]],
+                         ids=["one", "two"])
+def test_graph_kept_over_a_new_source_and_model(host, shots):
+    """The captured steps read source and model from the device: a survey's loop of new source or model, reset and
+    step as a graph captures once."""
+    p = Ctx(host, shots)
+    assert p.bound == 0
+    host.stub_reset()
+    for k in range(4):
+        for i, (n, _) in enumerate(shots):
+            p.source(i, (5 + k, 6, 7))
+            p.model(i, n)
+        assert host.fdtd_reset(p.c) == 0
+        assert host.fdtd_step_graph(p.c, 10) == 0
+    assert host.stub_instantiated() == 1
+    assert host.stub_launches(b"k_tile") == 10      # (captured once, by the tile kernel)
+    p.close()

@@ -89,7 +89,9 @@ int fdtd_pv_set_source(fdtd_pv_ctx *ctx, int32_t i, int32_t j, int32_t k, const 
  * for a receiver outside the grid (checked on the host: synchronises). */
 int fdtd_pv_set_receivers(fdtd_pv_ctx *ctx, const int32_t *rec_dev, int32_t nrec, float *traces_dev, int32_t cap);
 
-/* Advance nsteps steps (one kernel per step, or two, plus the receiver gather). */
+/* Advance nsteps steps (one kernel per step, or two, plus the receiver gather).
+ * A caller may capture the call (on a stream other than the null stream) and
+ * replay it; a replay repeats the captured call's source samples and trace rows. */
 int fdtd_pv_step(fdtd_pv_ctx *ctx, int32_t nsteps);
 
 /* Message of the last failed call on this context. */

@@ -458,6 +458,7 @@ struct fdtd_pv_ctx {
     // says which hold the state), and its box list
     bool tile = false;
     int par = 0, nwork = 0, ninner = 0;
+    bool fixed = false;   // a caller has captured work on the state: `par` stays as it is from call to call
     size_t o_prof = 0, o_work = 0, o_inner = 0;
     std::vector<float> prof;
     char *ws = nullptr;
@@ -500,10 +501,10 @@ struct fdtd_pv_ctx {
 
 static PvArgs pv_args(const fdtd_pv_ctx *ctx) {
     PvArgs g;
-    g.p = ctx->field(0);
+    g.p = ctx->field(ctx->cur(0, ctx->par));
     for (int d = 0; d < 3; ++d) {
-        g.v[d] = ctx->field(1 + d);
-        g.psv[d] = ctx->field(4 + d);
+        g.v[d] = ctx->field(ctx->cur(1 + d, ctx->par));
+        g.psv[d] = ctx->field(ctx->cur(4 + d, ctx->par));
         g.psp[d] = ctx->field(7 + d);
         g.n[d] = ctx->n[d];
         g.lo[d] = ctx->lo[d];
@@ -615,11 +616,21 @@ int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
     ctx->step = 0;
     ctx->rec0 = 0;
     ctx->par = 0;
+    ctx->fixed = false;
     return FDTD_OK;
+}
+
+// Work captured by the caller is replayed with the buffers it was captured
+// with, any number of times and between other calls: from the first such call on
+// every call leaves the state in the buffers it found it in.
+static void note_capture(fdtd_pv_ctx *ctx) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (ctx->st && hipStreamIsCapturing(ctx->st, &c) == hipSuccess && c != hipStreamCaptureStatusNone) ctx->fixed = true;
 }
 
 static int pv_copy(fdtd_pv_ctx *ctx, float *dst, const float *src, int to_padded) {
     if (!ctx->ws) PVFAIL(ctx, FDTD_ESTATE, "no workspace bound");
+    note_capture(ctx);
     hipLaunchKernelGGL(k_pv_copy, dim3((ctx->n[0] + 255) / 256, ctx->n[1], ctx->n[2]), dim3(256), 0, ctx->st, dst,
                        src, ctx->n[0], ctx->n[1], ctx->P, ctx->S, to_padded);
     PVHIP(ctx, hipGetLastError());
@@ -716,11 +727,20 @@ static int pv_step_tile(fdtd_pv_ctx *ctx, int nsteps) {
 int fdtd_pv_step(fdtd_pv_ctx *ctx, int32_t nsteps) {
     if (!ctx || nsteps < 0) return FDTD_EINVAL;
     if (!ctx->ws) PVFAIL(ctx, FDTD_ESTATE, "no workspace bound");
-    if (ctx->tile) return pv_step_tile(ctx, nsteps);
+    note_capture(ctx);
+    if (ctx->tile) {
+        const int tiled = ctx->fixed ? nsteps & ~1 : nsteps;   // (the stages work in place)
+        const int rc = pv_step_tile(ctx, tiled);
+        if (rc) return rc;
+        nsteps -= tiled;
+    }
     const dim3 grid((ctx->n[0] + 63) / 64, (ctx->n[1] + 3) / 4, ctx->n[2]), block(64, 4);
     const dim3 zgrid((ctx->n[0] + 63) / 64, (ctx->n[1] + kTY - 1) / kTY, (ctx->n[2] + kZC - 1) / kZC),
         zblock(64, kNW);
-    const bool naive = ctx->c.variant == 1;
+    // automatic choice: the z-march from 2^24 points up (measured crossover between
+    // 224^3 and 256^3: below it its workgroups fill the chip in too few rounds)
+    const double npts = (double)ctx->n[0] * ctx->n[1] * ctx->n[2];
+    const bool naive = ctx->c.variant == 1 || (ctx->c.variant == 0 && npts < (double)(1L << 24));
     for (int s = 0; s < nsteps; ++s) {
         PvArgs g = pv_args(ctx);
         if (naive) {

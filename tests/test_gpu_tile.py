@@ -428,3 +428,35 @@ def test_graph_replays_take_a_new_source_and_model(cases):
         _same(got, _out(q, tq))
         q.close()
     p.close()
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_captured_first_order_steps_replay(first):
+    """Steps captured by the caller, replayed with eager steps of odd counts between, against eager steps alone; the
+    state lies in the first (0) or second (1) buffers when captured."""
+    import torch
+
+    from paper_2606_06910_amd import PVPropagator
+
+    n, cpml = (65, 33, 25), (10, 7, 5, 8, 6, 3)
+    p0 = torch.from_numpy(np.random.default_rng(8).standard_normal(n[::-1]).astype(np.float32)).cuda()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s, ref = PVPropagator(n, cpml, 0.3, stream=st), PVPropagator(n, cpml, 0.3, stream=st)
+        for q in (s, ref):
+            q.set_pressure(p0)
+            q.step(first)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s.step(3)
+        for eager in (0, 1, 2, 5):
+            g.replay()
+            s.step(eager)
+            ref.step(3 + eager)
+            torch.cuda.synchronize()
+            a, b = s.get_pressure().cpu().numpy(), ref.get_pressure().cpu().numpy()
+            assert np.abs(b).max() > 0 and np.array_equal(a, b)
+        del g
+        s.close()
+        ref.close()

@@ -114,3 +114,46 @@ def test_graph_kept_over_a_new_source_and_model(host, shots):
     assert host.stub_instantiated() == 1
     assert host.stub_launches(b"k_tile") == 10      # (captured once, by the tile kernel)
     p.close()
+
+
+class PV:
+    """One first-order context on host memory."""
+
+    def __init__(self, L, n, cpml=(5,) * 6, variant=0, less=0):
+        self.L = L
+        cfg = _lib.PVConfig()
+        cfg.n[:], cfg.cpml[:], cfg.lam, cfg.variant = n, cpml, 0.05, variant
+        self.c, self.stream = ctypes.c_void_p(), np.zeros(8, np.uint8)
+        assert L.fdtd_pv_create(ctypes.byref(cfg), _ptr(self.stream), ctypes.byref(self.c)) == 0
+        nb = ctypes.c_size_t()
+        assert L.fdtd_pv_workspace_size(self.c, ctypes.byref(nb)) == 0
+        self.size = nb.value
+        self.ws = _aligned(self.size)
+        self.bound = L.fdtd_pv_bind_workspace(self.c, _ptr(self.ws), ctypes.c_size_t(self.size - less))
+
+    def steps(self, k):
+        """(launches of the one-launch step, launches of the stages) of k steps."""
+        self.L.stub_reset()
+        assert self.L.fdtd_pv_step(self.c, k) == 0
+        return tuple(self.L.stub_launches(name) for name in (b"k_pv_tile", b"k_pv_vel"))
+
+    def close(self):
+        self.L.fdtd_pv_destroy(self.c)
+
+
+def test_captured_first_order_steps_end_in_the_buffers_they_began_in(host):
+    """The one-launch step alternates between two buffers; a captured call, and every call after it, must not leave the
+    state in the other one, where a replay would not find it."""
+    p = PV(host, (40, 30, 20))
+    assert p.bound == 0
+    assert p.steps(3) == (3, 0)
+    host.stub_capturing(1)
+    try:
+        assert p.steps(3) == (2, 1)
+        assert p.steps(1) == (0, 1)
+        assert p.steps(4) == (4, 0)
+    finally:
+        host.stub_capturing(0)
+    assert p.steps(1) == (0, 1)
+    assert p.steps(6) == (6, 0)
+    p.close()

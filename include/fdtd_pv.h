@@ -65,11 +65,14 @@ int fdtd_pv_create(const fdtd_pv_config *cfg, void *hip_stream, fdtd_pv_ctx **ou
 
 /* Bytes of device workspace: p, v_x, v_y, v_z and the six memory-variable
  * fields (each padded by 4 points on every side), a second buffer of p, v and
- * the three psi_v where both stages run in one launch, and the profiles. */
+ * the three psi_v where both stages run in one launch (17 fields in all), and
+ * the profiles. */
 int fdtd_pv_workspace_size(const fdtd_pv_ctx *ctx, size_t *bytes);
 
-/* Hand the context a device workspace of at least fdtd_pv_workspace_size
- * bytes, 256-byte aligned (ENOMEM if smaller, EINVAL if misaligned).  Zeroes
+/* Hand the context a device workspace of fdtd_pv_workspace_size bytes, 256-byte
+ * aligned (EINVAL if misaligned).  A smaller one is accepted, and stepped by the
+ * two stages, down to the size that a context of variant 1 or 2 asks for (ENOMEM
+ * below it).  Zeroes
  * every field and uploads the profiles; synchronises the stream. */
 int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes);
 

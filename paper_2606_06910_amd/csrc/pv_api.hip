@@ -453,10 +453,10 @@ struct fdtd_pv_ctx {
     int n[3] = {}, lo[3] = {}, hi[3] = {};
     int nmax = 0;
     long P = 0, S = 0;
-    size_t elems = 0, field_bytes = 0, prof_bytes = 0, total = 0;
+    size_t elems = 0, field_bytes = 0, prof_bytes = 0, total = 0, least = 0;   // least: workspace of the stages
     // one-launch step (k_pv_tile): p, v and psi_v in two buffers each (fields 0 .. 6 and kNF .. kNF + 6, `par`
-    // says which hold the state), and its box list
-    bool tile = false;
+    // says which hold the state), and its box list.  tile: taken, as the rule says (one) and the bound workspace holds
+    bool one = false, tile = false;
     int par = 0, nwork = 0, ninner = 0;
     bool fixed = false;   // a caller has captured work on the state: `par` stays as it is from call to call
     size_t o_prof = 0, o_work = 0, o_inner = 0;
@@ -560,15 +560,11 @@ int fdtd_pv_create(const fdtd_pv_config *cfg, void *hip_stream, fdtd_pv_ctx **ou
     ctx->field_bytes = a256(ctx->elems * 4);
     ctx->prof_bytes = a256((size_t)3 * 3 * ctx->nmax * 4);
     // (the automatic variant: the one launch wins at every size measured, 48^3 to 640^3)
-    ctx->tile = cfg->variant == 0 && ctx->field_bytes < ((size_t)1 << 31);
-    ctx->o_prof = (size_t)(ctx->tile ? kNF + 7 : kNF) * ctx->field_bytes;
-    ctx->o_work = ctx->o_prof + ctx->prof_bytes;
-    ctx->total = ctx->o_work;
-    if (ctx->tile) {
-        const size_t list = a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
-        ctx->o_inner = ctx->o_work + list;
-        ctx->total += 2 * list;
-    }
+    ctx->one = cfg->variant == 0 && ctx->field_bytes < ((size_t)1 << 31);
+    ctx->least = kNF * ctx->field_bytes + ctx->prof_bytes;
+    ctx->total = ctx->least;
+    if (ctx->one)
+        ctx->total += 7 * ctx->field_bytes + 2 * a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
     ctx->prof.assign((size_t)3 * 3 * ctx->nmax, 0.0f);
     for (int d = 0; d < 3; ++d) {
         float *base = ctx->prof.data() + (size_t)d * 3 * ctx->nmax;
@@ -588,8 +584,13 @@ int fdtd_pv_workspace_size(const fdtd_pv_ctx *ctx, size_t *bytes) {
 int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
     if (!ctx || !dev_ptr) return FDTD_EINVAL;
     if (((uintptr_t)dev_ptr) & 255) PVFAIL(ctx, FDTD_EINVAL, "workspace must be 256-byte aligned");
-    if (bytes < ctx->total) PVFAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, ctx->total);
+    if (bytes < ctx->least) PVFAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, %zu needed", bytes, ctx->least);
     ctx->ws = (char *)dev_ptr;
+    // a workspace that holds the ten fields alone is stepped by the two stages
+    ctx->tile = ctx->one && bytes >= ctx->total;
+    ctx->o_prof = (size_t)(ctx->tile ? kNF + 7 : kNF) * ctx->field_bytes;
+    ctx->o_work = ctx->o_prof + ctx->prof_bytes;
+    ctx->o_inner = ctx->o_work + a256(sizeof(TileItem) * tile_list_bound(ctx->grid().boxes()));
     const size_t n16 = (size_t)kNF * ctx->field_bytes / 16;
     hipLaunchKernelGGL(k_pv_zero, dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 65536)), dim3(256), 0, ctx->st,
                        (uint4 *)ctx->ws, n16);

@@ -35,18 +35,27 @@ class PVPropagator:
         cfg.cpml[:] = [int(x) for x in cpml]
         cfg.lam = float(lam)
         cfg.variant = int(variant)
-        ctx = ctypes.c_void_p()
-        self._check(self.L.fdtd_pv_create(ctypes.byref(cfg), ctypes.c_void_p(self.stream.cuda_stream),
-                                          ctypes.byref(ctx)), None)
-        self.ctx = ctx
-        nb = ctypes.c_size_t()
-        self._check(self.L.fdtd_pv_workspace_size(self.ctx, ctypes.byref(nb)))
-        self.ws_bytes = int(nb.value)
-        self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
+        self.ctx, self.ws_bytes = self._create(cfg)
+        try:
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:
+            # the automatic variant keeps 17 fields; a workspace of the stages' ten will do
+            cfg.variant = 1
+            stages, self.ws_bytes = self._create(cfg)
+            self.L.fdtd_pv_destroy(stages)
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
         off = (-self.ws.data_ptr()) % 256
         self._check(self.L.fdtd_pv_bind_workspace(self.ctx, ctypes.c_void_p(self.ws.data_ptr() + off),
                                                   self.ws_bytes))
         self._keep = {}
+
+    def _create(self, cfg: PVConfig):
+        """(context, bytes of workspace) of a configuration."""
+        ctx, nb = ctypes.c_void_p(), ctypes.c_size_t()
+        self._check(self.L.fdtd_pv_create(ctypes.byref(cfg), ctypes.c_void_p(self.stream.cuda_stream),
+                                          ctypes.byref(ctx)), None)
+        self._check(self.L.fdtd_pv_workspace_size(ctx, ctypes.byref(nb)), ctx)
+        return ctx, int(nb.value)
 
     def _check(self, rc: int, ctx="self") -> None:
         if rc == FDTD_OK:

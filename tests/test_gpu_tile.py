@@ -460,3 +460,45 @@ def test_captured_first_order_steps_replay(first):
         del g
         s.close()
         ref.close()
+
+
+def _tight(monkeypatch, least):
+    """Allocations of more bytes than `least` (a workspace, with its alignment) fail."""
+    import torch
+
+    empty = torch.empty
+
+    def tight(*size, **kw):
+        if kw.get("dtype") == torch.uint8 and size[0] > least:
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", tight)
+
+
+def test_first_order_grid_where_seventeen_fields_do_not_fit(monkeypatch):
+    """The automatic variant falls back to the stages' ten fields, with the same bits."""
+    import torch
+
+    from paper_2606_06910_amd import PVPropagator
+
+    n, cpml = (65, 33, 25), (10, 7, 5, 8, 6, 3)
+    p0 = torch.from_numpy(np.random.default_rng(9).standard_normal(n[::-1]).astype(np.float32)).cuda()
+    wav = torch.from_numpy(synth.ricker(14, 0.3, 0.2).astype(np.float32))
+    got = []
+    least = PVPropagator(n, cpml, 0.3, variant=1).ws_bytes
+    for tight in (False, True):
+        if tight:
+            _tight(monkeypatch, least + 256)
+        s = PVPropagator(n, cpml, 0.3)
+        assert (s.ws_bytes == least) == tight
+        s.set_pressure(p0)
+        s.set_source((3, 4, 5), wav)
+        tr = s.record(np.array([[5, 6, 7], [60, 30, 20]], np.int32), 9)
+        s.step(4)
+        s.step(5)
+        torch.cuda.synchronize()
+        got.append([s.get_pressure().cpu().numpy(), tr.cpu().numpy()])
+        s.close()
+    assert np.abs(got[0][0]).max() > 0
+    _same(*got)

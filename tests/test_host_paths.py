@@ -157,3 +157,18 @@ def test_captured_first_order_steps_end_in_the_buffers_they_began_in(host):
     assert p.steps(1) == (0, 1)
     assert p.steps(6) == (6, 0)
     p.close()
+
+
+def test_first_order_workspace_of_ten_fields(host):
+    """What holds the ten fields of the stages is accepted and stepped by them; one byte less is refused."""
+    n = (40, 30, 20)
+    least = PV(host, n, variant=1)
+    p = PV(host, n)
+    assert p.bound == 0 and p.steps(2) == (2, 0) and p.size > least.size
+    gap = p.size - least.size
+    q = PV(host, n, less=gap)
+    assert q.bound == 0 and q.steps(2) == (0, 2)
+    r = PV(host, n, less=gap + 1)
+    assert r.bound == -4
+    for c in (least, p, q, r):
+        c.close()

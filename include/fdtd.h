@@ -109,8 +109,10 @@ int fdtd_create(const fdtd_shot_config *shots, int32_t nshots, void *hip_stream,
  * profiles, exchange buffers).  256-byte aligned sub-buffers. */
 int fdtd_workspace_size(const fdtd_ctx *ctx, size_t *bytes);
 
-/* Hand the context a device workspace of at least fdtd_workspace_size bytes.
- * Borrowed: the caller keeps it alive until fdtd_destroy and frees it.
+/* Hand the context a device workspace of fdtd_workspace_size bytes.  A smaller
+ * one is accepted down to the size that the same shots ask for with the variants
+ * of fdtd_get_plan named explicitly, and stepped by those kernels; ENOMEM below
+ * it.  Borrowed: the caller keeps it alive until fdtd_destroy and frees it.
  * Zeroes the wavefields and layer memory (enqueued on the stream). */
 int fdtd_bind_workspace(fdtd_ctx *ctx, void *dev_ptr, size_t bytes);
 

@@ -514,11 +514,14 @@ static void fill_desc(fdtd_ctx *ctx, int i) {
 static int upload_desc(fdtd_ctx *ctx) {
     for (size_t i = 0; i < ctx->shots.size(); ++i) fill_desc(ctx, (int)i);
     // both descriptor arrays in one copy (the second follows the first in the workspace)
-    const size_t nd = sizeof(DevShot) * ctx->hdesc.size(), nt = sizeof(TileDesc) * ctx->htile.size(), at = align256(nd);
+    const size_t nd = sizeof(DevShot) * ctx->hdesc.size(), at = align256(nd);
+    const bool tiles = std::any_of(ctx->shots.begin(), ctx->shots.end(), [](const ShotH &s) { return s.tile; });
+    const size_t nt = tiles ? sizeof(TileDesc) * ctx->htile.size() : 0;
     std::vector<char> both(at + nt);
     memcpy(both.data(), ctx->hdesc.data(), nd);
     memcpy(both.data() + at, ctx->htile.data(), nt);
-    HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), both.data(), both.size(), hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(wsp(ctx, ctx->o_desc), both.data(), nt ? at + nt : nd, hipMemcpyHostToDevice,
+                               ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return FDTD_OK;
 }
@@ -1058,7 +1061,9 @@ static void layout(fdtd_ctx *ctx) {
     ctx->o_stepc = take(256);
     ctx->o_scratch = take(256);
     ctx->o_desc = take(sizeof(DevShot) * nshots);
-    ctx->o_tdesc = take(sizeof(TileDesc) * nshots);   // (upload_desc copies both at once)
+    bool tiles = false;
+    for (const auto &s : ctx->shots) tiles = tiles || s.tile;
+    ctx->o_tdesc = take(tiles ? sizeof(TileDesc) * nshots : 0);   // (upload_desc copies both at once)
     size_t cap_all = 0;
     for (auto &s : ctx->shots) cap_all += work_capacity(s) + 8;
     ctx->o_work_all = take(sizeof(WorkItem) * cap_all);
@@ -1090,7 +1095,8 @@ static void layout(fdtd_ctx *ctx) {
         for (int p = 0; p < 2; ++p)
             for (int ph = 0; ph < 4; ++ph) s.o_jobs[p][ph] = take(sizeof(CopyJob) * 16);
     }
-    ctx->o_fill = take(sizeof(FillJob) * 11 * nshots);
+    // (a lone shot's list fits behind the scratch words: without the tile kernels it needs no more than ever)
+    ctx->o_fill = nshots == 1 ? ctx->o_scratch + 64 : take(sizeof(FillJob) * 11 * nshots);
     size_t tile_all = 0;
     for (auto &s : ctx->shots) {
         const size_t own = nshots > 1 ? sizeof(TileItem) * tile_capacity(s) : 0;
@@ -1339,8 +1345,17 @@ int fdtd_bind_workspace(fdtd_ctx *ctx, void *dev_ptr, size_t bytes) {
         HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
         HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
     }
-    if (bytes < ctx->need) FAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, need %zu", bytes, ctx->need);
     if (((uintptr_t)dev_ptr) & 255) FAIL(ctx, FDTD_EINVAL, "workspace must be 256-byte aligned");
+    if (bytes < ctx->need) {
+        // what the other kernels fit is stepped by them
+        const std::vector<ShotH> as_planned = ctx->shots;
+        fdtd_disable_tile(ctx);
+        if (bytes < ctx->need) {
+            ctx->shots = as_planned;
+            layout(ctx);
+            FAIL(ctx, FDTD_ENOMEM, "workspace of %zu bytes, need %zu", bytes, ctx->need);
+        }
+    }
     ctx->ws = (char *)dev_ptr;
     ctx->ws_bytes = bytes;
     fdtd_clear_graphs(ctx);

@@ -71,19 +71,29 @@ class Propagator:
         self.shots = list(shots)
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
-        arr = (ShotConfig * len(shots))(*[s.c() for s in shots])
-        ctx = ctypes.c_void_p()
-        rc = self.L.fdtd_create(arr, len(shots), ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(ctx))
-        check(rc)
-        self.ctx = ctx
-        nb = ctypes.c_size_t()
-        check(self.L.fdtd_workspace_size(self.ctx, ctypes.byref(nb)), self.ctx)
-        self.ws_bytes = int(nb.value)
-        self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
+        self.ctx, self.ws_bytes = self._create([s.c() for s in shots])
+        try:
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
+        except torch.OutOfMemoryError:
+            # the one-launch step keeps a second copy of psi; the kernels of the reported plan do without
+            cfgs = [s.c() for s in shots]
+            for i, c in enumerate(cfgs):
+                c.variant = self.plan(i)[0]
+            other, self.ws_bytes = self._create(cfgs)
+            self.L.fdtd_destroy(other)
+            self.ws = torch.empty(self.ws_bytes + 256, dtype=torch.uint8, device=self.device)
         base = self.ws.data_ptr()
         off = (-base) % 256
         check(self.L.fdtd_bind_workspace(self.ctx, ctypes.c_void_p(base + off), self.ws_bytes), self.ctx)
         self._keep = {}
+
+    def _create(self, cfgs):
+        """(context, bytes of workspace) of shot configurations."""
+        ctx, nb = ctypes.c_void_p(), ctypes.c_size_t()
+        check(self.L.fdtd_create((ShotConfig * len(cfgs))(*cfgs), len(cfgs), ctypes.c_void_p(self.stream.cuda_stream),
+                                 ctypes.byref(ctx)))
+        check(self.L.fdtd_workspace_size(ctx, ctypes.byref(nb)), ctx)
+        return ctx, int(nb.value)
 
     # -- setup ---------------------------------------------------------------
     def set_velocity(self, shot: int, v: torch.Tensor) -> None:

@@ -502,3 +502,24 @@ def test_first_order_grid_where_seventeen_fields_do_not_fit(monkeypatch):
         s.close()
     assert np.abs(got[0][0]).max() > 0
     _same(*got)
+
+
+@pytest.mark.parametrize("cases", [GEOMETRIES[1:2], GEOMETRIES[:2]], ids=["one", "two"])
+def test_shots_where_a_second_psi_does_not_fit(monkeypatch, cases):
+    """The automatic variant falls back to the kernels of its reported plan, with the same bits."""
+    nt, got = 9, []
+    p, _, _ = _prop(cases, nt, [NAIVE if len(cases) == 1 else ZMARCH] * len(cases))
+    least = p.ws_bytes
+    p.close()
+    for tight in (False, True):
+        if tight:
+            _tight(monkeypatch, least + 256)
+        p, ws, tr = _prop(cases, nt, [AUTO] * len(cases))
+        assert (p.ws_bytes == least) == tight
+        _start(p, ws)
+        p.step(4)
+        p.step(5, graph=True)
+        got.append(_out(p, tr))
+        p.close()
+    assert np.abs(got[0][1]).max() > 0
+    _same(*got)

@@ -70,8 +70,9 @@ class Ctx:
         assert L.fdtd_create(arr, len(shots), None, ctypes.byref(self.c)) == 0
         nb = ctypes.c_size_t()
         assert L.fdtd_workspace_size(self.c, ctypes.byref(nb)) == 0
-        self.ws = _aligned(nb.value)
-        self.bound = L.fdtd_bind_workspace(self.c, _ptr(self.ws), ctypes.c_size_t(nb.value - less))
+        self.size = nb.value
+        self.ws = _aligned(self.size)
+        self.bound = L.fdtd_bind_workspace(self.c, _ptr(self.ws), ctypes.c_size_t(self.size - less))
         if self.bound != 0:
             return
         for i, (n, _) in enumerate(shots):
@@ -170,5 +171,30 @@ def test_first_order_workspace_of_ten_fields(host):
     assert q.bound == 0 and q.steps(2) == (0, 2)
     r = PV(host, n, less=gap + 1)
     assert r.bound == -4
+    for c in (least, p, q, r):
+        c.close()
+
+
+@pytest.mark.parametrize("shots,variant", [([((40, 36, 33), (8,) * 6)], 1),
+                                           ([((40, 36, 33), (8,) * 6), ((33, 40, 36), (6,) * 6)], 2)], ids=["one", "two"])
+@pytest.mark.parametrize("storage", [0, 1])
+def test_workspace_without_second_psi(host, shots, variant, storage):
+    """What holds the shots of the explicit variant is accepted for the automatic one and stepped by its kernels; one
+    byte less is refused, and the full size still takes the one launch."""
+    least = Ctx(host, shots, variant, storage)
+    p = Ctx(host, shots, 0, storage)
+    gap = p.size - least.size
+    assert p.bound == 0 and gap > 0
+    q = Ctx(host, shots, 0, storage, less=gap)
+    assert q.bound == 0
+    for c, tiled in ((least, 0), (p, 4), (q, 0)):
+        host.stub_reset()
+        assert host.fdtd_step(c.c, 4) == 0
+        assert host.stub_launches(b"k_tile") == tiled
+    r = Ctx(host, shots, 0, storage, less=gap + 1)
+    assert r.bound == -4
+    assert host.fdtd_bind_workspace(r.c, _ptr(r.ws), ctypes.c_size_t(r.size)) == 0
+    nb = ctypes.c_size_t()
+    assert host.fdtd_workspace_size(r.c, ctypes.byref(nb)) == 0 and nb.value == p.size
     for c in (least, p, q, r):
         c.close()

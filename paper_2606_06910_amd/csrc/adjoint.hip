@@ -734,6 +734,7 @@ static int adjoint_sweep(fdtd_ctx *ctx, const std::vector<int> &sh, int nt, cons
     const AdjTile *atab_d = (const AdjTile *)(s0h.ck_buf + L0.atab);
     const TileItem *items_d = (const TileItem *)(s0h.ck_buf + L0.items);
     const std::vector<TileItem> items = tile_list(grids);
+    if (items.size() * sizeof(TileItem) > L0.grp - L0.items) AFAIL(ctx, FDTD_EINVAL, "box list overflow");
     const AdjGroups *grp_d = (const AdjGroups *)(s0h.ck_buf + L0.grp);
     std::vector<AdjGroups> grp(items.size(), AdjGroups{0, 0});
     for (size_t i = 0; i < items.size() && !at_box.empty(); ++i) {

@@ -606,6 +606,10 @@ int fdtd_pv_bind_workspace(fdtd_pv_ctx *ctx, void *dev_ptr, size_t bytes) {
         const InnerBox ib{TILE_X, (double)ctx->n[0] * ctx->n[1] * ctx->n[2] >= kPvInner ? TILE_Z : 0};
         work = tile_list({ctx->grid()}, ib);
         inner = tile_list({ctx->grid()}, ib, TILE_INNER);
+        if (std::max(work.size(), inner.size()) > tile_list_bound(ctx->grid().boxes())) {
+            ctx->ws = nullptr;
+            PVFAIL(ctx, FDTD_EINVAL, "box list overflow");
+        }
         ctx->nwork = (int)work.size();
         ctx->ninner = (int)inner.size();
         PVHIP(ctx, hipMemcpyAsync(ctx->ws + ctx->o_inner, inner.data(), sizeof(TileItem) * inner.size(),

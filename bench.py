@@ -66,10 +66,15 @@ def band_split(n, cpml):
     return inner, N - inner
 
 
+def point_bytes(field_bytes=4):
+    """Algorithmic bytes of one point's update: u^n, u^{n-1}, m in and u^{n+1}
+    out in FP32 (16); u^n, d^n, m in and u^{n+1}, d^{n+1} out in 16-bit storage (12)."""
+    return 4 * field_bytes + 4 if field_bytes == 2 else 3 * field_bytes + 4
+
+
 def interior_kernel_bytes(n, cpml, field_bytes=4):
-    """Algorithmic bytes of one z-march launch (points outside every band):
-    read u^n, u^{n-1}, m and write u^{n+1} per point."""
-    return (3 * field_bytes + 4) * band_split(n, cpml)[0]
+    """Algorithmic bytes of one z-march launch (points outside every band)."""
+    return point_bytes(field_bytes) * band_split(n, cpml)[0]
 
 
 def band_kernel_bytes(n, cpml, field_bytes=4):
@@ -77,7 +82,7 @@ def band_kernel_bytes(n, cpml, field_bytes=4):
     in the kernel): the four arrays per band point, a read + write of zeta per
     layer point and axis, a read + write of psi_x and psi_z, a read of psi_y."""
     sx, sy, sz = (slab_points_axis(n, cpml, d) for d in range(3))
-    return (3 * field_bytes + 4) * band_split(n, cpml)[1] + 8 * (sx + sy + sz) + 8 * (sx + sz) + 4 * sy
+    return point_bytes(field_bytes) * band_split(n, cpml)[1] + 8 * (sx + sy + sz) + 8 * (sx + sz) + 4 * sy
 
 
 def psi_kernel_bytes(n, cpml, field_bytes=4):
@@ -87,9 +92,9 @@ def psi_kernel_bytes(n, cpml, field_bytes=4):
 
 
 def step_bytes(n, cpml, field_bytes=4):
-    """Algorithmic bytes of a whole step (16 B/point + 16 B per layer point-axis in FP32)."""
+    """Algorithmic bytes of a whole step (16 B/point in FP32, 12 in 16-bit storage, + 16 B per layer point-axis)."""
     N = n[0] * n[1] * n[2]
-    return (3 * field_bytes + 4) * N + 16 * slab_points(n, cpml)
+    return point_bytes(field_bytes) * N + 16 * slab_points(n, cpml)
 
 
 def inner_points(n, cpml, storage=0, total=None):
@@ -117,7 +122,7 @@ def tile_kernel_bytes(shapes, cpml, storage=0):
     total = sum(a * b * c for a, b, c in shapes)
     fb = 2 if storage else 4
     whole = sum(step_bytes(sh, cpml, fb) for sh in shapes)
-    inner = (3 * fb + 4) * sum(inner_points(sh, cpml, storage, total) for sh in shapes)
+    inner = point_bytes(fb) * sum(inner_points(sh, cpml, storage, total) for sh in shapes)
     return {"update": inner, "band": whole - inner} if inner else {"update": whole}
 
 
@@ -341,7 +346,7 @@ def precision_leg(K=200):
             kb = tile_kernel_bytes([(n, n, n)], (20,) * 6, st)
             out[name]["roofline"] = roofline(kb["update"], tm["update"][0], tile_names(st, len(kb) > 1)["update"])
         else:
-            nb = (16 if st == 0 else 12) * band_split((n, n, n), (20,) * 6)[0]
+            nb = interior_kernel_bytes((n, n, n), (20,) * 6, 4 if st == 0 else 2)
             out[name]["roofline"] = roofline(nb, tm["update"][0], "k_zmarch<%s> (points outside the layer bands)" %
                                              {0: "float", 1: "_Float16", 2: "__bf16"}[st])
         p.close()

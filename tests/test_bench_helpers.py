@@ -70,3 +70,22 @@ def test_adjoint_step_bytes_without_layers(every, G):
     n = (10, 12, 14)
     N = 10 * 12 * 14
     assert bench.adjoint_step_bytes(n, (0,) * 6, every) == pytest.approx(N * (16 + 12 + 16 + 8 + 16 / G))
+
+
+def test_sixteen_bit_points_are_12_bytes():
+    # u^n, d^n, m in, u^{n+1}, d^{n+1} out: 2 + 2 + 4 + 2 + 2
+    n = (283, 243, 237)
+    N = 283 * 243 * 237
+    assert bench.point_bytes(4) == 16 and bench.point_bytes(2) == 12
+    assert bench.step_bytes(n, (0,) * 6, 2) == 12 * N
+    assert bench.interior_kernel_bytes(n, (0,) * 6, 2) == 12 * N
+    kb = bench.tile_kernel_bytes([n], (10, 12, 9, 20, 15, 11), 1)
+    assert kb["update"] == 12 * bench.inner_points(n, (10, 12, 9, 20, 15, 11), 1)
+    assert sum(kb.values()) == 12 * N + 16 * bench.slab_points(n, (10, 12, 9, 20, 15, 11))
+
+
+def test_tile_launches_share_the_step_bytes():
+    n, cpml = (512, 512, 512), (20,) * 6
+    kb = bench.tile_kernel_bytes([n], cpml)
+    assert kb["update"] == 16 * bench.inner_points(n, cpml) and sum(kb.values()) == bench.step_bytes(n, cpml)
+    assert bench.tile_kernel_bytes([(64, 64, 64)], cpml) == {"update": bench.step_bytes((64, 64, 64), cpml)}

@@ -30,3 +30,21 @@ def test_tile_lists_brute_force(tmp_path, flags, cases):
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout + out.stderr
     inner, face = (int(v) for v in out.stdout.split()[2:4])
     assert inner > cases and face > cases      # every part was there to be checked
+
+
+def test_bench_inner_points_match_the_library(tmp_path):
+    """bench.py prices the interior's launch with its own count of the inner region, which must be the library's."""
+    import bench
+
+    cases = [(n, cp, st) for n in ((512, 512, 512), (480, 460, 456), (261, 243, 197), (611, 387, 453), (97, 200, 640),
+                                   (129, 250, 512), (300, 300, 300), (64, 1024, 300))
+             for cp in ((20,) * 6, (10, 12, 9, 20, 15, 11), (0, 20, 20, 0, 0, 20), (0,) * 6) for st in (0, 1)
+             if n[0] * n[1] * n[2] >= (16000000 if st else 12000000)]
+    line = []
+    for n, cp, st in cases:
+        deep = st == 0 and n[0] * n[1] * n[2] >= 100000000
+        line.append(" ".join(map(str, n + cp + (64 if st else 32, 16 if deep else 8))))
+    out = subprocess.run([_build(tmp_path), "inner"], input="\n".join(line), check=True, capture_output=True, text=True,
+                         timeout=60)
+    got = [int(v) for v in out.stdout.split()]
+    assert max(got) > 0 and got == [bench.inner_points(*c) for c in cases]

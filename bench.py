@@ -139,18 +139,34 @@ def tile_names(storage, split):
             "band": "k_tile<%s>%s (the other boxes)" % (t, " and k_face" if storage else "")}
 
 
+def grad_pass_bytes(every):
+    """Algorithmic bytes per point and step of the gradient pass: mu^{n+1} and
+    one increment per step, the FP64 accumulator read and written once per pass of
+    G <= 16 steps, a segment split evenly."""
+    passes = -(-every // 16)
+    return 8 + 16 / -(-every // passes)
+
+
+def adjoint_tile_step_bytes(n, cpml, every):
+    """Algorithmic bytes of one step of an FP32 adjoint sweep on the box
+    kernels: the recomputed forward step, which writes the level increment too;
+    the reverse step in one launch, which reads mu^{n+1}, mu^{n+2}, m and writes
+    mu^n on every point, and reads and writes zeta_b and psi_b on each axis' layer
+    points; and the gradient pass."""
+    N = n[0] * n[1] * n[2]
+    return step_bytes(n, cpml) + 4 * N + 16 * N + 16 * slab_points(n, cpml) + grad_pass_bytes(every) * N
+
+
 def adjoint_step_bytes(n, cpml, every):
-    """Algorithmic bytes of one step of an FP32 adjoint sweep: the recomputed
+    """The same where the reverse step takes three passes (a context with a
+    shot whose z layers are less than 20 planes apart): the recomputed
     forward step and its level increment (two levels read, one written); on
     each axis' layer points pass 1 (mu and zeta_b read; zeta_b, E and K
     written) and pass 2 (E and psi_b read; W and psi_b written); pass 3 on
     every point (mu^{n+1}, mu^{n+2}, m read; mu^n written); and the gradient
-    pass (mu^{n+1} and one increment per step, the FP64 accumulator read and
-    written once per pass of G <= 16 steps, a segment split evenly)."""
+    pass."""
     N = n[0] * n[1] * n[2]
-    passes = -(-every // 16)
-    G = -(-every // passes)
-    return step_bytes(n, cpml) + 12 * N + (20 + 16) * slab_points(n, cpml) + 16 * N + (8 + 16 / G) * N
+    return step_bytes(n, cpml) + 12 * N + (20 + 16) * slab_points(n, cpml) + 16 * N + grad_pass_bytes(every) * N
 
 
 def sweep_roofline(nbytes_per_step, steps, ms):
@@ -513,7 +529,7 @@ def adjoint_leg(nshots=3, K=600, every=25):
         f, a = run([d])
         one_f += f
         one_a += a
-    nb = sum(adjoint_step_bytes(w.n, w.cpml, every) for w, _ in data)
+    nb = sum(adjoint_tile_step_bytes(w.n, w.cpml, every) for w, _ in data)
     return {"shots": [list(shapes[i]) for i in order], "steps": K, "checkpoint_every": every,
             "forward_with_checkpoints_mpts": round(npts * K / (fwd_ms / 1e3) / 1e6, 1),
             "adjoint_mpts": round(npts * K / (adj_ms / 1e3) / 1e6, 1),
@@ -663,7 +679,7 @@ def batched_fwd_adj_leg(K=600, every=25, nshots=24):
     gnorm = float(torch.sqrt(sum((g * g).sum() for g in grads)))
     finite = all(bool(torch.isfinite(g).all()) for g in grads)
     p.close()
-    nb = sum(adjoint_step_bytes(w.n, w.cpml, every) for w, _ in data)
+    nb = sum(adjoint_tile_step_bytes(w.n, w.cpml, every) for w, _ in data)
     return {"shots": nshots, "points": npts, "steps": K, "checkpoint_every": every, "receivers_per_shot": 64,
             "forward_with_checkpoints_mpts": round(npts * K / (fwd_ms / 1e3) / 1e6, 1),
             "gradient_mpts": round(npts * K / (adj_ms / 1e3) / 1e6, 1),

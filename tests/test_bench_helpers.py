@@ -89,3 +89,13 @@ def test_tile_launches_share_the_step_bytes():
     kb = bench.tile_kernel_bytes([n], cpml)
     assert kb["update"] == 16 * bench.inner_points(n, cpml) and sum(kb.values()) == bench.step_bytes(n, cpml)
     assert bench.tile_kernel_bytes([(64, 64, 64)], cpml) == {"update": bench.step_bytes((64, 64, 64), cpml)}
+
+
+@pytest.mark.parametrize("every,G", [(1, 1), (16, 16), (17, 9), (25, 13)])
+def test_adjoint_tile_step_bytes(every, G):
+    # per point: forward step 16 B with its increment 4 B, reverse step 16 B, gradient pass 8 + 16 / G B; per layer point
+    # and axis: psi and zeta, then psi_b and zeta_b, each read and written, 16 B each
+    n, cpml = (40, 42, 44), (5, 6, 0, 7, 8, 9)
+    N = 40 * 42 * 44
+    slab = 11 * 42 * 44 + 7 * 40 * 44 + 17 * 40 * 42
+    assert bench.adjoint_tile_step_bytes(n, cpml, every) == pytest.approx(N * (16 + 4 + 16 + 8 + 16 / G) + 32 * slab)

@@ -505,23 +505,13 @@ template <typename T> struct Buf2 {
     static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
         __builtin_amdgcn_raw_buffer_store_b32(narrow(v), r, vo, so, kStoreNT);
     }
-    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
-        __builtin_amdgcn_raw_buffer_store_b32(narrow(v), r, vo, so, 0);
-    }
 };
 template <> struct Buf2<float> {
-    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ float2 ld(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
     }
     static __device__ __forceinline__ float2 ldnt(Rsrc r, uint32_t vo, uint32_t so) {
         return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, kLoadNT));
-    }
-    static __device__ __forceinline__ void st(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vo, so, kStoreNT);
-    }
-    static __device__ __forceinline__ void stc(Rsrc r, uint32_t vo, uint32_t so, float2 v) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vo, so, 0);
     }
 };
 

@@ -638,16 +638,17 @@ __global__ __launch_bounds__(256, 4) void k_tile(const DevShot *__restrict__ sho
     tile_box<T, AX_ANY, NT, INC>(shot_desc<ONE>(descs, wi), wi, A, stepc, lds);
 }
 
-// launch f(ONE, NT, INC as std::bool_constant); only FP32 fields have increments
+// launch f(ONE, NT, INC as std::bool_constant); only FP32 fields have the non-temporal build and increments
 template <typename T, typename F>
 static void with_flags(bool one, bool nt, bool inc, F f) {
-    auto b = [&](auto ONE, auto NT) {
+    auto a = [&](auto ONE) {
         if constexpr (!IsInc<T>::v) {
-            if (inc) return f(ONE, NT, std::true_type{});
+            auto b = [&](auto NT) { inc ? f(ONE, NT, std::true_type{}) : f(ONE, NT, std::false_type{}); };
+            nt ? b(std::true_type{}) : b(std::false_type{});
+        } else {
+            f(ONE, std::false_type{}, std::false_type{});
         }
-        f(ONE, NT, std::false_type{});
     };
-    auto a = [&](auto ONE) { nt ? b(ONE, std::true_type{}) : b(ONE, std::false_type{}); };
     one ? a(std::true_type{}) : a(std::false_type{});
 }
 

@@ -523,3 +523,60 @@ def test_shots_where_a_second_psi_does_not_fit(monkeypatch, cases):
         p.close()
     assert np.abs(got[0][1]).max() > 0
     _same(*got)
+
+
+def _single_naive(cases, nt, storage):
+    out = []
+    for c in cases:
+        p, ws, tr = _prop([c], nt, [NAIVE], storage)
+        _start(p, ws)
+        p.step(nt)
+        out += _out(p, tr)
+        p.close()
+    return out
+
+
+@pytest.mark.parametrize("storage", [1, 2])
+@pytest.mark.parametrize("cases", [
+    GEOMETRIES,                                                                               # k_tile alone
+    [((220, 190, 200), (15,) * 6), ((240, 200, 180), (15, 10, 0, 9, 20, 15))],                # all three launches
+    LARGE16[:1],                                                                              # a lone shot's graph
+], ids=["small", "large", "lone"])
+def test_sixteen_bit_batch_equals_single_shots(cases, storage):
+    """16-bit shots of one context (descriptors by the items' shot), eager and as a graph that is replayed, against each
+    alone on the naive kernel."""
+    nt = 4
+    single = _single_naive(cases, nt, storage)
+    p, ws, tr = _prop(cases, nt, [AUTO] * len(cases), storage)
+    for graph in (False, True, True):
+        for t in tr:
+            t.zero_()
+        _start(p, ws)
+        p.step(nt, graph=graph)
+        _same(_out(p, tr), single)
+    p.close()
+
+
+def test_gradients_of_a_context_with_tile_and_other_shots():
+    """Batched sweep over tile, naive and z-march shots (their increments in a pass of its own, the tile shots stepped by
+    k_tile all the same) and each shot's own sweep, against a context of naive shots."""
+    import torch
+
+    nt = 13
+    cases = [GEOMETRIES[0], GEOMETRIES[1], GEOMETRIES[4], GEOMETRIES[9]]
+    got = []
+    for variants in ([AUTO, NAIVE, ZMARCH, AUTO], [NAIVE] * 4):
+        p, ws, tr = _prop(cases, nt, variants)
+        for i in range(4):
+            p.set_checkpointing(i, 5, nt)
+        p.reset()
+        p.step(nt)
+        g = torch.Generator().manual_seed(6)
+        resid = [torch.randn(nt, 12, generator=g) for _ in cases]
+        grads = p.adjoint_all(nt, resid) + [p.adjoint(i, nt, resid[i]) for i in range(4)]
+        got.append([x.cpu().numpy() for x in tr + grads])
+        p.close()
+    assert all(np.abs(x).max() > 0 for x in got[0])
+    for i in range(4):
+        assert np.array_equal(got[0][4 + i], got[0][8 + i])
+    _same(*got)

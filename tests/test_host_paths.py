@@ -198,3 +198,29 @@ def test_workspace_without_second_psi(host, shots, variant, storage):
     assert host.fdtd_workspace_size(r.c, ctypes.byref(nb)) == 0 and nb.value == p.size
     for c in (least, p, q, r):
         c.close()
+
+
+# points at which a launch of its own for the interior begins: 1.2e7 in FP32, 1.6e7 in 16-bit storage (and k_face with it)
+@pytest.mark.parametrize("shots,storage,launches", [
+    ([((261, 243, 197), (10, 12, 9, 20, 15, 11))], 0, (1, 0, 1)),
+    ([((256, 240, 200), (0, 20, 20, 0, 0, 20))], 0, (1, 0, 1)),
+    ([((97, 200, 640), (20, 20, 90, 90, 20, 20))], 0, (1, 0, 1)),
+    ([((261, 243, 197), (10, 12, 9, 20, 15, 11))], 1, (0, 0, 1)),
+    ([((250, 240, 199), (20,) * 6)], 0, (0, 0, 1)),
+    ([((283, 243, 237), (10, 12, 9, 20, 15, 11))], 1, (1, 1, 1)),
+    ([((160, 170, 640), (20, 20, 70, 70, 20, 20))], 2, (1, 1, 1)),
+    ([((129, 250, 512), (20, 2, 20, 20, 20, 20))], 2, (0, 1, 1)),     # no box fits between the x bands
+    ([((180, 190, 200), (15,) * 6), ((200, 170, 180), (15, 10, 0, 9, 20, 15))], 0, (1, 0, 1)),
+    ([((220, 190, 200), (15,) * 6), ((240, 200, 180), (15, 10, 0, 9, 20, 15))], 1, (1, 1, 1)),
+    ([((220, 190, 200), (15,) * 6), ((240, 200, 180), (15, 10, 0, 9, 20, 15))], 2, (1, 1, 1)),
+])
+def test_launches_of_a_step(host, shots, storage, launches):
+    """Which of k_inner, k_face and k_tile a step of these shots takes: the grids whose bits the GPU tests compare are
+    those that reach the launches."""
+    p = Ctx(host, shots, storage=storage)
+    assert p.bound == 0
+    host.stub_reset()
+    assert host.fdtd_step(p.c, 1) == 0
+    assert tuple(host.stub_launches(k) for k in (b"k_inner", b"k_face", b"k_tile")) == launches
+    assert all(host.stub_blocks(k) > 0 for k, n in zip((b"k_inner", b"k_face", b"k_tile"), launches) if n)
+    p.close()

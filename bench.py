@@ -12,6 +12,7 @@ Prints one JSON line.  With --gpus above 1 it exits: the library runs on one GPU
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -280,14 +281,21 @@ TILE_SOURCES = ("paper_2606_06910_amd/csrc/kernels_tile.hip", "paper_2606_06910_
                 "paper_2606_06910_amd/csrc/tile_host.hpp", "paper_2606_06910_amd/csrc/fdtd_dev.hpp")
 
 
+def code_only(text):
+    """C++ source without its comments, blank lines and trailing blanks."""
+    text = re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S)
+    return "\n".join(line.rstrip() for line in text.split("\n") if line.strip())
+
+
 def sources_digest(sources=ZMARCH_SOURCES):
-    """sha256 over a kernel's source files (identifies the kernel the counters were taken on)."""
+    """sha256 over the code of a kernel's source files, comments left out
+    (identifies the kernel the counters were taken on)."""
     import hashlib
 
     h = hashlib.sha256()
     for f in sources:
-        with open(os.path.join(ROOT, f), "rb") as fh:
-            h.update(fh.read())
+        with open(os.path.join(ROOT, f)) as fh:
+            h.update(code_only(fh.read()).encode())
     return h.hexdigest()
 
 
@@ -578,8 +586,6 @@ def batched_leg(K=600, nshots=24):
         return e0.elapsed_time(e1)
 
     pb = Propagator(shots)
-    setup(pb, range(nshots))
-    pb.autotune(os.path.join(ROOT, "paper_2606_06910_amd", "autotune_cache.json"))
     setup(pb, range(nshots))
     ms_b = timed(pb, K)
     # per-kernel durations (eager, the kernels of a step one after another) and

@@ -233,13 +233,17 @@ int fdtd_adjoint(fdtd_ctx *ctx, int32_t shot, int32_t nt, const float *resid_dev
  * undefined; keeps the step count. */
 int fdtd_adjoint_batch(fdtd_ctx *ctx, int32_t nt, const float *const *resid_dev, double *const *grad_v_dev);
 
-/* Time candidate kernel shapes / temporal-block depths for every shot on
- * this device and keep the fastest per shape bucket; results are merged into
- * the JSON cache at cache_path (NULL = no file).  Synchronises; leaves the
- * wavefields reset. */
+/* Time candidate z-march shapes for every shot that takes the z-march (ghost
+ * faces, or FDTD_VARIANT_ZMARCH) on this device and keep the fastest per shape
+ * bucket; results are merged into the JSON cache at cache_path (NULL = no file).
+ * The naive kernel and the one-launch step of automatic shots without ghost
+ * faces have one shape: such shots are left as they are and add nothing to the
+ * cache.  Synchronises; leaves the wavefields reset. */
 int fdtd_autotune(fdtd_ctx *ctx, const char *cache_path);
 
-/* Fix the kernel plan of one shot by hand (what fdtd_autotune chooses):
+/* Fix the kernel plan of one shot by hand (what fdtd_autotune chooses).  An
+ * automatic shot on the one-launch step leaves it for the kernels named here, for
+ * good (the automatic variant cannot be set again; measured up to 3 x slower):
  * variant (naive / z-march / temporal blocking), z-march tile height
  * (tile_ry 1, 2, 4 or 8: tiles of 8*tile_ry rows), x points per lane
  * (tile_cols 1: tiles 64 wide; 2: tiles 128 wide with paired loads, tile_ry
@@ -250,7 +254,9 @@ int fdtd_set_plan(fdtd_ctx *ctx, int32_t shot, int32_t variant, int32_t tile_ry,
                   int32_t tile_cols);
 
 /* Choice made for one shot: variant, tile height (tile_ry), temporal depth,
- * x points per lane (tile_cols).  Any output pointer may be NULL. */
+ * x points per lane (tile_cols).  Any output pointer may be NULL.  For an
+ * automatic shot on the one-launch step this is the plan that it replaces, and
+ * that the shot takes in a workspace too small for the one-launch step. */
 int fdtd_get_plan(const fdtd_ctx *ctx, int32_t shot, int32_t *variant, int32_t *tile_ry, int32_t *tblock_k,
                   int32_t *tile_cols);
 
@@ -260,16 +266,20 @@ int fdtd_get_scale(const fdtd_ctx *ctx, int32_t shot, double *scale);
 /* Per-kernel timing for measurement: while enabled (eager fdtd_step only;
  * fdtd_step_graph returns FDTD_EUNSUPPORTED), every launch of the kernel
  * classes below is bracketed by HIP events on the context's stream, and the
- * kernels of a step run one after another (otherwise the interior update
- * runs on a second stream, concurrently with the psi pass and the band
- * kernels), so that each duration is the kernel's own.
+ * kernels of a step run one after another (otherwise the z-march runs on a
+ * second stream, concurrently with the psi pass and the band kernels), so that
+ * each duration is the kernel's own.
  * fdtd_get_timing synchronises, returns the mean duration (ms) and count of
  * one class since timing was enabled, and keeps accumulating.
  * Classes: 0 = single-step update of the points outside the layer bands
- * (z-march kernel; the naive kernel updates every point), 1 = psi pre-pass,
- * 2 = receiver gather, 3 = ghost pack/unpack, 4 = update of the layer-band
- * points, 5 = temporal-blocking kernel (K steps of the interior box per
- * launch).  Enabling again clears the counters. */
+ * (z-march kernel; the naive kernel updates every point; of automatic shots
+ * without ghost faces the interior's launch, or the one launch that does the
+ * whole step), 1 = psi pre-pass (none in those), 2 = receiver gather (in those
+ * after the last step of a call and every 256th: a step's launch records the step
+ * before), 3 = ghost pack/unpack, 4 = update of the layer-band points (in those
+ * the launch or two launches of the boxes that the interior's leaves),
+ * 5 = temporal-blocking kernel (K steps of the interior box per launch).
+ * Enabling again clears the counters. */
 int fdtd_set_timing(fdtd_ctx *ctx, int32_t enable);
 int fdtd_get_timing(fdtd_ctx *ctx, int32_t kernel_class, double *mean_ms, int64_t *count);
 

@@ -99,3 +99,15 @@ def test_adjoint_tile_step_bytes(every, G):
     N = 40 * 42 * 44
     slab = 11 * 42 * 44 + 7 * 40 * 44 + 17 * 40 * 42
     assert bench.adjoint_tile_step_bytes(n, cpml, every) == pytest.approx(N * (16 + 4 + 16 + 8 + 16 / G) + 32 * slab)
+
+
+def test_sources_digest_is_of_the_code(tmp_path, monkeypatch):
+    """Counters stay valid over an edit of comments and go stale with any of the code."""
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    f = tmp_path / "k.hip"
+    f.write_text("// 54 registers\nint a; /* two\n lines */ int b;   // tail\n")
+    first = bench.sources_digest(("k.hip",))
+    f.write_text("// 52 registers, 2 MB\n\nint a; /* one */ int b;\n")
+    assert bench.sources_digest(("k.hip",)) == first
+    f.write_text("// 54 registers\nint a; int c;\n")
+    assert bench.sources_digest(("k.hip",)) != first

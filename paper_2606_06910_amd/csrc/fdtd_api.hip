@@ -294,8 +294,9 @@ static bool tile_rule(const ShotH &s) {
 }
 // How the tile shots of a context of `points` points in all are stepped: k_inner's
 // boxes (z = 0: k_tile takes every box, one launch), and nt, k_tile's non-temporal
-// hint.  A launch of its own for the points outside the bands
-// (54 instead of 115 VGPRs, 8 instead of 4 waves per SIMD) costs one launch more;
+// hint.  A launch of its own for the points outside the bands (8 planes deep 52
+// VGPRs and eight blocks per CU, 16 deep 84 and four, against k_tile's 114 and four)
+// costs one launch more;
 // us per step without it / with boxes of 8 / of 16 planes, FP32: 160^3 30.3 / 34.7
 // / 35.8, 200^3 52.9 / 56.1 / 57.1, 256^3 106 / 106 / 106, 384^3 294 / 277 / 278,
 // 512^3 650 / 617 / 613, 768^3 - / 1908 / 1887.  In 16-bit storage the boxes are 64
@@ -305,6 +306,12 @@ static bool tile_rule(const ShotH &s) {
 // 256 MiB last-level cache: FP32 200^3 52.9 -> 59.9, 256^3 108.5 -> 105.5, 512^3 640
 // -> 617; not in 16-bit storage, where a row of k_tile's box is half a line and its
 // stores have to meet their other half in L2 (512^3 640 -> 687).
+// A step of a batch is one launch of each kind over all shots, so the sum over the
+// shots decides, not their size; us per step by the sum / by the largest shot: FP32
+// 64 of 64^3 146 / 151, 24 of 96^3 173 / 171, 8 of 128^3 136 / 140, 8 of 160^3 219 /
+// 222, 4 of 200^3 227 / 230; FP16 24 of 96^3 183 / 176, 8 of 160^3 242 / 228.  The
+// recomputed steps of one shot's gradient follow it too: 121 x 133 x 122 out of 24
+// shots, 50 steps, 3.03 ms against 2.90.
 static void tile_plan(long points, int storage, InnerBox &inner, bool &nt) {
     const bool large = points >= (storage == FDTD_F32 ? 12000000 : 16000000);
     inner.x = storage == FDTD_F32 ? TILE_X : 2 * TILE_X;

@@ -20,10 +20,10 @@
 // points, 100 steps, 5.45 -> 4.68 ms; of three shots of 7.7 M, 24.0 -> 22.2 ms.
 //
 // What bounds it: instruction issue and load latency at four waves per SIMD, as
-// in k_tile (118 VGPRs, 31 KB of LDS: E is turned into K where it lies, which
+// in k_tile (119 VGPRs, 31 KB of LDS: E is turned into K where it lies, which
 // costs two barriers and saves 13 KB).  Three batched shots of 7.7 M points in
 // all (15-cell layers, 64 % of the points in a band): the three passes 36 + 46 +
-// 89 us, this kernel 84 us per reverse step (1.5 TB/s of its algorithmic bytes);
+// 89 us, this kernel 84 us per reverse step (0.26 GB counted: 3.1 TB/s);
 // one shot of 0.89 M points: 8.5 + 8.9 + 18 -> 19 us.
 #include "adj_tile.hpp"
 #include "tile_dev.hpp"

@@ -14,9 +14,10 @@
 // recorded by extra blocks of the next step's launch.
 //
 // What bounds it: at 64^3 (one block per CU) the chain of one block: launch,
-// list item, loads, two barriers, stores; from 128^3 up instruction issue (118
-// VALU and 78 scalar instructions per plane of 64 points on a 160^3 grid with
-// 20-cell layers) and the load latency that four waves per SIMD leave open.
+// list item, loads, two barriers, stores; from 128^3 up instruction issue (117
+// VALU and 90 scalar instructions per plane of 64 points on a 160^3 grid with
+// 20-cell layers, VALU busy 33 % of the time) and the load latency that four waves
+// per SIMD leave open.
 // Why this box: 32 points are a 128-byte line; 4 planes keep the column (20
 // planes of u^n), its old psi and the second state within 114 VGPRs and the
 // three LDS arrays within 31 KB, so that four blocks share a CU; asking for
@@ -381,12 +382,13 @@ __device__ __forceinline__ void tile_box(const ConstDesc &s, const TileItem &wi,
 // FP32 boxes of TX x TY x IZ points outside every band and wholly inside the grid
 // (TileItem flags: the shot only): u^{n+1} alone, from the box's column and an
 // LDS box with a 4-point halo along x and y.  Bound by HBM: 512^3 with 20-cell
-// layers, 97 M points in 336 us, 4.6 TB/s of the 16 bytes a point cannot do
-// without, 5.4 TB/s counted (u^n is fetched 1.7 times: whole lines at the bricks'
-// x faces); the z-march takes 585 us for them on the half of the CUs the band
-// kernel leaves it, and 345 us on all.  Boxes of 8 planes hold 54 VGPRs and 20 KB
-// of LDS: eight blocks per CU, the memory's latency hidden by other blocks
-// instead of a register queue along z.
+// layers, 96 M points in 333 us, 4.6 TB/s of the 16 bytes a point cannot do
+// without, 5.3 TB/s counted (u^n is fetched 1.57 times: whole lines at the bricks'
+// x faces); the z-march takes 586 us for them on the half of the CUs the band
+// kernel leaves it, and 345 us on all.  The memory's latency is hidden by other
+// blocks and not by a register queue along z: boxes of 16 planes, which 512^3
+// takes, hold 84 VGPRs and 40 KB of LDS, four blocks per CU, those of 8 planes 52
+// and 20 KB, eight.
 template <int IZ, bool INC>
 __device__ __forceinline__ void inner_box(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                           const int *__restrict__ stepc) {
@@ -477,7 +479,8 @@ __device__ __forceinline__ void inner_box(const ConstDesc &s, const TileItem &wi
 // points took two, and a row of the box is one whole line, which the non-temporal
 // stores need.  611 x 387 x 453 BF16, 16-cell layers: 68 M points in 280 us (boxes 32
 // wide) -> 178 us for 69 M (12 bytes a point: 4.6 TB/s); 768^3 FP16 332 M points in
-// 858 us.  94 VGPRs and 37 KB of LDS (FP32, read eight bytes at a time): four blocks per CU.
+// 866 us (4.6 TB/s, 5.3 counted).  94 VGPRs (BF16: 103) and 37 KB of LDS (FP32, read
+// eight bytes at a time): four blocks per CU.
 template <typename T, int IZ>
 __device__ __forceinline__ void inner_pair(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                            const int *__restrict__ stepc) {
@@ -596,7 +599,7 @@ __global__ __launch_bounds__(256) void k_inner(const TileDesc *__restrict__ desc
 // and instruction issue, and that pays: 768^3 FP16 35.9 -> 34.9 ms for 20 steps, 611 x
 // 387 x 453 BF16 20.4 -> 19.8 ms for 40.  In FP32 it does not (512^3 283 us for k_tile
 // alone, 227 + 56 for both; 24 batched shots 864, 544 + 337): its boxes already move
-// 4.5 to 5 TB/s, counted, at four blocks per CU.
+// 4.4 to 4.8 TB/s, counted, at four blocks per CU.
 template <typename T>
 __device__ __forceinline__ void face_box(const ConstDesc &s, const TileItem &wi, const TileStep &A,
                                          const int *__restrict__ stepc, float *lds) {

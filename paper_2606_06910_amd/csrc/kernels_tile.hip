@@ -25,7 +25,7 @@
 // before the first wait, and one buffer descriptor covers the whole shot
 // (seven of them, and tests kept in scalar register pairs, cost 30 scalar
 // spills and 10 %).  Per step, before (psi passes, naive or z-march and band
-// kernels, record) and after: 64^3 19.5 -> 8.2 us, 101 x 87 x 119 (eager) 38 ->
+// kernels, record) and after: 64^3 19.5 -> 8.0 us, 101 x 87 x 119 (eager) 38 ->
 // 14 us, 160^3 100 -> 29 us (142 Gpts/s, 4.0 TB/s of the algorithmic bytes), 24
 // batched shots of 96 .. 288 points per axis, with k_inner, 1.45 -> 1.14 ms.
 #include "fdtd_launch.hpp"

@@ -74,11 +74,11 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **, size_t, hipS
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
-    memcpy(d, s, n);
+    if (n > 0) memcpy(d, s, n);
     return hipSuccess;
 }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
-    memcpy(d, s, n);
+    if (n > 0) memcpy(d, s, n);
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
